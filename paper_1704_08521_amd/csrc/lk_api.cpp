@@ -586,7 +586,7 @@ int lc_get_base_flow(lc_ctx* c, double* U, double* P) {
     double* tmp = nullptr;
     long ld = 0;
     if ((rc = krylov_ws(c, 1, &tmp, &ld))) return rc;
-    KLAUNCH(c, LC_K_RESIDUAL, launch_momentum(c->g, c->U, c->U, c->w, 1.0 / c->re, 0.5, true, std::cos(c->alpha),
+    KLAUNCH(c, LC_K_RESIDUAL, launch_momentum(c->g, c->U, c->U, c->w, 1.0 / c->re, true, std::cos(c->alpha),
                                               std::sin(c->alpha), c->stream));
     lc_stats st;
     rc = lc_project(c, c->w, tmp, P, LC_FP64, 1e-13, 4, &st);
@@ -600,7 +600,7 @@ int lc_jacobian_apply(lc_ctx* c, const double* v, double* w) {
   int rc = check_ready(c);
   if (rc) return rc;
   if (!aligned(v) || !aligned(w) || v == w) return fail(c, LC_EINVAL, "bad or aliased velocity pointers");
-  KLAUNCH(c, LC_K_MOMENTUM, launch_momentum(c->g, c->U, v, w, 1.0 / c->re, 1.0, false, 0, 0, c->stream));
+  KLAUNCH(c, LC_K_MOMENTUM, launch_momentum(c->g, c->U, v, w, 1.0 / c->re, false, 0, 0, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return LC_OK;
 }
@@ -609,7 +609,7 @@ int lc_residual(lc_ctx* c, const double* U, double* R) {
   int rc = check_ready(c);
   if (rc) return rc;
   if (!aligned(U) || !aligned(R) || U == R) return fail(c, LC_EINVAL, "bad or aliased velocity pointers");
-  KLAUNCH(c, LC_K_RESIDUAL, launch_momentum(c->g, U, U, R, 1.0 / c->re, 0.5, true, std::cos(c->alpha), std::sin(c->alpha),
+  KLAUNCH(c, LC_K_RESIDUAL, launch_momentum(c->g, U, U, R, 1.0 / c->re, true, std::cos(c->alpha), std::sin(c->alpha),
                             c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return LC_OK;
@@ -772,7 +772,7 @@ int lc_krylov_vector(lc_ctx* c, const double* vin, double* vout, double* pout, i
   if (rc) return rc;
   if (!aligned(vin) || !aligned(vout) || vin == vout) return fail(c, LC_EINVAL, "bad or aliased pointers");
   const size_t rec0 = c->recs.size();
-  KLAUNCH(c, LC_K_MOMENTUM, launch_momentum(c->g, c->U, vin, c->w, 1.0 / c->re, 1.0, false, 0, 0, c->stream));
+  KLAUNCH(c, LC_K_MOMENTUM, launch_momentum(c->g, c->U, vin, c->w, 1.0 / c->re, false, 0, 0, c->stream));
   rc = project_impl(c, c->w, vout, pout, precision, tol, max_iter, st);
   if (rc >= 0) fill_phases(c, st, rec0);
   if (st) st->ms_total = now_ms() - t0;

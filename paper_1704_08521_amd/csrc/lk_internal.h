@@ -44,11 +44,10 @@ inline VelLayout vel_layout(int nx, int ny, int nz) {
 // ------------------------------------------------------------ launchers
 // All launchers enqueue on `s` and return the launch status.
 
-// out = rre * Lap_g(b) - s * [C(a, b) + C(b, a)], lid only if `lid` is set.
-// Jacobian: a = U, b = v, s = 1, lid off.  Residual: a = b = U, s = 1/2, lid on.
+// out = rre * Lap_g(b) - s * [C(a, b) + C(b, a)].
+// Jacobian: a = U, b = v, lid off, s = 1.  Residual: a = b = U, lid on, s = 1/2.
 hipError_t launch_momentum(const GridDev& g, const double* a, const double* b, double* out,
-                           double rre, double s, bool lid, double lid_u, double lid_v,
-                           hipStream_t st);
+                           double rre, bool lid, double lid_u, double lid_v, hipStream_t st);
 
 // r = D v (cell), and per-block partial sums of V r^2 into `partials`
 // (nblocks returned through *nparts; partials may be null).

@@ -513,7 +513,7 @@ extern "C" int lc_newton_residual(lc_ctx* c, double* F, double* res_inf) {
   int rc = check_ready(c);
   if (rc) return rc;
   if (!F || !aligned(F) || !res_inf) return fail(c, LC_EINVAL, "bad pointers");
-  KLAUNCH(c, LC_K_RESIDUAL, launch_momentum(c->g, c->U, c->U, c->w, 1.0 / c->re, 0.5, true, std::cos(c->alpha),
+  KLAUNCH(c, LC_K_RESIDUAL, launch_momentum(c->g, c->U, c->U, c->w, 1.0 / c->re, true, std::cos(c->alpha),
                                             std::sin(c->alpha), c->stream));
   lc_stats st;
   rc = lc_project(c, c->w, F, nullptr, LC_FP64, 1e-13, 4, &st);

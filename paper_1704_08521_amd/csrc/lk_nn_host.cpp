@@ -507,7 +507,7 @@ int lc_net_train(lc_ctx* c, lc_net* n, int steps, double lr, uint64_t seed, doub
       HIPCHK(c, launch_zero_walls(rs, c->nx, c->ny, c->nz, c->stream));
       int r2 = lc_project(c, rs, v, nullptr, LC_FP64, 1e-10, 3, nullptr);
       if (r2 < 0) return r2;
-      KLAUNCH(c, LC_K_MOMENTUM, launch_momentum(c->g, c->U, v, c->w, 1.0 / c->re, 1.0, false, 0, 0, c->stream));
+      KLAUNCH(c, LC_K_MOMENTUM, launch_momentum(c->g, c->U, v, c->w, 1.0 / c->re, false, 0, 0, c->stream));
       double n0 = 0.0;
       if ((r2 = vnorm_div(c, c->w, c->r, &n0))) return r2;
       if ((r2 = poisson(c, c->r, c->phi, LC_FP64))) return r2;

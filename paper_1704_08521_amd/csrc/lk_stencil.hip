@@ -10,20 +10,6 @@
 namespace lk {
 namespace {
 
-// ------------------------------------------------------------------ momentum
-// One block owns a TX x TY column of (i, j) positions and marches along z over
-// a chunk of planes.  For each of the six input fields (advecting a = U and
-// advected b, components u, v, w) the planes k and k+1 with a one-cell x/y halo live
-// in LDS (17 KB); the few plane k-1 values a step needs are carried in registers from
-// the step before, and so are the products on the level between two planes (the edge
-// fluxes at (x_i, z_k) and (y_j, z_k), the z-momentum's centre product), which two
-// consecutive steps share.  Positions outside a field's stored range are
-// filled with the wall value of that position: 0 on wall-normal faces, beyond
-// tangential walls 0 or, for the advected field of the nonlinear residual, the
-// lid velocity at z = 1 (eq. 4).  With these ghosts the wall fluxes of the
-// Laplacian ((first - wall)/half width) and the vanishing edge fluxes on walls
-// follow from the interior formulas, so the compute has no wall branches.
-
 // Block id -> tile: workgroups are dispatched round-robin over the 8 XCDs, so
 // consecutive ids land on different L2s.  Renumber so that each XCD receives a
 // contiguous range of tiles (x fastest, then y, then z chunk): neighbouring tiles
@@ -35,311 +21,329 @@ __device__ __forceinline__ int xcd_tile(int bid, int nb) {
   return xcd < rem ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
 }
 
-template <bool LID, int TX, int TY>
-__global__ void __launch_bounds__(TX* TY) k_momentum(GridDev g, const double* __restrict__ a,
-                                                    const double* __restrict__ b, double* __restrict__ out, double rre,
-                                                    double s, double lid_u, double lid_v, int kchunk, int nbx,
-                                                    int nby) {
-  constexpr int MPX = TX + 2, MPY = TY + 2, MPS = MPX * MPY;
-  __shared__ double sm[6][2][MPS];  // 0..2: a (u, v, w); 3..5: b (u, v, w); planes k, k+1
+// ------------------------------------------------------------------ momentum
+// A row of 32 lanes owns 60 faces along x, two neighbouring ones per lane (its lanes hold
+// i0 - 2 .. i0 + 61; the first and the last lane are halo); a wave is two rows, a block four waves
+// on eight consecutive rows, marching along z over a chunk of planes.  Every lane loads its pair of
+// each of the six fields (a = U and b, components u, v, w) one plane ahead; the pairs reach the
+// neighbouring rows through LDS, and the rows around the block are loaded by its waves in turn.
+// Neighbours along x come from the neighbouring lane, and what two planes share is carried in
+// registers.  Each momentum flux - viscous and convective together, in flux form - is formed
+// once per lane: the edge product a b + b a at (x_i, y_j) serves the y flux of u and the x flux
+// of v, and a lane hands a flux on instead of the four values it is made of.
+// Positions outside a field's stored range hold the wall value of that position: 0 on
+// wall-normal faces, beyond tangential walls 0 or, for the advected field of the nonlinear
+// residual, the lid velocity at z = 1 (eq. 4).  With these ghosts the wall fluxes of the
+// Laplacian ((first - wall)/half width) and the vanishing edge fluxes on walls follow from the
+// interior formulas, so the compute has no wall branches.
+// What bounds it: at 200^3 it moves 657 MB (111 us at the 5.9 TB/s that a kernel reading two
+// fields and writing one reaches), issues about 60 us of vector instructions at two waves per
+// SIMD, and its loads and stores take the address unit about 35 us (16 cycles per load
+// instruction of a CU whether a lane asks for 8 or 16 bytes, hence the pairs).  Measured, against
+// 16 x 8 tiles whose threads each took one face and all neighbours from LDS: 16^3 14 against 32 us,
+// 64^3 18 / 28, 100^3 24 / 35, 150^3 69 / 88, 200^3 153 / 181 (3.8 TB/s of 3 fields), 256^3 283 / 354;
+// 97 x 121 x 65 22 / 32.  Rows of 64 lanes leave more of them idle (150^3 85 us), rows of 16 do
+// more halo work (200^3 163 us); everything in registers with no LDS (8-byte loads of every
+// neighbouring row) is bound by the address unit: 189 us with two rows per wave, 218 us with one.
+
+typedef double D2 __attribute__((ext_vector_type(2)));
+typedef unsigned U2 __attribute__((ext_vector_type(2)));
+typedef unsigned U4 __attribute__((ext_vector_type(4)));
+
+// x of the next lower / higher position of a pair (undefined in the wave's first / last lane,
+// whose results are halo).
+template <int CTRL>
+__device__ __forceinline__ double wave_shift(double x) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ D2 below(D2 x) { return D2{wave_shift<0x138>(x.y), x.x}; }
+__device__ __forceinline__ D2 above(D2 x) { return D2{x.y, wave_shift<0x130>(x.x)}; }
+
+// Lane l of a wave-wide register, as a wave-uniform value.
+__device__ __forceinline__ double lane_value(double x, int l) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, l);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+__device__ __forceinline__ D2 fma2(D2 a, D2 b, D2 c) { return D2{fma(a.x, b.x, c.x), fma(a.y, b.y, c.y)}; }
+__device__ __forceinline__ D2 fma2(double a, D2 b, D2 c) { return D2{fma(a, b.x, c.x), fma(a, b.y, c.y)}; }
+
+constexpr int kMomWY = 4;                                 // waves per block
+constexpr int kMomMaxChunk = 13;                          // planes per chunk (at most 62: a lane each for its z metrics)
+constexpr int kMomL = 32;                                 // lanes per row
+constexpr int kMomTX = 2 * kMomL - 4;                     // faces along x per row
+constexpr int kMomTY = kMomWY * 64 / kMomL;               // rows per block
+
+template <bool LID, bool ODD>
+__global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const double* __restrict__ a,
+                                                           const double* __restrict__ b, double* __restrict__ out,
+                                                           double rre, double lid_u, double lid_v, int kchunk, int nbx,
+                                                           int nby) {
+  constexpr int L = kMomL, TX = kMomTX, TY = kMomTY, NR = TY + 2;  // rows in LDS per field
+  static_assert(L == 32, "a load of the rows around the block holds one below and one above it");
+  constexpr int NH = (6 + kMomWY - 1) / kMomWY;  // of those a wave's share of the six fields
+  // plane in work: rows j0 - 1 .. j0 + TY of a (u, v, w) and b (u, v, w); one row nobody reads
+  __shared__ D2 sm[(6 * NR + 1) * L];
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
-  const size_t nu = (size_t)(nx + 1) * ny * nz, nv = (size_t)nx * (ny + 1) * nz;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int bx = tile % nbx, by = (tile / nbx) % nby, bz = tile / (nbx * nby);
-  const int tx = threadIdx.x % TX, ty = threadIdx.x / TX, tid = threadIdx.x;
-  const int i0 = bx * TX, j0 = by * TY;
-  const int kb = bz * kchunk;
-  const int ke = min(kb + kchunk, nz + 1);
-  const int i = i0 + tx, j = j0 + ty;
-  const double* src[6] = {a, a + nu, a + nu + nv, b, b + nu, b + nu + nv};
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sub = lane / L, li = lane % L, rb = wave * (64 / L) + sub;
+  const int j0 = by * TY, j = j0 + rb;
+  const int i = bx * TX + 2 * li - 2;  // the lane's faces are i and i + 1
+  const int kb = bz * kchunk, ke = min(kb + kchunk, nz + 1);
+  const size_t nu = (size_t)(nx + 1) * ny * nz, nv = (size_t)nx * (ny + 1) * nz;
 
-  // Halo positions of this thread (fixed along the march): in-plane byte offset per
-  // component, kGhost for a ghost position.  The loads are raw buffer loads, which return 0
-  // at or past a component's size, so a ghost (or a plane outside the field) costs no
-  // select; a plane adds k * (plane stride).  The host keeps every component below 2^31
-  // bytes, so an in-range offset plus kGhost cannot wrap.
+  // Raw buffer accesses: a byte offset of the lane and row plus the wave-uniform one of the plane.  A
+  // load at or past the given size returns 0 and a store there is dropped, so lanes without a
+  // valid face take the offset kGhost and a plane outside the field the size 0: no access has a
+  // branch.  A pair with one valid face never reaches past its component: wall rows of v and wall planes of w are not
+  // loaded, and u's last entry of a row is a wall face.  The host keeps every component below
+  // 2^31 bytes.
   constexpr unsigned kGhost = 1u << 31;
-  constexpr int NT = TX * TY;
-  constexpr int PER = (MPS + NT - 1) / NT;
-  unsigned col[3][PER];
-  bool xy[3][PER];
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = min(tid + q * NT, MPS - 1);  // the surplus threads re-read the last entry
-    const int jj = j0 - 1 + e / MPX, ii = i0 - 1 + e % MPX;
-    const bool in_i = (ii >= 0) & (ii < nx), in_j = (jj >= 0) & (jj < ny);
-    xy[0][q] = (ii > 0) & (ii < nx) & in_j;
-    xy[1][q] = (jj > 0) & (jj < ny) & in_i;
-    xy[2][q] = in_i & in_j;
-    col[0][q] = xy[0][q] ? 8u * (unsigned)(jj * (nx + 1) + ii) : kGhost;
-    col[1][q] = xy[1][q] ? 8u * (unsigned)(jj * nx + ii) : kGhost;
-    col[2][q] = xy[2][q] ? 8u * (unsigned)(jj * nx + ii) : kGhost;
-  }
-  const unsigned pstride[3] = {8u * (unsigned)(ny * (nx + 1)), 8u * (unsigned)((ny + 1) * nx),
-                               8u * (unsigned)(ny * nx)};
   const unsigned nbytes[3] = {(unsigned)(8 * nu), (unsigned)(8 * nv), (unsigned)(8 * (size_t)nx * ny * (nz + 1))};
-  __amdgpu_buffer_rsrc_t rs[6];
-#pragma unroll
-  for (int arr = 0; arr < 6; ++arr)  // raw buffer (stride 0), 32-bit data format
-    rs[arr] = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(src[arr]), (short)0, (int)nbytes[arr % 3],
-                                                0x00020000);
-
-  // Plane loads go to registers first and are written to LDS one step later, so
-  // the next plane is in flight while the current one is computed.
-  double r0[6][PER];
-  auto load = [&](double(&reg)[6][PER], int k) {
-    const bool kin_uv = (k >= 0) & (k < nz), kin_w = (k > 0) & (k < nz);
-#pragma unroll
-    for (int arr = 0; arr < 6; ++arr) {
-      const int comp = arr % 3;
-      const bool kin = comp == 2 ? kin_w : kin_uv;
-      const unsigned kofs = (unsigned)k * pstride[comp];
-      const double lid = comp == 0 ? lid_u : lid_v;
-#pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const unsigned off = kin ? col[comp][q] + kofs : kGhost;
-        const double x = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs[arr], off, 0, 0));
-        // the advected field of the nonlinear residual carries the lid velocity above z = 1
-        reg[arr][q] = (LID && arr >= 3 && comp < 2 && xy[comp][q] && k == nz) ? lid : x;
-      }
-    }
+  const size_t at[3] = {0, nu, nu + nv};
+  auto buffer = [&](const double* p, int c, unsigned in) {  // raw buffer (stride 0), 32-bit data format
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p + at[c]), (short)0, (int)(nbytes[c] & in),
+                                             0x00020000);
   };
-  auto store = [&](const double(&reg)[6][PER], int k) {
-    const int slot = (k + 2) & 1;
-#pragma unroll
-    for (int arr = 0; arr < 6; ++arr) {
-#pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int e = tid + q * NT;
-        if (e < MPS) sm[arr][slot][e] = reg[arr][q];
-      }
-    }
+  const bool u0 = i > 0 && i < nx, u1 = i + 1 > 0 && i + 1 < nx;  // interior x-faces
+  const bool c0 = i >= 0 && i < nx, c1 = i + 1 >= 0 && i + 1 < nx;  // cells
+  const unsigned row[3] = {8u * (nx + 1), 8u * nx, 8u * nx};
+  const unsigned plane[3] = {row[0] * ny, row[1] * (ny + 1), row[2] * ny};
+  auto offset = [&](int c, int jj) {
+    const bool in = (c == 0 ? (u0 || u1) : (c0 || c1)) && (c == 1 ? jj > 0 : jj >= 0) && jj < ny;
+    return in ? jj * row[c] + 8u * i : kGhost;
   };
+  auto load = [&](const double* p, int c, unsigned vo, int k) {
+    const unsigned in = -(unsigned)((c == 2 ? k > 0 : k >= 0) & (k < nz) & (k <= ke));
+    return __builtin_bit_cast(D2, __builtin_amdgcn_raw_buffer_load_b128(buffer(p, c, in), (int)vo,
+                                                                        (int)((unsigned)k * plane[c] & in), 0));
+  };
+  auto mask = [&](D2 x, int c) { return D2{(c == 0 ? u0 : c0) ? x.x : 0.0, (c == 0 ? u1 : c1) ? x.y : 0.0}; };
+  const unsigned ofs[3] = {offset(0, j), offset(1, j), offset(2, j)};
 
-  // per-thread x and y metrics (fixed along the march); out-of-range entries unused
-  const double thx0 = (i <= nx) ? g.x.th[i] : 0.0, thx1 = (i + 1 <= nx) ? g.x.th[i + 1] : 0.0;
-  const double rdx0 = (i < nx) ? g.x.rd[i] : 0.0, rdxm = (i >= 1 && i - 1 < nx) ? g.x.rd[i - 1] : 0.0;
-  const double rddx0 = (i <= nx) ? g.x.rdd[i] : 0.0, rddx1 = (i + 1 <= nx) ? g.x.rdd[i + 1] : 0.0;
-  const double thy0 = (j <= ny) ? g.y.th[j] : 0.0, thy1 = (j + 1 <= ny) ? g.y.th[j + 1] : 0.0;
-  const double rdy0 = (j < ny) ? g.y.rd[j] : 0.0, rdym = (j >= 1 && j - 1 < ny) ? g.y.rd[j - 1] : 0.0;
-  const double rddy0 = (j <= ny) ? g.y.rdd[j] : 0.0, rddy1 = (j + 1 <= ny) ? g.y.rdd[j + 1] : 0.0;
-
-  double cm[6], c0[6], cp[6];
-  double exz0, eyz0, czc0;  // the zf[k] level products (see compute)
-  double nm0, nm3, nm1, nm4;  // plane k-1: u-fields at (0, +1), v-fields at (+1, 0)
-  auto compute = [&](int k) {
-    const int p0 = (k + 2) & 1, pp = (k + 3) & 1;  // planes k, k+1
-    // S(arr, plane, dj, di)
-#define S(arr, pl, dj, di) sm[arr][pl][(ty + 1 + (dj)) * MPX + (tx + 1 + (di))]
-    // own-column values of planes k-1 and k, and the four plane k-1 neighbours the z-momentum
-    // edges need, are carried in registers from the previous steps; only plane k+1's own
-    // column is read here
+  // the rows around the block
+  struct Halo {
+    const double* p;
+    unsigned bytes, plane, ofs;
+    int k0, field, lds;  // first plane; field; position in LDS
+    bool m0, m1;
+  } halo[NH];
 #pragma unroll
-    for (int arr = 0; arr < 6; ++arr) cp[arr] = S(arr, pp, 0, 0);
-
-    const double thz0 = g.z.th[k], thz1 = (k + 1 <= nz) ? g.z.th[k + 1] : 0.0;
-    const double rdz0 = (k < nz) ? g.z.rd[k] : 0.0, rdzm = (k >= 1) ? g.z.rd[k - 1] : 0.0;
-    const double rddz0 = g.z.rdd[k], rddz1 = (k + 1 <= nz) ? g.z.rdd[k + 1] : 0.0;
-    // products on the level zf[k + 1] between planes k and k + 1, used again (as the level
-    // zf[k]) by the next step: the edge fluxes at (xf[i], zf[k + 1]) and (yf[j], zf[k + 1]),
-    // and the z-momentum's centre product of cell k
-    double exz1, eyz1, czc1;
-    {
-      const double aw = lerp(S(2, pp, 0, -1), cp[2], thx0);
-      const double bw = lerp(S(5, pp, 0, -1), cp[5], thx0);
-      const double au = lerp(c0[0], cp[0], thz1);
-      const double bu = lerp(c0[3], cp[3], thz1);
-      exz1 = aw * bu + bw * au;
-    }
-    {
-      const double aw = lerp(S(2, pp, -1, 0), cp[2], thy0);
-      const double bw = lerp(S(5, pp, -1, 0), cp[5], thy0);
-      const double av = lerp(c0[1], cp[1], thz1);
-      const double bv = lerp(c0[4], cp[4], thz1);
-      eyz1 = aw * bv + bw * av;
-    }
-    {
-      const double ap = 0.5 * (c0[2] + cp[2]), bp = 0.5 * (c0[5] + cp[5]);
-      czc1 = ap * bp;
-    }
-
-    // ---- x-momentum at the x-face (i, j, k)
-    if (k < nz && j < ny && i <= nx) {
-      double val = 0.0;
-      if (i >= 1 && i <= nx - 1) {
-        const double bc = c0[3];
-        double lap = ((S(3, p0, 0, 1) - bc) * rdx0 - (bc - S(3, p0, 0, -1)) * rdxm) * rddx0;
-        lap += ((S(3, p0, 1, 0) - bc) * rddy1 - (bc - S(3, p0, -1, 0)) * rddy0) * rdy0;
-        lap += ((cp[3] - bc) * rddz1 - (bc - cm[3]) * rddz0) * rdz0;
-        const double ac = c0[0];
-        const double am = 0.5 * (S(0, p0, 0, -1) + ac), ap = 0.5 * (ac + S(0, p0, 0, 1));
-        const double bm = 0.5 * (S(3, p0, 0, -1) + bc), bp = 0.5 * (bc + S(3, p0, 0, 1));
-        double conv = 2.0 * (ap * bp - am * bm) * rddx0;
-        // edges (xf[i], yf[j + dj])
-        double e0, e1;
-        {
-          const double av = lerp(S(1, p0, 0, -1), c0[1], thx0);
-          const double bv = lerp(S(4, p0, 0, -1), c0[4], thx0);
-          const double au = lerp(S(0, p0, -1, 0), c0[0], thy0);
-          const double bu = lerp(S(3, p0, -1, 0), c0[3], thy0);
-          e0 = av * bu + bv * au;
-        }
-        {
-          const double av = lerp(S(1, p0, 1, -1), S(1, p0, 1, 0), thx0);
-          const double bv = lerp(S(4, p0, 1, -1), S(4, p0, 1, 0), thx0);
-          const double au = lerp(c0[0], S(0, p0, 1, 0), thy1);
-          const double bu = lerp(c0[3], S(3, p0, 1, 0), thy1);
-          e1 = av * bu + bv * au;
-        }
-        conv += (e1 - e0) * rdy0;
-        // edges (xf[i], zf[k]) and (xf[i], zf[k + 1]): the first carried from the step before
-        conv += (exz1 - exz0) * rdz0;
-        val = rre * lap - s * conv;
-      }
-      out[((size_t)k * ny + j) * (nx + 1) + i] = val;
-    }
-
-    // ---- y-momentum at the y-face (i, j, k)
-    if (k < nz && j <= ny && i < nx) {
-      double val = 0.0;
-      if (j >= 1 && j <= ny - 1) {
-        const double bc = c0[4];
-        double lap = ((S(4, p0, 1, 0) - bc) * rdy0 - (bc - S(4, p0, -1, 0)) * rdym) * rddy0;
-        lap += ((S(4, p0, 0, 1) - bc) * rddx1 - (bc - S(4, p0, 0, -1)) * rddx0) * rdx0;
-        lap += ((cp[4] - bc) * rddz1 - (bc - cm[4]) * rddz0) * rdz0;
-        double e0, e1;
-        // edges (xf[i + di], yf[j])
-        {
-          const double au = lerp(S(0, p0, -1, 0), c0[0], thy0);
-          const double bu = lerp(S(3, p0, -1, 0), c0[3], thy0);
-          const double av = lerp(S(1, p0, 0, -1), c0[1], thx0);
-          const double bv = lerp(S(4, p0, 0, -1), c0[4], thx0);
-          e0 = au * bv + bu * av;
-        }
-        {
-          const double au = lerp(S(0, p0, -1, 1), S(0, p0, 0, 1), thy0);
-          const double bu = lerp(S(3, p0, -1, 1), S(3, p0, 0, 1), thy0);
-          const double av = lerp(c0[1], S(1, p0, 0, 1), thx1);
-          const double bv = lerp(c0[4], S(4, p0, 0, 1), thx1);
-          e1 = au * bv + bu * av;
-        }
-        double conv = (e1 - e0) * rdx0;
-        const double ac = c0[1];
-        const double am = 0.5 * (S(1, p0, -1, 0) + ac), ap = 0.5 * (ac + S(1, p0, 1, 0));
-        const double bm = 0.5 * (S(4, p0, -1, 0) + bc), bp = 0.5 * (bc + S(4, p0, 1, 0));
-        conv += 2.0 * (ap * bp - am * bm) * rddy0;
-        // edges (yf[j], zf[k]) and (yf[j], zf[k + 1]): the first carried from the step before
-        conv += (eyz1 - eyz0) * rdz0;
-        val = rre * lap - s * conv;
-      }
-      out[nu + ((size_t)k * (ny + 1) + j) * nx + i] = val;
-    }
-
-    // ---- z-momentum at the z-face (i, j, k)
-    if (k <= nz && j < ny && i < nx) {
-      double val = 0.0;
-      if (k >= 1 && k <= nz - 1) {
-        const double bc = c0[5];
-        double lap = ((cp[5] - bc) * rdz0 - (bc - cm[5]) * rdzm) * rddz0;
-        lap += ((S(5, p0, 0, 1) - bc) * rddx1 - (bc - S(5, p0, 0, -1)) * rddx0) * rdx0;
-        lap += ((S(5, p0, 1, 0) - bc) * rddy1 - (bc - S(5, p0, -1, 0)) * rddy0) * rdy0;
-        double e0, e1;
-        // edges (xf[i + di], zf[k]); the one at xf[i] is the x-momentum's, carried
-        e0 = exz0;
-        {
-          const double au = lerp(nm0, S(0, p0, 0, 1), thz0);
-          const double bu = lerp(nm3, S(3, p0, 0, 1), thz0);
-          const double aw = lerp(c0[2], S(2, p0, 0, 1), thx1);
-          const double bw = lerp(c0[5], S(5, p0, 0, 1), thx1);
-          e1 = au * bw + bu * aw;
-        }
-        double conv = (e1 - e0) * rdx0;
-        // edges (yf[j + dj], zf[k]); the one at yf[j] is the y-momentum's, carried
-        e0 = eyz0;
-        {
-          const double av = lerp(nm1, S(1, p0, 1, 0), thz0);
-          const double bv = lerp(nm4, S(4, p0, 1, 0), thz0);
-          const double aw = lerp(c0[2], S(2, p0, 1, 0), thy1);
-          const double bw = lerp(c0[5], S(5, p0, 1, 0), thy1);
-          e1 = av * bw + bv * aw;
-        }
-        conv += (e1 - e0) * rdy0;
-        conv += 2.0 * (czc1 - czc0) * rddz0;
-        val = rre * lap - s * conv;
-      }
-      out[nu + nv + ((size_t)k * ny + j) * nx + i] = val;
-    }
-    nm0 = S(0, p0, 0, 1);
-    nm3 = S(3, p0, 0, 1);
-    nm1 = S(1, p0, 1, 0);
-    nm4 = S(4, p0, 1, 0);
-#undef S
-#pragma unroll
-    for (int arr = 0; arr < 6; ++arr) {
-      cm[arr] = c0[arr];
-      c0[arr] = cp[arr];
-    }
-    exz0 = exz1;
-    eyz0 = eyz1;
-    czc0 = czc1;
+  for (int t = 0; t < NH; ++t) {
+    const int e = wave * NH + t, f = min(e, 5), c = f % 3;
+    const bool use = e < 6;
+    Halo& h = halo[t];
+    h.p = (f < 3 ? a : b) + (c == 0 ? 0 : c == 1 ? nu : nu + nv);
+    h.bytes = c == 0 ? nbytes[0] : c == 1 ? nbytes[1] : nbytes[2];
+    h.plane = c == 0 ? plane[0] : c == 1 ? plane[1] : plane[2];
+    h.ofs = use ? offset(c, sub ? j0 + TY : j0 - 1) : kGhost;
+    h.k0 = c == 2 ? 1 : 0;
+    h.field = f;
+    h.lds = (use ? f * NR + (sub ? TY + 1 : 0) : 6 * NR) * L + li;
+    h.m0 = c == 0 ? u0 : c0;
+    h.m1 = c == 0 ? u1 : c1;
+  }
+  auto hload = [&](const Halo& h, int k) {
+    const unsigned in = -(unsigned)((k >= h.k0) & (k < nz) & (k <= ke));
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(h.p), (short)0, (int)(h.bytes & in), 0x00020000);
+    return __builtin_bit_cast(
+        D2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)h.ofs, (int)((unsigned)k * h.plane & in), 0));
   };
 
-  // LDS holds planes k and k+1 (two slots); plane kb - 1 passes through once for the values
-  // carried in registers.  The next plane is loaded into registers during a step and
-  // written to the freed slot after it.
-#define S(arr, pl, dj, di) sm[arr][pl][(ty + 1 + (dj)) * MPX + (tx + 1 + (di))]
+  // metrics: of the lane (x, y: fixed) and of the plane (z: lane l holds those of plane kb - 1 + l,
+  // read back without a wait on memory)
+  D2 thx, rdx, rddx;
   {
-    const int sl = (kb + 1) & 1;  // plane kb - 1
-    load(r0, kb - 1);
-    store(r0, kb - 1);
-    __syncthreads();
+    auto xc = [&](int q) { return max(0, min(q, nx - 1)); };
+    auto xf = [&](int q) { return max(0, min(q, nx)); };
+    thx = D2{g.x.th[xf(i)], g.x.th[xf(i + 1)]};
+    rdx = D2{g.x.rd[xc(i)], g.x.rd[xc(i + 1)]};
+    rddx = D2{g.x.rdd[xf(i)], g.x.rdd[xf(i + 1)]};
+  }
+  const int jc = max(0, min(j, ny - 1)), jf = max(0, min(j, ny)), jf1 = min(jf + 1, ny);
+  const double thy0 = g.y.th[jf], thy1 = g.y.th[jf1], rddy0 = g.y.rdd[jf], rddy1 = g.y.rdd[jf1];
+  const double rdy0 = g.y.rd[max(jc - 1, 0)], rdy1 = g.y.rd[jc];
+  const int zl = kb - 1 + lane, zc = max(0, min(zl, nz - 1)), zf = max(0, min(zl, nz));
+  const double zth = g.z.th[zf], zrd = g.z.rd[zc], zrdd = g.z.rdd[zf];
+
+  // stores: whole pairs, and the single face that ends a row of odd length (u's for even nx,
+  // v's and w's for odd nx)
+  const bool own = li >= 1 && li <= TX / 2;
+  auto store_offset = [&](int c, bool whole) {
+    const int n = c == 0 ? nx + 1 : nx;
+    const bool in = own && i < n && (i + 1 < n) == whole && (c == 1 ? j <= ny : j < ny);
+    return in ? j * row[c] + 8u * i : kGhost;
+  };
+  const unsigned sto[3] = {store_offset(0, true), store_offset(1, true), store_offset(2, true)};
+  const unsigned sto1[3] = {store_offset(0, false), store_offset(1, false), store_offset(2, false)};
+  auto put = [&](D2 x, int c, int k, bool in) {
+    const unsigned m = -(unsigned)in, so = (unsigned)k * plane[c] & m;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, x), buffer(out, c, m), (int)sto[c], (int)so, 0);
+    if ((c == 0) != ODD)
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, x.x), buffer(out, c, m), (int)sto1[c], (int)so, 0);
+  };
+
+  // carried from the plane below: own values (and v of the row above), z fluxes, and what the
+  // faces have so far
+  D2 ou[2], ov[2], ot[2], ow[2];
+  D2 tuz = 0.0, tvz = 0.0, twz = 0.0, su = 0.0, sv = 0.0, sw = 0.0;
+  // (the advecting field is scaled by Re, and by 1/2 for the residual, as it is read: the fluxes are
+  // then Re times the momentum's and the sums are divided by Re as they are stored)
+  const double sa = LID ? 0.5 / rre : 1.0 / rre;
+  const unsigned ofst = offset(1, j + 1);
 #pragma unroll
-    for (int arr = 0; arr < 6; ++arr) cm[arr] = S(arr, sl, 0, 0);
-    nm0 = S(0, sl, 0, 1);
-    nm3 = S(3, sl, 0, 1);
-    nm1 = S(1, sl, 1, 0);
-    nm4 = S(4, sl, 1, 0);
-    __syncthreads();
+  for (int f = 0; f < 2; ++f) {
+    const double* p = f ? b : a;
+    const double q = f ? 1.0 : sa;
+    ou[f] = q * mask(load(p, 0, ofs[0], kb - 1), 0);
+    ov[f] = q * mask(load(p, 1, ofs[1], kb - 1), 1);
+    ot[f] = q * mask(load(p, 1, ofst, kb - 1), 1);
+    ow[f] = q * mask(load(p, 2, ofs[2], kb - 1), 2);
   }
-  load(r0, kb);
-  store(r0, kb);
-  load(r0, kb + 1);
-  store(r0, kb + 1);
-  __syncthreads();
+  D2 N[6], H[NH];
+  auto fetch = [&](int k) {
 #pragma unroll
-  for (int arr = 0; arr < 6; ++arr) c0[arr] = S(arr, kb & 1, 0, 0);
-  {
-    // the zf[kb] level products from planes kb - 1 (registers) and kb
-    const int p0 = kb & 1;
-    const double thz0 = g.z.th[kb];
-    {
-      const double aw = lerp(S(2, p0, 0, -1), c0[2], thx0);
-      const double bw = lerp(S(5, p0, 0, -1), c0[5], thx0);
-      const double au = lerp(cm[0], c0[0], thz0);
-      const double bu = lerp(cm[3], c0[3], thz0);
-      exz0 = aw * bu + bw * au;
+    for (int f = 0; f < 6; ++f) N[f] = load(f < 3 ? a : b, f % 3, ofs[f % 3], k);
+#pragma unroll
+    for (int t = 0; t < NH; ++t) H[t] = hload(halo[t], k);
+  };
+  auto row_at = [&](int f, int r) { return sm[(f * NR + rb + r) * L + li]; };  // row j - 1 + r of the plane in work
+  fetch(kb);
+  // A plane's results wait in registers until the next stage has its input, and are stored ahead of its
+  // loads: memory operations complete in order, so a store behind the loads would be waited for
+  // with them at once.
+  D2 res[3] = {0.0, 0.0, 0.0};
+  auto flush = [&](int k) {  // plane k's, k < ke; none before the first
+    put(res[0], 0, k, k >= kb && k < nz);
+    put(res[1], 1, k, k >= kb && k < nz);
+    put(res[2], 2, k, k >= kb);
+  };
+  for (int k = kb; k <= ke; ++k) {
+    D2 O[6];
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+      O[f] = mask(N[f], f % 3);
+      if (f < 3) O[f] *= sa;
     }
-    {
-      const double aw = lerp(S(2, p0, -1, 0), c0[2], thy0);
-      const double bw = lerp(S(5, p0, -1, 0), c0[5], thy0);
-      const double av = lerp(cm[1], c0[1], thz0);
-      const double bv = lerp(cm[4], c0[4], thz0);
-      eyz0 = aw * bv + bw * av;
+    D2 h[NH];
+#pragma unroll
+    for (int t = 0; t < NH; ++t) {
+      h[t] = D2{halo[t].m0 ? H[t].x : 0.0, halo[t].m1 ? H[t].y : 0.0};
+      h[t] *= halo[t].field < 3 ? sa : 1.0;
     }
-    {
-      const double am = 0.5 * (cm[2] + c0[2]), bm = 0.5 * (cm[5] + c0[5]);
-      czc0 = am * bm;
+    if (LID && k == nz) {  // the advected field carries the lid velocity above z = 1
+      if (j < ny) O[3] = D2{u0 ? lid_u : 0.0, u1 ? lid_u : 0.0};
+      if (j > 0 && j < ny) O[4] = D2{c0 ? lid_v : 0.0, c1 ? lid_v : 0.0};
+#pragma unroll
+      for (int t = 0; t < NH; ++t)
+        if ((halo[t].field == 3 || halo[t].field == 4) && halo[t].ofs != kGhost) {
+          const double x = halo[t].field == 3 ? lid_u : lid_v;
+          h[t] = D2{halo[t].m0 ? x : 0.0, halo[t].m1 ? x : 0.0};
+        }
     }
-  }
-#undef S
-  if (kb + 2 <= ke) load(r0, kb + 2);
-  for (int k = kb; k < ke; ++k) {
-    compute(k);
+#pragma unroll
+    for (int f = 0; f < 6; ++f) sm[(f * NR + rb + 1) * L + li] = O[f];
+#pragma unroll
+    for (int t = 0; t < NH; ++t) sm[halo[t].lds] = h[t];
+    flush(k - 2);
+    fetch(k + 1);
     __syncthreads();
-    if (k + 2 <= ke) store(r0, k + 2);
+
+    const int l = k - kb + 1;
+    const double thz = lane_value(zth, l), rddz = lane_value(zrdd, l);
+    const double rdzm = lane_value(zrd, l - 1), rddzm = lane_value(zrdd, l - 1);
+    D2 nsw;
+    {  // edges (x_i, z_k): z flux of u, x flux of w
+      const D2 aw0 = below(O[2]), bw0 = below(O[5]);
+      const D2 dbw = O[5] - bw0, dbu = O[3] - ou[1];
+      const D2 aw = fma2(thx, O[2] - aw0, aw0), bw = fma2(thx, dbw, bw0);
+      const D2 au = fma2(thz, O[0] - ou[0], ou[0]), bu = fma2(thz, dbu, ou[1]);
+      const D2 e = fma2(aw, bu, bw * au);
+      const D2 tz = fma2(rddz, dbu, -e), tx = fma2(rddx, dbw, -e);
+      nsw = (above(tx) - tx) * rdx;
+      const D2 val = fma2(rdzm, tz - tuz, su);
+      res[0] = D2{u0 ? rre * val.x : 0.0, u1 ? rre * val.y : 0.0};
+      tuz = tz;
+    }
+    {  // edges (y_j, z_k) and (y_{j+1}, z_k): z flux of v, y flux of w
+      const D2 aw0 = row_at(2, 0), bw0 = row_at(5, 0);
+      const D2 dbw = O[5] - bw0, dbv = O[4] - ov[1];
+      const D2 aw = fma2(thy0, O[2] - aw0, aw0), bw = fma2(thy0, dbw, bw0);
+      const D2 av = fma2(thz, O[1] - ov[0], ov[0]), bv = fma2(thz, dbv, ov[1]);
+      const D2 e = fma2(aw, bv, bw * av);
+      const D2 tz = fma2(rddz, dbv, -e);
+      nsw = fma2(-rdy1, fma2(rddy0, dbw, -e), nsw);
+      const D2 val = fma2(rdzm, tz - tvz, sv);
+      res[1] = j > 0 && j < ny ? rre * val : D2{0.0, 0.0};
+      tvz = tz;
+    }
+    {
+      const D2 aw1 = row_at(2, 2), bw1 = row_at(5, 2);
+      const D2 av1 = row_at(1, 2), bv1 = row_at(4, 2);
+      const D2 dbw = bw1 - O[5];
+      const D2 aw = fma2(thy1, aw1 - O[2], O[2]), bw = fma2(thy1, dbw, O[5]);
+      const D2 av = fma2(thz, av1 - ot[0], ot[0]), bv = fma2(thz, bv1 - ot[1], ot[1]);
+      const D2 e = fma2(aw, bv, bw * av);
+      nsw = fma2(rdy1, fma2(rddy1, dbw, -e), nsw);
+      ot[0] = av1;
+      ot[1] = bv1;
+    }
+    {  // centre of cell k - 1: z flux of w
+      const D2 aw = ow[0] + O[2], bw = ow[1] + O[5];
+      const D2 tz = fma2(rdzm, O[5] - ow[1], -((0.5 * aw) * bw));
+      res[2] = k > 1 && k <= nz ? rre * fma2(rddzm, tz - twz, sw) : D2{0.0, 0.0};
+      twz = tz;
+      sw = nsw;
+    }
+    {  // centres along x
+      const D2 au1 = above(O[0]), bu1 = above(O[3]);
+      const D2 au = O[0] + au1, bu = O[3] + bu1;
+      const D2 t = fma2(rdx, bu1 - O[3], -((0.5 * au) * bu));
+      su = (t - below(t)) * rddx;
+    }
+    {  // edges (x_i, y_j) and (x_i, y_{j+1}): y flux of u, x flux of v
+      const D2 au0 = row_at(0, 0), bu0 = row_at(3, 0);
+      const D2 av0 = below(O[1]), bv0 = below(O[4]);
+      const D2 dbv = O[4] - bv0, dbu = O[3] - bu0;
+      const D2 av = fma2(thx, O[1] - av0, av0), bv = fma2(thx, dbv, bv0);
+      const D2 au = fma2(thy0, O[0] - au0, au0), bu = fma2(thy0, dbu, bu0);
+      const D2 e = fma2(av, bu, bv * au);
+      const D2 tx = fma2(rddx, dbv, -e);
+      su = fma2(-rdy1, fma2(rddy0, dbu, -e), su);
+      sv = (above(tx) - tx) * rdx;
+    }
+    {
+      const D2 au1 = row_at(0, 2), bu1 = row_at(3, 2);
+      const D2 av0 = below(ot[0]), bv0 = below(ot[1]);
+      const D2 dbu = bu1 - O[3];
+      const D2 av = fma2(thx, ot[0] - av0, av0), bv = fma2(thx, ot[1] - bv0, bv0);
+      const D2 au = fma2(thy1, au1 - O[0], O[0]), bu = fma2(thy1, dbu, O[3]);
+      const D2 e = fma2(av, bu, bv * au);
+      su = fma2(rdy1, fma2(rddy1, dbu, -e), su);
+    }
+    {  // centres along y
+      const D2 avm = row_at(1, 0), bvm = row_at(4, 0);
+      const D2 tm = fma2(rdy0, O[4] - bvm, -((0.5 * (avm + O[1])) * (bvm + O[4])));
+      const D2 tp = fma2(rdy1, ot[1] - O[4], -((0.5 * (O[1] + ot[0])) * (O[4] + ot[1])));
+      sv = fma2(rddy0, tp - tm, sv);
+    }
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      ou[f] = O[3 * f];
+      ov[f] = O[3 * f + 1];
+      ow[f] = O[3 * f + 2];
+    }
     __syncthreads();
-    if (k + 3 <= ke) load(r0, k + 3);
   }
+  flush(ke - 1);
 }
 
 // ---------------------------------------------------------------- divergence
@@ -428,29 +432,45 @@ __global__ void __launch_bounds__(kCorTX* kCorTY) k_correct(GridDev g, const dou
 }  // namespace
 
 // ==================================================================== launchers
-// Tile of the momentum stencil: TX x TY threads; the nz + 1 planes are split into the
-// nearest whole number of kMomChunk-plane chunks, ceil((nz + 1) / that number) planes each
-// (the last takes the rest), one chunk per block.  Measured at
-// 200^3 (201 planes, same bits for every length): 12 planes 191-192 us, 14 196-198, 17
-// 193-195, 24 197-199, 29 197-198, 41 218; 8 and 10 (a last chunk of one plane) 197-201.
-constexpr int kMomTX = 16, kMomTY = 8, kMomChunk = 12;
+// Momentum stencil: the nz + 1 planes are split into chunks, one per block.  Two blocks fit a CU
+// (registers), so up to kMomSlots run at once; the number of chunks is the one whose rounds of
+// blocks, each as long as a chunk's planes and its start-up, end soonest.  Chunks stay short
+// because neighbouring blocks then read their common rows and planes at about the same time, from
+// the L2: at 256^3 13 planes 283 us, 16 to 20 292-304 us, 34 323 us; at 200^3 12 to 20 150-155 us, 34 177 us.
+constexpr int kMomSlots = 512;
 
-hipError_t launch_momentum(const GridDev& g, const double* a, const double* b, double* out, double rre, double s,
-                           bool lid, double lid_u, double lid_v, hipStream_t st) {
+int momentum_chunk(int nx, int ny, int nz) {
+  const long tiles = (long)blocks_for(nx + 1, kMomTX) * blocks_for(ny + 1, kMomTY);
+  int best = 0;
+  double least = 0.0;
+  for (int nch = 1; nch <= std::max(1, (nz + 1) / 3); ++nch) {
+    const int planes = (int)blocks_for(nz + 1, nch);
+    if (planes > kMomMaxChunk) continue;
+    const long rounds = blocks_for((size_t)tiles * blocks_for(nz + 1, planes), kMomSlots);
+    const double cost = rounds * (planes + 2.5);
+    if (!best || cost < least) best = planes, least = cost;
+  }
+  return best;
+}
+
+hipError_t launch_momentum(const GridDev& g, const double* a, const double* b, double* out, double rre, bool lid,
+                           double lid_u, double lid_v, hipStream_t st) {
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
   const VelLayout L = vel_layout(nx, ny, nz);
   if (8 * std::max(L.nu, std::max(L.nv, L.nw)) >= (size_t(1) << 31)) return hipErrorInvalidValue;
   const int nbx = (int)blocks_for(nx + 1, kMomTX), nby = (int)blocks_for(ny + 1, kMomTY);
-  const int nch = std::max(1, (nz + 1 + kMomChunk / 2) / kMomChunk);
-  const int kchunk = (int)blocks_for(nz + 1, nch);
-  const int nbz = (int)blocks_for(nz + 1, kchunk);
-  const dim3 grid(nbx * nby * nbz), block(kMomTX * kMomTY);
-  if (lid)
-    hipLaunchKernelGGL((k_momentum<true, kMomTX, kMomTY>), grid, block, 0, st, g, a, b, out, rre, s, lid_u, lid_v,
-                       kchunk, nbx, nby);
-  else
-    hipLaunchKernelGGL((k_momentum<false, kMomTX, kMomTY>), grid, block, 0, st, g, a, b, out, rre, s, 0.0, 0.0,
-                       kchunk, nbx, nby);
+  const int kchunk = momentum_chunk(nx, ny, nz);
+  const dim3 grid(nbx * nby * blocks_for(nz + 1, kchunk)), block(64 * kMomWY);
+#define LK_MOM(LID, ODD) \
+  hipLaunchKernelGGL((k_momentum<LID, ODD>), grid, block, 0, st, g, a, b, out, rre, lid_u, lid_v, kchunk, nbx, nby)
+  if (lid) {
+    if (nx & 1) LK_MOM(true, true);
+    else LK_MOM(true, false);
+  } else {
+    if (nx & 1) LK_MOM(false, true);
+    else LK_MOM(false, false);
+  }
+#undef LK_MOM
   return hipGetLastError();
 }
 
