@@ -13,6 +13,7 @@
 #include "lk_ctx.h"
 #include "lk_internal.h"
 #include "lk_linalg.h"
+#include "lk_lines.h"
 #include "lk_modes.h"
 
 using namespace lk;
@@ -168,125 +169,34 @@ int upload_grid(lc_ctx* c) {
   return LC_OK;
 }
 
-// (D G) phi = r by transforming with S^T M along x, y, z, dividing by the sums of
-// the axis eigenvalues (constant mode set to zero) and transforming back with S.
+// (D G) phi = r by the tensor-product solve.  TPT: transforms with S^T M along y and z, one tridiagonal
+// solve per x-line, transforms back with S.  TPF: transforms along x, y and z and a division by
+// the sums of the axis eigenvalues (constant mode set to zero).
 template <typename T>
 int tp_solve(lc_ctx* c, const T* r, T* phi, T* t1, T* t2) {
   const int nx = c->nx, ny = c->ny, nz = c->nz;
-  const long pl = (long)nx * ny;
-  auto pick = [](const AxisModes& M, int which) -> const T* {
-    if constexpr (sizeof(T) == sizeof(double)) {
-      const double* a[4] = {M.F, M.Bk, M.FT, M.BkT};
-      return (const T*)a[which];
-    } else {
-      const float* a[4] = {M.F32, M.Bk32, M.FT32, M.BkT32};
-      return (const T*)a[which];
-    }
-  };
-  auto half = [](const AxisModes& M, int which) -> const T* {
-    if constexpr (sizeof(T) == sizeof(double))
-      return (const T*)M.h64[which];
-    else
-      return (const T*)M.h32[which];
-  };
-  auto packs = [](const AxisModes& M, int which) -> const T* {
-    if constexpr (sizeof(T) == sizeof(double))
-      return (const T*)M.p64[which];
-    else
-      return (const T*)M.p32[which];
-  };
-  auto lams = [](const AxisModes& M) { return M.sym ? M.lam_s : M.lam; };
   const AxisModes &X = c->modes[0], &Y = c->modes[1], &Z = c->modes[2];
+  auto lams = [](const AxisModes& M) { return M.sym ? M.lam_s : M.lam; };
   hipStream_t s = c->stream;
-  const int n_yz = ny * nz, n_xz = nx * nz;
-  const double* nul = nullptr;
-  {
-    if (c->poisson_method == LC_POISSON_TPT && nx <= tridiag_x_max()) {
-      // TPT: forward y and z, tridiagonal solves along x, backward z and y
-      if (Y.mf)
-        KLAUNCH(c, LC_K_TP_Y, launch_mff_left<T>(ny, n_xz, packs(Y, 0), packs(Y, 1), r, t1, nx, pl, nx, s));
-      else if (Y.sym)
-        KLAUNCH(c, LC_K_TP_Y, launch_tpf_left<T>(ny, n_xz, half(Y, 0), half(Y, 1), r, t1, nx, pl, nx, nul, nul, nul, 1,
-                                                 0, 0, 0, s));
-      else
-        KLAUNCH(c, LC_K_TP_Y, launch_tp_left<T>(ny, n_xz, ny, pick(Y, 0), r, t1, nx, pl, nx, nul, nul, nul, 1, 0, 0, 0,
-                                                s));
-      if (Z.mf)
-        KLAUNCH(c, LC_K_TP_Z, launch_mff_left<T>(nz, (int)pl, packs(Z, 0), packs(Z, 1), t1, t2, (int)pl, 0, pl, s));
-      else if (Z.sym)
-        KLAUNCH(c, LC_K_TP_Z, launch_tpf_left<T>(nz, (int)pl, half(Z, 0), half(Z, 1), t1, t2, (int)pl, 0, pl, nul, nul,
-                                                 nul, 1, 0, 0, 0, s));
-      else
-        KLAUNCH(c, LC_K_TP_Z, launch_tp_left<T>(nz, (int)pl, nz, pick(Z, 0), t1, t2, (int)pl, 0, pl, nul, nul, nul, 1, 0,
-                                                0, 0, s));
-      KLAUNCH(c, LC_K_TRIDIAG,
-              launch_tridiag_x<T>(c->g, lams(Y), lams(Z), c->zero_mode[1], c->zero_mode[2], t2, t1, s));
-      if (Z.mf)
-        KLAUNCH(c, LC_K_TP_Z, launch_mfu_left<T>(nz, (int)pl, packs(Z, 2), packs(Z, 3), t1, t2, (int)pl, 0, pl, nul,
-                                                 nul, nul, 1, 0, 0, 0, s));
-      else if (Z.sym)
-        KLAUNCH(c, LC_K_TP_Z, launch_tpu_left<T>(nz, (int)pl, half(Z, 2), half(Z, 3), t1, t2, (int)pl, 0, pl, s));
-      else
-        KLAUNCH(c, LC_K_TP_Z, launch_tp_left<T>(nz, (int)pl, nz, pick(Z, 1), t1, t2, (int)pl, 0, pl, nul, nul, nul, 1, 0,
-                                                0, 0, s));
-      if (Y.mf)
-        KLAUNCH(c, LC_K_TP_Y, launch_mfu_left<T>(ny, n_xz, packs(Y, 2), packs(Y, 3), t2, phi, nx, pl, nx, nul, nul, nul,
-                                                 1, 0, 0, 0, s));
-      else if (Y.sym)
-        KLAUNCH(c, LC_K_TP_Y, launch_tpu_left<T>(ny, n_xz, half(Y, 2), half(Y, 3), t2, phi, nx, pl, nx, s));
-      else
-        KLAUNCH(c, LC_K_TP_Y, launch_tp_left<T>(ny, n_xz, ny, pick(Y, 1), t2, phi, nx, pl, nx, nul, nul, nul, 1, 0, 0, 0,
-                                                s));
-      return LC_OK;
-    }
+  const int pl = nx * ny;
+  const Columns cy{nx * nz, nx, pl, nx, c->ncell}, cz{pl, pl, 0, pl, c->ncell};
+  const LineScale none;
+  if (c->poisson_method == LC_POISSON_TPT && nx <= tridiag_x_max()) {
+    KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, r, t1, none, s));
+    KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t1, t2, none, s));
+    KLAUNCH(c, LC_K_TRIDIAG,
+            launch_tridiag_x<T>(c->g, lams(Y), lams(Z), c->zero_mode[1], c->zero_mode[2], t2, t1, s));
+    KLAUNCH(c, LC_K_TP_Z, left_backward<T>(Z, nz, cz, t1, t2, none, s));
+    KLAUNCH(c, LC_K_TP_Y, left_backward<T>(Y, ny, cy, t2, phi, none, s));
+    return LC_OK;
   }
-  // forward: x (contiguous lines), y (columns (k, i), rows nx apart), z (rows nx*ny apart),
-  // the division by lam_x + lam_y + lam_z fused into the z transform; a mirror-symmetric
-  // axis uses the folded half-size transforms (modes parity-sorted)
-  // (mirror-symmetric axes with he <= kMfMaxHalf run on the matrix cores)
-  if (X.mf)
-    KLAUNCH(c, LC_K_TP_X, launch_mff_right<T>(nx, n_yz, r, packs(X, 0), packs(X, 1), t1, s));
-  else if (X.sym)
-    KLAUNCH(c, LC_K_TP_X, launch_tpf_right<T>(nx, n_yz, r, half(X, 4), half(X, 5), t1, s));
-  else
-    KLAUNCH(c, LC_K_TP_X, launch_tp_right<T>(n_yz, nx, nx, r, pick(X, 2), t1, s));
-  if (Y.mf)
-    KLAUNCH(c, LC_K_TP_Y, launch_mff_left<T>(ny, n_xz, packs(Y, 0), packs(Y, 1), t1, t2, nx, pl, nx, s));
-  else if (Y.sym)
-    KLAUNCH(c, LC_K_TP_Y, launch_tpf_left<T>(ny, n_xz, half(Y, 0), half(Y, 1), t1, t2, nx, pl, nx, nul, nul, nul, 1, 0, 0,
-                                             0, s));
-  else
-    KLAUNCH(c, LC_K_TP_Y, launch_tp_left<T>(ny, n_xz, ny, pick(Y, 0), t1, t2, nx, pl, nx, nul, nul, nul, 1, 0, 0, 0, s));
-  if (Z.mf)  // (the eigenvalue division then happens in the backward z transform)
-    KLAUNCH(c, LC_K_TP_Z, launch_mff_left<T>(nz, (int)pl, packs(Z, 0), packs(Z, 1), t2, t1, (int)pl, 0, pl, s));
-  else if (Z.sym)
-    KLAUNCH(c, LC_K_TP_Z, launch_tpf_left<T>(nz, (int)pl, half(Z, 0), half(Z, 1), t2, t1, (int)pl, 0, pl, lams(Z),
-                                             lams(Y), lams(X), nx, c->zero_mode[2], c->zero_mode[1], c->zero_mode[0], s));
-  else
-    KLAUNCH(c, LC_K_TP_Z, launch_tp_left<T>(nz, (int)pl, nz, pick(Z, 0), t2, t1, (int)pl, 0, pl, lams(Z), lams(Y),
-                                            lams(X), nx, c->zero_mode[2], c->zero_mode[1], c->zero_mode[0], s));
-  // backward: z, y, x
-  if (Z.mf)
-    KLAUNCH(c, LC_K_TP_Z, launch_mfu_left<T>(nz, (int)pl, packs(Z, 2), packs(Z, 3), t1, t2, (int)pl, 0, pl, lams(Z),
-                                             lams(Y), lams(X), nx, c->zero_mode[2], c->zero_mode[1], c->zero_mode[0], s));
-  else if (Z.sym)
-    KLAUNCH(c, LC_K_TP_Z, launch_tpu_left<T>(nz, (int)pl, half(Z, 2), half(Z, 3), t1, t2, (int)pl, 0, pl, s));
-  else
-    KLAUNCH(c, LC_K_TP_Z, launch_tp_left<T>(nz, (int)pl, nz, pick(Z, 1), t1, t2, (int)pl, 0, pl, nul, nul, nul, 1, 0, 0,
-                                            0, s));
-  if (Y.mf)
-    KLAUNCH(c, LC_K_TP_Y, launch_mfu_left<T>(ny, n_xz, packs(Y, 2), packs(Y, 3), t2, t1, nx, pl, nx, nul, nul, nul, 1, 0,
-                                             0, 0, s));
-  else if (Y.sym)
-    KLAUNCH(c, LC_K_TP_Y, launch_tpu_left<T>(ny, n_xz, half(Y, 2), half(Y, 3), t2, t1, nx, pl, nx, s));
-  else
-    KLAUNCH(c, LC_K_TP_Y, launch_tp_left<T>(ny, n_xz, ny, pick(Y, 1), t2, t1, nx, pl, nx, nul, nul, nul, 1, 0, 0, 0, s));
-  if (X.mf)
-    KLAUNCH(c, LC_K_TP_X, launch_mfu_right<T>(nx, n_yz, t1, packs(X, 2), packs(X, 3), phi, s));
-  else if (X.sym)
-    KLAUNCH(c, LC_K_TP_X, launch_tpu_right<T>(nx, n_yz, t1, half(X, 6), half(X, 7), phi, s));
-  else
-    KLAUNCH(c, LC_K_TP_X, launch_tp_right<T>(n_yz, nx, nx, t1, pick(X, 3), phi, s));
+  const LineScale sc{lams(Z), lams(Y), lams(X), nx, c->zero_mode[2], c->zero_mode[1], c->zero_mode[0]};
+  KLAUNCH(c, LC_K_TP_X, right_forward<T>(X, nx, ny * nz, r, t1, s));
+  KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, t1, t2, none, s));
+  KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t2, t1, sc, s));
+  KLAUNCH(c, LC_K_TP_Z, left_backward<T>(Z, nz, cz, t1, t2, sc, s));
+  KLAUNCH(c, LC_K_TP_Y, left_backward<T>(Y, ny, cy, t2, t1, none, s));
+  KLAUNCH(c, LC_K_TP_X, right_backward<T>(X, nx, ny * nz, t1, phi, s));
   return LC_OK;
 }
 

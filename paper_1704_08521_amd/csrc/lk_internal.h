@@ -140,6 +140,18 @@ template <typename T>
 hipError_t launch_mfu_left(int n, int N, const T* Pse, const T* Pso, const T* B, T* C, int nseg, long seg_stride,
                            long kstride, const double* lm, const double* ly, const double* lx, int nxs, int zm, int zj,
                            int zi, hipStream_t st);
+// FP64 left transforms (lk_mx.hip): both half matrices as 4 x 4 pieces, [step of 4 contracted
+// indices][group of 4 rows][16 values][even, odd]: value (o, k) of one parity at mx_pack_index, zero outside
+// the matrix.  `elems` values in the field (below 2^31 bytes); scaling as above.
+__host__ __device__ constexpr long mx_pack_index(int o, int k, int he, int odd) {
+  return (((long)(k / 4) * ((he + 3) / 4) + o / 4) * 16 + (k % 4) * 4 + o % 4) * 2 + odd;
+}
+__host__ __device__ constexpr long mx_pack_size(int he) { return (long)((he + 3) / 4) * ((he + 3) / 4) * 32; }
+hipError_t launch_mxf_left(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
+                           long seg_stride, long kstride, hipStream_t st);
+hipError_t launch_mxu_left(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
+                           long seg_stride, long kstride, const double* lm, const double* ly, const double* lx, int nxs,
+                           int zm, int zj, int zi, hipStream_t st);
 template <typename T>
 hipError_t launch_mff_right(int n, int Mlines, const T* A, const T* Pe, const T* Po, T* C, hipStream_t st);
 template <typename T>

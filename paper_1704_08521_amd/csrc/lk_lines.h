@@ -1,0 +1,95 @@
+// Transforms of every grid line along one axis with the axis's factors, in the variant that suits the axis: FP64 and
+// FP32 matrix cores (mirror-symmetric, half length <= kMfMaxHalf), folded vector-FMA kernels (longer
+// mirror-symmetric axes) or the full mode matrix.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "lk_ctx.h"
+#include "lk_internal.h"
+
+namespace lk {
+
+// Division by lm[mode] + ly[j] + lx[i] between a forward and a backward left transform (column = j * nxs + i), the mode
+// (zm, zj, zi) set to zero (negative: none).  The vector-FMA kernels divide in the forward
+// transform, the matrix-core ones in the backward one; both calls of a pair get the same scale.
+struct LineScale {
+  const double *lm = nullptr, *ly = nullptr, *lx = nullptr;
+  int nxs = 1, zm = 0, zj = 0, zi = 0;
+};
+
+// Columns of a left transform: column q starts at (q / nseg) * seg_stride + q % nseg, rows kstride apart, in a
+// field of `elems` values.
+struct Columns {
+  int count, nseg;
+  long seg_stride, kstride;
+  size_t elems;
+};
+
+template <typename T>
+const T* mode_full(const AxisModes& M, int which) {
+  const double* d[4] = {M.F, M.Bk, M.FT, M.BkT};
+  const float* f[4] = {M.F32, M.Bk32, M.FT32, M.BkT32};
+  if constexpr (sizeof(T) == sizeof(double)) return d[which];
+  else return f[which];
+}
+template <typename T>
+const T* mode_half(const AxisModes& M, int which) {
+  if constexpr (sizeof(T) == sizeof(double)) return M.h64[which];
+  else return M.h32[which];
+}
+template <typename T>
+const T* mode_pack(const AxisModes& M, int which) {
+  if constexpr (sizeof(T) == sizeof(double)) return M.p64[which];
+  else return M.p32[which];
+}
+
+template <typename T>
+hipError_t left_forward(const AxisModes& M, int n, const Columns& q, const T* in, T* out, const LineScale& s,
+                        hipStream_t st) {
+  if (M.mf) {
+    if constexpr (sizeof(T) == sizeof(double))
+      return launch_mxf_left(n, q.count, M.x64[0], in, out, q.elems, q.nseg, q.seg_stride, q.kstride, st);
+    else
+      return launch_mff_left(n, q.count, M.p32[0], M.p32[1], in, out, q.nseg, q.seg_stride, q.kstride, st);
+  }
+  if (M.sym)
+    return launch_tpf_left<T>(n, q.count, mode_half<T>(M, 0), mode_half<T>(M, 1), in, out, q.nseg, q.seg_stride,
+                              q.kstride, s.lm, s.ly, s.lx, s.nxs, s.zm, s.zj, s.zi, st);
+  return launch_tp_left<T>(n, q.count, n, mode_full<T>(M, 0), in, out, q.nseg, q.seg_stride, q.kstride, s.lm, s.ly,
+                           s.lx, s.nxs, s.zm, s.zj, s.zi, st);
+}
+
+template <typename T>
+hipError_t left_backward(const AxisModes& M, int n, const Columns& q, const T* in, T* out, const LineScale& s,
+                         hipStream_t st) {
+  if (M.mf) {
+    if constexpr (sizeof(T) == sizeof(double))
+      return launch_mxu_left(n, q.count, M.x64[1], in, out, q.elems, q.nseg, q.seg_stride, q.kstride, s.lm,
+                             s.ly, s.lx, s.nxs, s.zm, s.zj, s.zi, st);
+    else
+      return launch_mfu_left(n, q.count, M.p32[2], M.p32[3], in, out, q.nseg, q.seg_stride, q.kstride, s.lm, s.ly,
+                             s.lx, s.nxs, s.zm, s.zj, s.zi, st);
+  }
+  if (M.sym)
+    return launch_tpu_left<T>(n, q.count, mode_half<T>(M, 2), mode_half<T>(M, 3), in, out, q.nseg, q.seg_stride,
+                              q.kstride, st);
+  return launch_tp_left<T>(n, q.count, n, mode_full<T>(M, 1), in, out, q.nseg, q.seg_stride, q.kstride, nullptr, nullptr,
+                           nullptr, 1, 0, 0, 0, st);
+}
+
+template <typename T>
+hipError_t right_forward(const AxisModes& M, int n, int lines, const T* in, T* out, hipStream_t st) {
+  if (M.mf) return launch_mff_right<T>(n, lines, in, mode_pack<T>(M, 0), mode_pack<T>(M, 1), out, st);
+  if (M.sym) return launch_tpf_right<T>(n, lines, in, mode_half<T>(M, 4), mode_half<T>(M, 5), out, st);
+  return launch_tp_right<T>(lines, n, n, in, mode_full<T>(M, 2), out, st);
+}
+
+template <typename T>
+hipError_t right_backward(const AxisModes& M, int n, int lines, const T* in, T* out, hipStream_t st) {
+  if (M.mf) return launch_mfu_right<T>(n, lines, in, mode_pack<T>(M, 2), mode_pack<T>(M, 3), out, st);
+  if (M.sym) return launch_tpu_right<T>(n, lines, in, mode_half<T>(M, 6), mode_half<T>(M, 7), out, st);
+  return launch_tp_right<T>(lines, n, n, in, mode_full<T>(M, 3), out, st);
+}
+
+}  // namespace lk

@@ -6,59 +6,28 @@
 
 #include "lk_ctx.h"
 #include "lk_internal.h"
+#include "lk_lines.h"
 
 using namespace lk;
 
 namespace {
 
-// One transform pass along `axis` (0 x, 1 y, 2 z), forward (S^T M) or backward (S),
-// in the same variant the 3D solver picks for that axis: matrix cores, folded
-// half-size transforms of a mirror-symmetric axis, or the full matrices.
+// One transform pass along `axis` (0 x, 1 y, 2 z), forward (S^T M) or backward (S).  Left transforms: y runs over columns
+// (k, i) with rows nx apart in segments of nx columns, one plane apart; z over the columns of a
+// plane with rows a plane apart.
 int axis_pass(lc_ctx* c, int axis, bool fwd, const double* in, double* out) {
-  const int nx = c->nx, ny = c->ny, nz = c->nz;
-  const long pl = (long)nx * ny;
-  const int n_yz = ny * nz, n_xz = nx * nz;
+  const int nx = c->nx, ny = c->ny, nz = c->nz, pl = nx * ny;
   const AxisModes& M = c->modes[axis];
-  const double* nul = nullptr;
   hipStream_t s = c->stream;
   if (axis == 0) {
-    if (M.mf) {
-      if (fwd)
-        KLAUNCH(c, LC_K_TP_X, launch_mff_right<double>(nx, n_yz, in, M.p64[0], M.p64[1], out, s));
-      else
-        KLAUNCH(c, LC_K_TP_X, launch_mfu_right<double>(nx, n_yz, in, M.p64[2], M.p64[3], out, s));
-    } else if (M.sym) {
-      if (fwd)
-        KLAUNCH(c, LC_K_TP_X, launch_tpf_right<double>(nx, n_yz, in, M.h64[4], M.h64[5], out, s));
-      else
-        KLAUNCH(c, LC_K_TP_X, launch_tpu_right<double>(nx, n_yz, in, M.h64[6], M.h64[7], out, s));
-    } else {
-      KLAUNCH(c, LC_K_TP_X, launch_tp_right<double>(n_yz, nx, nx, in, fwd ? M.FT : M.BkT, out, s));
-    }
+    if (fwd) KLAUNCH(c, LC_K_TP_X, right_forward<double>(M, nx, ny * nz, in, out, s));
+    else KLAUNCH(c, LC_K_TP_X, right_backward<double>(M, nx, ny * nz, in, out, s));
     return LC_OK;
   }
-  // left transforms: y runs over columns (k, i) with rows nx apart in segments of nx
-  // columns, pl apart; z over the pl columns with rows pl apart
-  const int kid = axis == 1 ? LC_K_TP_Y : LC_K_TP_Z;
-  const int n = axis == 1 ? ny : nz, cols = axis == 1 ? n_xz : (int)pl;
-  const int nseg = axis == 1 ? nx : (int)pl;
-  const long sstride = axis == 1 ? pl : 0, rstride = axis == 1 ? (long)nx : pl;
-  if (M.mf) {
-    if (fwd)
-      KLAUNCH(c, kid, launch_mff_left<double>(n, cols, M.p64[0], M.p64[1], in, out, nseg, sstride, rstride, s));
-    else
-      KLAUNCH(c, kid, launch_mfu_left<double>(n, cols, M.p64[2], M.p64[3], in, out, nseg, sstride, rstride, nul, nul, nul,
-                                              1, 0, 0, 0, s));
-  } else if (M.sym) {
-    if (fwd)
-      KLAUNCH(c, kid, launch_tpf_left<double>(n, cols, M.h64[0], M.h64[1], in, out, nseg, sstride, rstride, nul, nul, nul,
-                                              1, 0, 0, 0, s));
-    else
-      KLAUNCH(c, kid, launch_tpu_left<double>(n, cols, M.h64[2], M.h64[3], in, out, nseg, sstride, rstride, s));
-  } else {
-    KLAUNCH(c, kid, launch_tp_left<double>(n, cols, n, fwd ? M.F : M.Bk, in, out, nseg, sstride, rstride, nul, nul, nul,
-                                           1, 0, 0, 0, s));
-  }
+  const Columns q = axis == 1 ? Columns{nx * nz, nx, pl, nx, c->ncell} : Columns{pl, pl, 0, pl, c->ncell};
+  const int kid = axis == 1 ? LC_K_TP_Y : LC_K_TP_Z, n = axis == 1 ? ny : nz;
+  if (fwd) KLAUNCH(c, kid, left_forward<double>(M, n, q, in, out, LineScale{}, s));
+  else KLAUNCH(c, kid, left_backward<double>(M, n, q, in, out, LineScale{}, s));
   return LC_OK;
 }
 

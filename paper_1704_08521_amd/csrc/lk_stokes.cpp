@@ -17,6 +17,7 @@
 #include "lk_ctx.h"
 #include "lk_internal.h"
 #include "lk_linalg.h"
+#include "lk_lines.h"
 #include "lk_modes.h"
 
 using namespace lk;
@@ -93,60 +94,17 @@ int viscous_scales(lc_ctx* c, double dt) {
 // + l_x[i], backward transforms with S.  in, out: distinct; tmp: one component of scratch.
 int tp3(lc_ctx* c, const AxisModes& X, const AxisModes& Y, const AxisModes& Z, int Lx, int Ly, int Lz,
         const double* sx, const double* sy, const double* sz, const double* in, double* out, double* tmp) {
-  const long pl = (long)Lx * Ly;
-  const int n_yz = Ly * Lz, n_xz = Lx * Lz;
+  const int pl = Lx * Ly;
+  const size_t elems = (size_t)pl * Lz;
   hipStream_t s = c->stream;
-  const double* nul = nullptr;
-  // forward x: in -> tmp
-  if (X.mf)
-    KLAUNCH(c, LC_K_TP_X, launch_mff_right<double>(Lx, n_yz, in, X.p64[0], X.p64[1], tmp, s));
-  else if (X.sym)
-    KLAUNCH(c, LC_K_TP_X, launch_tpf_right<double>(Lx, n_yz, in, X.h64[4], X.h64[5], tmp, s));
-  else
-    KLAUNCH(c, LC_K_TP_X, launch_tp_right<double>(n_yz, Lx, Lx, in, X.FT, tmp, s));
-  // forward y: tmp -> out
-  if (Y.mf)
-    KLAUNCH(c, LC_K_TP_Y, launch_mff_left<double>(Ly, n_xz, Y.p64[0], Y.p64[1], tmp, out, Lx, pl, Lx, s));
-  else if (Y.sym)
-    KLAUNCH(c, LC_K_TP_Y, launch_tpf_left<double>(Ly, n_xz, Y.h64[0], Y.h64[1], tmp, out, Lx, pl, Lx, nul, nul, nul,
-                                                  1, 0, 0, 0, s));
-  else
-    KLAUNCH(c, LC_K_TP_Y,
-            launch_tp_left<double>(Ly, n_xz, Ly, Y.F, tmp, out, Lx, pl, Lx, nul, nul, nul, 1, 0, 0, 0, s));
-  // forward z: out -> tmp (the division here unless the backward matrix-core transform takes it)
-  if (Z.mf)
-    KLAUNCH(c, LC_K_TP_Z, launch_mff_left<double>(Lz, (int)pl, Z.p64[0], Z.p64[1], out, tmp, (int)pl, 0, pl, s));
-  else if (Z.sym)
-    KLAUNCH(c, LC_K_TP_Z, launch_tpf_left<double>(Lz, (int)pl, Z.h64[0], Z.h64[1], out, tmp, (int)pl, 0, pl, sz, sy,
-                                                  sx, Lx, -1, -1, -1, s));
-  else
-    KLAUNCH(c, LC_K_TP_Z, launch_tp_left<double>(Lz, (int)pl, Lz, Z.F, out, tmp, (int)pl, 0, pl, sz, sy, sx, Lx, -1,
-                                                 -1, -1, s));
-  // backward z: tmp -> out
-  if (Z.mf)
-    KLAUNCH(c, LC_K_TP_Z, launch_mfu_left<double>(Lz, (int)pl, Z.p64[2], Z.p64[3], tmp, out, (int)pl, 0, pl, sz, sy,
-                                                  sx, Lx, -1, -1, -1, s));
-  else if (Z.sym)
-    KLAUNCH(c, LC_K_TP_Z, launch_tpu_left<double>(Lz, (int)pl, Z.h64[2], Z.h64[3], tmp, out, (int)pl, 0, pl, s));
-  else
-    KLAUNCH(c, LC_K_TP_Z, launch_tp_left<double>(Lz, (int)pl, Lz, Z.Bk, tmp, out, (int)pl, 0, pl, nul, nul, nul, 1,
-                                                 0, 0, 0, s));
-  // backward y: out -> tmp
-  if (Y.mf)
-    KLAUNCH(c, LC_K_TP_Y, launch_mfu_left<double>(Ly, n_xz, Y.p64[2], Y.p64[3], out, tmp, Lx, pl, Lx, nul, nul, nul,
-                                                  1, 0, 0, 0, s));
-  else if (Y.sym)
-    KLAUNCH(c, LC_K_TP_Y, launch_tpu_left<double>(Ly, n_xz, Y.h64[2], Y.h64[3], out, tmp, Lx, pl, Lx, s));
-  else
-    KLAUNCH(c, LC_K_TP_Y,
-            launch_tp_left<double>(Ly, n_xz, Ly, Y.Bk, out, tmp, Lx, pl, Lx, nul, nul, nul, 1, 0, 0, 0, s));
-  // backward x: tmp -> out
-  if (X.mf)
-    KLAUNCH(c, LC_K_TP_X, launch_mfu_right<double>(Lx, n_yz, tmp, X.p64[2], X.p64[3], out, s));
-  else if (X.sym)
-    KLAUNCH(c, LC_K_TP_X, launch_tpu_right<double>(Lx, n_yz, tmp, X.h64[6], X.h64[7], out, s));
-  else
-    KLAUNCH(c, LC_K_TP_X, launch_tp_right<double>(n_yz, Lx, Lx, tmp, X.BkT, out, s));
+  const Columns cy{Lx * Lz, Lx, pl, Lx, elems}, cz{pl, pl, 0, pl, elems};
+  const LineScale none, sc{sz, sy, sx, Lx, -1, -1, -1};
+  KLAUNCH(c, LC_K_TP_X, right_forward<double>(X, Lx, Ly * Lz, in, tmp, s));
+  KLAUNCH(c, LC_K_TP_Y, left_forward<double>(Y, Ly, cy, tmp, out, none, s));
+  KLAUNCH(c, LC_K_TP_Z, left_forward<double>(Z, Lz, cz, out, tmp, sc, s));
+  KLAUNCH(c, LC_K_TP_Z, left_backward<double>(Z, Lz, cz, tmp, out, sc, s));
+  KLAUNCH(c, LC_K_TP_Y, left_backward<double>(Y, Ly, cy, out, tmp, none, s));
+  KLAUNCH(c, LC_K_TP_X, right_backward<double>(X, Lx, Ly * Lz, tmp, out, s));
   return LC_OK;
 }
 

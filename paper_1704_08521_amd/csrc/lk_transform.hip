@@ -1184,14 +1184,15 @@ hipError_t launch_mfu_right(int n, int Mlines, const T* A, const T* Pse, const T
 }
 #undef LK_MF_SWITCH
 
-#define LK_MF_INST(T)                                                                                            \
-  template hipError_t launch_mff_left<T>(int, int, const T*, const T*, const T*, T*, int, long, long, hipStream_t); \
-  template hipError_t launch_mfu_left<T>(int, int, const T*, const T*, const T*, T*, int, long, long, const double*, \
-                                         const double*, const double*, int, int, int, int, hipStream_t);          \
-  template hipError_t launch_mff_right<T>(int, int, const T*, const T*, const T*, T*, hipStream_t);                \
+#define LK_MF_INST(T)                                                                                     \
+  template hipError_t launch_mff_right<T>(int, int, const T*, const T*, const T*, T*, hipStream_t);         \
   template hipError_t launch_mfu_right<T>(int, int, const T*, const T*, const T*, T*, hipStream_t);
 LK_MF_INST(double)
 LK_MF_INST(float)
+template hipError_t launch_mff_left<float>(int, int, const float*, const float*, const float*, float*, int, long, long,
+                                           hipStream_t);
+template hipError_t launch_mfu_left<float>(int, int, const float*, const float*, const float*, float*, int, long, long,
+                                           const double*, const double*, const double*, int, int, int, int, hipStream_t);
 #undef LK_MF_INST
 
 }  // namespace lk
