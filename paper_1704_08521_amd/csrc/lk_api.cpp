@@ -90,22 +90,53 @@ double now_ms() {
   return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
 }
 
-// Fixed-order reduction of partials on the device, then one scalar to the host.
-int reduce_to_host(lc_ctx* c, int nparts, double* out) {
-  KLAUNCH(c, LC_K_REDUCE, launch_sum(c->partials, nparts, c->dsum, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->hsum, c->dsum, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  *out = *c->hsum;
+// Where the terms of slot `slot` go: to the host when it adds them itself, else to the device scratch.
+static double* parts_of(lc_ctx* c, int slot, int nparts) {
+  return nparts <= kHostParts ? c->hsum_d + kSumSlots + (size_t)slot * kHostParts : c->partials;
+}
+
+static int finish_queue(lc_ctx* c, int slot, int nparts) {
+  c->pending[slot] = nparts <= kHostParts ? nparts : 0;
+  if (nparts > kHostParts) KLAUNCH(c, LC_K_REDUCE, launch_sum(c->partials, nparts, c->hsum_d + slot, c->stream));
   return LC_OK;
 }
 
+int div_queue(lc_ctx* c, const double* v, double* r, int slot) {
+  const int np = divergence_parts(c->nx, c->ny, c->nz);
+  KLAUNCH(c, LC_K_DIVERGENCE, launch_divergence(c->g, v, r, parts_of(c, slot, np), c->stream));
+  return finish_queue(c, slot, np);
+}
+
+int dot_queue(lc_ctx* c, const double* a, const double* b, int slot) {
+  int np = dot_parts(c->nvel);
+  KLAUNCH(c, LC_K_VECTOR, launch_dot_partials(a, b, c->nvel, parts_of(c, slot, np), &np, c->stream));
+  return finish_queue(c, slot, np);
+}
+
+int sums_wait(lc_ctx* c) {
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  return LC_OK;
+}
+
+// The terms in the order of the reduction kernel (launch_sum): a tree over 1024 of them.
+double sum_of(const lc_ctx* c, int slot) {
+  const int n = c->pending[slot];
+  if (!n) return c->hsum[slot];
+  static_assert(kHostParts <= 1024, "one term per thread of the reduction kernel");
+  double t[kHostParts];
+  std::memcpy(t, c->hsum + kSumSlots + (size_t)slot * kHostParts, n * sizeof(double));
+  int m = n;
+  for (int w = 512; w > 0; w >>= 1) {
+    for (int i = 0; i + w < m; ++i) t[i] += t[i + w];
+    m = std::min(m, w);
+  }
+  return t[0];
+}
+
 int vnorm_div(lc_ctx* c, const double* v, double* r, double* out) {
-  int np = 0;
-  KLAUNCH(c, LC_K_DIVERGENCE, launch_divergence(c->g, v, r, c->partials, &np, c->stream));
-  double s2 = 0.0;
-  int rc = reduce_to_host(c, np, &s2);
-  if (rc) return rc;
-  *out = std::sqrt(s2);
+  int rc = div_queue(c, v, r, 0);
+  if (rc || (rc = sums_wait(c))) return rc;
+  *out = std::sqrt(sum_of(c, 0));
   return LC_OK;
 }
 
@@ -218,17 +249,17 @@ int check_ready(lc_ctx* c) {
 bool aligned(const void* p) { return p && ((uintptr_t)p % 8 == 0); }
 
 int reduce_max_to_host(lc_ctx* c, int nparts, double* out) {
-  KLAUNCH(c, LC_K_REDUCE, launch_max(c->partials, nparts, c->dsum, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->hsum, c->dsum, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  KLAUNCH(c, LC_K_REDUCE, launch_max(c->partials, nparts, c->hsum_d, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  *out = *c->hsum;
+  *out = c->hsum[0];
   return LC_OK;
 }
 
 int vdot(lc_ctx* c, const double* a, const double* b, double* out) {
-  int np = 0;
-  KLAUNCH(c, LC_K_VECTOR, launch_dot_partials(a, b, c->nvel, c->partials, &np, c->stream));
-  return reduce_to_host(c, np, out);
+  int rc = dot_queue(c, a, b, 0);
+  if (rc || (rc = sums_wait(c))) return rc;
+  *out = sum_of(c, 0);
+  return LC_OK;
 }
 
 int vmaxabs(lc_ctx* c, const double* a, double* out) {
@@ -277,9 +308,7 @@ void init_dims(lc_ctx* c, int nx, int ny, int nz) {
   c->nvel = vel_layout(nx, ny, nz).total();
   c->ncell = (size_t)nx * ny * nz;
   c->max_parts = (int)((c->ncell + kReduceBlock - 1) / kReduceBlock) + kGsBlocks * kGsChunk;
-  // the divergence kernel: 64 x 4 cells x 4 planes per block
-  const size_t nd = (size_t)((nx + 63) / 64) * ((ny + 3) / 4) * ((nz + 3) / 4);
-  if (nd > (size_t)c->max_parts) c->max_parts = (int)nd;
+  c->max_parts = std::max(c->max_parts, divergence_parts(nx, ny, nz));
 }
 
 // The context's device buffers, in a fixed order.  With a caller workspace (or a dry run)
@@ -292,7 +321,7 @@ bool carve_all(lc_ctx* c) {
             dalloc(c, &c->t1, c->ncell) == hipSuccess && dalloc(c, &c->t2, c->ncell) == hipSuccess &&
             dalloc(c, &c->r32, c->ncell) == hipSuccess && dalloc(c, &c->t1_32, c->ncell) == hipSuccess &&
             dalloc(c, &c->t2_32, c->ncell) == hipSuccess && dalloc(c, &c->partials, c->max_parts) == hipSuccess &&
-            dalloc(c, &c->dsum, 1) == hipSuccess && dalloc(c, &c->dsmall, kSmall) == hipSuccess;
+            dalloc(c, &c->dsmall, kSmall) == hipSuccess;
   if (!ok || !(c->arena || c->dry)) return ok;
   const int nx = c->nx, ny = c->ny, nz = c->nz;
   size_t mbytes = 0;
@@ -338,7 +367,10 @@ int create(lc_ctx** out, int nx, int ny, int nz, void* ws, size_t ws_bytes, void
     return fail(nullptr, LC_ENOMEM, "device allocation failed for %dx%dx%d", nx, ny, nz);
   }
   ok = hipHostMalloc((void**)&c->hsmall, kSmall * sizeof(double), hipHostMallocDefault) == hipSuccess &&
-       hipHostMalloc((void**)&c->hsum, sizeof(double), hipHostMallocDefault) == hipSuccess;
+       hipHostMalloc((void**)&c->hsum, kSumSlots * (1 + kHostParts) * sizeof(double), hipHostMallocDefault) ==
+           hipSuccess &&
+       hipHostGetDevicePointer((void**)&c->hsmall_d, c->hsmall, 0) == hipSuccess &&
+       hipHostGetDevicePointer((void**)&c->hsum_d, c->hsum, 0) == hipSuccess;
   if (!ok) {
     lc_destroy(c);
     return fail(nullptr, LC_ENOMEM, "pinned host allocation failed");
@@ -392,7 +424,7 @@ int lc_destroy(lc_ctx* c) {
   else (void)hipDeviceSynchronize();
   if (!c->arena) {  // carved buffers belong to the caller's workspace
     void* ptrs[] = {c->U, c->w, c->r, c->phi, c->t1, c->t2, c->r32, c->t1_32, c->t2_32, c->partials,
-                    c->dsum, c->metric, c->modes_mem, c->dsmall, c->kws, c->ucr, c->stokes_mem, c->vscale, c->hs};
+                    c->metric, c->modes_mem, c->dsmall, c->kws, c->ucr, c->stokes_mem, c->vscale, c->hs};
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
   }
@@ -599,9 +631,23 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   lc_stats& S = st ? *st : local;
   std::memset(&S, 0, sizeof S);
   S.guess_eps = 1.0;
-  double n0 = 0.0;
-  rc = vnorm_div(c, w, c->r, &n0);
-  if (rc) return rc;
+  // One pass of the SIMPLE loop (Section 3): solve, correct, certify (slot 1).  The certificate of an FP64
+  // pass (exact solve: it nearly always ends the loop) only reduces the norm; D v is then written
+  // again if another pass needs it.  FP32 passes (one more always follows at tight tolerances)
+  // keep D v from the certificate.
+  const int pass_precision = precision == LC_LEARNED ? LC_MIXED : precision;
+  const bool keep_r = pass_precision != LC_FP64;
+  auto pass = [&](bool accumulate) -> int {
+    int e = poisson(c, c->r, c->phi, pass_precision);
+    if (e) return e;
+    KLAUNCH(c, LC_K_CORRECT, launch_correct(c->g, w, c->phi, v, p, accumulate, c->stream));
+    return div_queue(c, v, keep_r ? c->r : nullptr, 1);
+  };
+  // The first pass does not depend on |D w|, so without a guess it is queued behind it and both norms
+  // come with one wait.
+  const bool ahead = precision != LC_LEARNED;
+  if ((rc = div_queue(c, w, c->r, 0)) || (ahead && (rc = pass(false))) || (rc = sums_wait(c))) return rc;
+  const double n0 = std::sqrt(sum_of(c, 0));
   if (!std::isfinite(n0)) return fail(c, LC_EINVAL, "non-finite input");
   S.rho0 = n0;
   if (n0 == 0.0) {
@@ -615,7 +661,6 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   // Learned form: the network's correction starts the loop (v = w - G phi0, p = phi0),
   // then mixed-precision passes; without gain it falls back to v = w, p = 0.
   bool started = false;
-  const int pass_precision = precision == LC_LEARNED ? LC_MIXED : precision;
   if (precision == LC_LEARNED) {
     double fit = 1.0;
     rc = learned_start(c, w, v, p, &started, &fit);
@@ -635,17 +680,9 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
     }
   }
   // SIMPLE loop (Section 3): v = w, p = 0; repeat {solve; v -= G phi; p += phi}
-  // The certificate of an FP64 pass (exact solve: it nearly always ends the loop) only
-  // reduces the norm; D v is then written again if another pass needs it.  FP32 passes
-  // (one more always follows at tight tolerances) keep D v from the certificate.
   for (int it = 0; it < max_iter; ++it) {
-    rc = poisson(c, c->r, c->phi, pass_precision);
-    if (rc) return rc;
-    KLAUNCH(c, LC_K_CORRECT, launch_correct(c->g, w, c->phi, v, p, started || it > 0, c->stream));
-    double nk = 0.0;
-    const bool keep_r = pass_precision != LC_FP64;
-    rc = vnorm_div(c, v, keep_r ? c->r : nullptr, &nk);
-    if (rc) return rc;
+    if (!(ahead && it == 0) && ((rc = pass(started || it > 0)) || (rc = sums_wait(c)))) return rc;
+    double nk = std::sqrt(sum_of(c, 1));
     if (!keep_r && nk / n0 > tol && it + 1 < max_iter) {
       rc = vnorm_div(c, v, c->r, &nk);
       if (rc) return rc;
@@ -691,9 +728,7 @@ int lc_krylov_vector(lc_ctx* c, const double* vin, double* vout, double* pout, i
 
 int lc_dot(lc_ctx* c, const double* a, const double* b, double* out) {
   if (!c || !aligned(a) || !aligned(b) || !out) return fail(c, LC_EINVAL, "bad pointers");
-  int np = 0;
-  KLAUNCH(c, LC_K_VECTOR, launch_dot_partials(a, b, c->nvel, c->partials, &np, c->stream));
-  return reduce_to_host(c, np, out);
+  return vdot(c, a, b, out);
 }
 
 }  // extern "C"

@@ -56,6 +56,13 @@ struct AxisModes {
 
 }  // namespace lk
 
+namespace lk {
+constexpr int kSumSlots = 3;
+// Sums of at most this many terms are added by the host: a reduction kernel costs a launch of about 4 us, the
+// terms about 1 us on their way and in the sum (a 64^3 Krylov vector has 256 of them, 100^3 1250).
+constexpr int kHostParts = 1024;
+}  // namespace lk
+
 struct lc_ctx {
   using AxisHost = lk::AxisHost;
   using AxisModes = lk::AxisModes;
@@ -82,8 +89,11 @@ struct lc_ctx {
   float *r32 = nullptr, *t1_32 = nullptr, *t2_32 = nullptr;
   double* partials = nullptr;
   int max_parts = 0;
-  double* dsum = nullptr;   // device scalar
-  double* hsum = nullptr;   // pinned host scalar
+  // Results of reductions, in pinned host memory that the kernels write and the host reads after it
+  // has waited for the stream: per slot the sum and, for sums of few terms, the terms themselves
+  // (kHostParts; the host then adds them in the kernel's order).  hsum_d is the device's address.
+  double *hsum = nullptr, *hsum_d = nullptr;
+  int pending[lk::kSumSlots] = {};  // terms the host has to add (0: the sum is there)
   size_t nvel = 0, ncell = 0;
   // profiling: event pairs around launches on `stream`
   struct Rec {
@@ -94,7 +104,7 @@ struct lc_ctx {
   double* kws = nullptr;
   size_t kws_n = 0;
   double* dsmall = nullptr;  // kSmall doubles
-  double* hsmall = nullptr;  // kSmall doubles, pinned
+  double *hsmall = nullptr, *hsmall_d = nullptr;  // kSmall doubles, pinned (and the device's address)
   double* ucr = nullptr;     // critical-Re driver: two stored steady states + a residual
   lc_net* net = nullptr;     // learned guess (not owned)
   // Stokes-preconditioned vectors: the viscous step (I/dt - Re^-1 Lap_0)^-1 by the tensor
@@ -153,9 +163,15 @@ hipEvent_t take_event(lc_ctx* c);
 double now_ms();
 bool aligned(const void* p);
 int check_ready(lc_ctx* c);
-// fixed-order device reduction of c->partials (sum or max) to a host scalar
-int reduce_to_host(lc_ctx* c, int nparts, double* out);
+// fixed-order device reduction of c->partials (max) to a host scalar
 int reduce_max_to_host(lc_ctx* c, int nparts, double* out);
+// Sums in two halves, so that several wait together: queue the kernels of slot `slot` (0 .. kSumSlots - 1),
+// wait for the stream, read the slot.  div_queue: sum V (D v)^2 (r receives D v when not null);
+// dot_queue: a . b.
+int div_queue(lc_ctx* c, const double* v, double* r, int slot);
+int dot_queue(lc_ctx* c, const double* a, const double* b, int slot);
+int sums_wait(lc_ctx* c);
+double sum_of(const lc_ctx* c, int slot);
 // |D v|_V (r receives D v when not null)
 int vnorm_div(lc_ctx* c, const double* v, double* r, double* out);
 // pressure-correction solve in the given precision

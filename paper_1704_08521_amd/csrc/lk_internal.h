@@ -49,10 +49,10 @@ inline VelLayout vel_layout(int nx, int ny, int nz) {
 hipError_t launch_momentum(const GridDev& g, const double* a, const double* b, double* out,
                            double rre, bool lid, double lid_u, double lid_v, hipStream_t st);
 
-// r = D v (cell), and per-block partial sums of V r^2 into `partials`
-// (nblocks returned through *nparts; partials may be null).
-hipError_t launch_divergence(const GridDev& g, const double* v, double* r, double* partials,
-                             int* nparts, hipStream_t st);
+// r = D v (cell, may be null), and the divergence_parts() per-block partial sums of V r^2 into
+// `partials` (may be null; device memory, or pinned host memory).
+int divergence_parts(int nx, int ny, int nz);
+hipError_t launch_divergence(const GridDev& g, const double* v, double* r, double* partials, hipStream_t st);
 
 // v = w - G phi (interior faces), zero on walls; p = phi if p != null.
 // If accumulate: v -= G phi in place on v (w ignored) and p += phi.
@@ -62,7 +62,8 @@ hipError_t launch_correct(const GridDev& g, const double* w, const double* phi, 
 // Fixed-order sum of n partials into out[0] (one block).
 hipError_t launch_sum(const double* partials, int n, double* out, hipStream_t st);
 
-// Per-block partial dot products of two arrays of length n.
+// Per-block partial dot products of two arrays of length n (dot_parts of them).
+int dot_parts(size_t n);
 hipError_t launch_dot_partials(const double* a, const double* b, size_t n, double* partials,
                                int* nparts, hipStream_t st);
 
@@ -202,8 +203,9 @@ constexpr int kReduceBlock = 256;
 // Classical Gram-Schmidt: h[i] = V_i . w (i < nv; basis vectors ld apart; h on the device,
 // fixed-order sums), then w -= sum_i h[i] V_i.  partials holds kGsBlocks * kGsChunk doubles.
 constexpr int kGsBlocks = 2048, kGsChunk = 8;
+// host_h (may be null) receives h as well.
 hipError_t launch_gs_dot(const double* V, long ld, int nv, const double* w, size_t n, double* partials,
-                         double* h, hipStream_t st);
+                         double* h, double* host_h, hipStream_t st);
 hipError_t launch_gs_update(const double* V, long ld, int nv, const double* h, double* w, size_t n, hipStream_t st);
 
 }  // namespace lk

@@ -2,6 +2,8 @@
 // fill and wall zeroing.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "lk_device.h"
 
 namespace lk {
@@ -173,9 +175,9 @@ __global__ void __launch_bounds__(kReduceBlock) k_block_dot(const double* __rest
   }
 }
 
-// out[b] = fixed-order sum of partials[b * seg .. b * seg + seg) (one block per segment)
+// out[b] (and out2[b] when not null) = fixed-order sum of partials[b * seg .. b * seg + seg) (one block per segment)
 __global__ void __launch_bounds__(1024) k_sum_segments(const double* __restrict__ partials, int seg,
-                                                       double* __restrict__ out) {
+                                                       double* __restrict__ out, double* __restrict__ out2) {
   __shared__ double sh[1024];
   const double* p = partials + (size_t)blockIdx.x * seg;
   double t = 0.0;
@@ -186,7 +188,10 @@ __global__ void __launch_bounds__(1024) k_sum_segments(const double* __restrict_
     if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = sh[0];
+  if (threadIdx.x == 0) {
+    out[blockIdx.x] = sh[0];
+    if (out2) out2[blockIdx.x] = sh[0];
+  }
 }
 
 // w -= sum_i h[i] V[i] (i < nv, coefficients from device memory, summed in order i)
@@ -233,14 +238,15 @@ hipError_t launch_combine(const double* V, long ld, int nv, const double* Q, int
 }
 
 hipError_t launch_gs_dot(const double* V, long ld, int nv, const double* w, size_t n, double* partials,
-                         double* h, hipStream_t st) {
+                         double* h, double* host_h, hipStream_t st) {
   unsigned nb = blocks_for(n, kReduceBlock);
   if (nb > (unsigned)kGsBlocks) nb = kGsBlocks;
   for (int i0 = 0; i0 < nv; i0 += kGsChunk) {
     const int cnt = nv - i0 < kGsChunk ? nv - i0 : kGsChunk;
     hipLaunchKernelGGL(k_block_dot<kGsChunk>, dim3(nb), dim3(kReduceBlock), 0, st, V + (size_t)i0 * ld, ld, cnt, w,
                        n, partials);
-    hipLaunchKernelGGL(k_sum_segments, dim3(cnt), dim3(1024), 0, st, partials, (int)nb, h + i0);
+    hipLaunchKernelGGL(k_sum_segments, dim3(cnt), dim3(1024), 0, st, partials, (int)nb, h + i0,
+                       host_h ? host_h + i0 : nullptr);
   }
   return hipGetLastError();
 }
@@ -255,10 +261,11 @@ hipError_t launch_sum(const double* partials, int n, double* out, hipStream_t st
   return hipGetLastError();
 }
 
+int dot_parts(size_t n) { return (int)std::min<size_t>((n + kReduceBlock - 1) / kReduceBlock, 4096); }
+
 hipError_t launch_dot_partials(const double* a, const double* b, size_t n, double* partials, int* nparts,
                                hipStream_t st) {
-  unsigned nb = blocks_for(n, kReduceBlock);
-  if (nb > 4096) nb = 4096;
+  const unsigned nb = (unsigned)dot_parts(n);
   if (nparts) *nparts = (int)nb;
   hipLaunchKernelGGL(k_dot, dim3(nb), dim3(kReduceBlock), 0, st, a, b, n, partials);
   return hipGetLastError();

@@ -100,21 +100,19 @@ int vproject(lc_ctx* c, double* x, double* tmp) {
 // receives the projections, h[nv] the final norm.
 int mgs(lc_ctx* c, const Basis& V, int nv, double* w, double* h) {
   if (nv + 1 > kSmall) return fail(c, LC_EINVAL, "basis too large");
-  double before = 0.0;
-  int rc = vdot(c, w, w, &before);
-  if (rc) return rc;
-  before = vnorm(before);
   std::fill(h, h + nv + 1, 0.0);
-  double after = before;
+  int rc;
+  double before = 0.0, after = 0.0;
   for (int pass = 0; pass < 2; ++pass) {
-    KLAUNCH(c, LC_K_VECTOR, launch_gs_dot(V.at(0), V.ld, nv, w, c->nvel, c->partials, c->dsmall, c->stream));
+    // the norm before, the projections and the norm after come with one wait
+    if (pass == 0 && (rc = dot_queue(c, w, w, 0))) return rc;
+    KLAUNCH(c, LC_K_VECTOR,
+            launch_gs_dot(V.at(0), V.ld, nv, w, c->nvel, c->partials, c->dsmall, c->hsmall_d, c->stream));
     KLAUNCH(c, LC_K_VECTOR, launch_gs_update(V.at(0), V.ld, nv, c->dsmall, w, c->nvel, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->hsmall, c->dsmall, nv * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    double a2 = 0.0;
-    rc = vdot(c, w, w, &a2);  // synchronizes the stream
-    if (rc) return rc;
+    if ((rc = dot_queue(c, w, w, 1)) || (rc = sums_wait(c))) return rc;
+    if (pass == 0) before = vnorm(sum_of(c, 0));
     for (int i = 0; i < nv; ++i) h[i] += c->hsmall[i];
-    after = vnorm(a2);
+    after = vnorm(sum_of(c, 1));
     if (!(after < 0.7071067811865476 * before)) break;
     before = after;
   }

@@ -216,8 +216,10 @@ hipError_t mx_launch(int n, int N, const double* P, const double* B, double* C, 
   const int nw = (int)std::min<long>(MAXW, std::max<long>(1, (tiles * classes + 255) / 256));
   const dim3 grid((unsigned)((tiles + nw - 1) / nw * classes)), block(64 * nw);
   auto run = [&](auto kernel) {
-    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    if (lds > 65536) {  // past the default limit
+      hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(kernel, grid, block, lds, st, n, he, ho, N, P, G, classes, B, C, (unsigned)(8 * elems), nseg,
                        (unsigned)seg_stride, (unsigned)kstride, sc ? *sc : MxScale{});
     return hipGetLastError();

@@ -276,8 +276,7 @@ int learned_start(lc_ctx* c, const double* w, double* v, double* p, bool* used, 
   if ((rc = run_forward(c, n))) return rc;
   KLAUNCH(c, LC_K_NN_MISC, nn_unpack(n->y, c->phi, c->nx, c->ny, c->nz, pad4(c->ny), pad4(c->nx), 1.0, c->stream));
   KLAUNCH(c, LC_K_CORRECT, launch_correct(c->g, w, c->phi, v, nullptr, false, c->stream));
-  int np = 0;
-  KLAUNCH(c, LC_K_DIVERGENCE, launch_divergence(c->g, v, c->t1, nullptr, &np, c->stream));
+  KLAUNCH(c, LC_K_DIVERGENCE, launch_divergence(c->g, v, c->t1, nullptr, c->stream));
   // t1 = D(w - G y) - D w = -D G y
   KLAUNCH(c, LC_K_VECTOR, launch_axpy(c->ncell, -1.0, c->r, c->t1, c->stream));
   const int nb = small_blocks((long)c->ncell);

@@ -474,14 +474,16 @@ hipError_t launch_momentum(const GridDev& g, const double* a, const double* b, d
   return hipGetLastError();
 }
 
-hipError_t launch_divergence(const GridDev& g, const double* v, double* r, double* partials, int* nparts,
-                             hipStream_t st) {
+int divergence_parts(int nx, int ny, int nz) {
+  return (int)(blocks_for(nx, kDivTX) * blocks_for(ny, kDivTY) * blocks_for(nz, kDivKZ));
+}
+
+hipError_t launch_divergence(const GridDev& g, const double* v, double* r, double* partials, hipStream_t st) {
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
   const VelLayout L = vel_layout(nx, ny, nz);
   Vel V{v, v + L.ov(), v + L.ow(), Idx{nx, ny, nz}};
   const int nbx = (int)blocks_for(nx, kDivTX), nby = (int)blocks_for(ny, kDivTY);
-  const unsigned nb = (unsigned)(nbx * nby * (int)blocks_for(nz, kDivKZ));
-  if (nparts) *nparts = (int)nb;
+  const unsigned nb = (unsigned)divergence_parts(nx, ny, nz);
   hipLaunchKernelGGL(k_divergence<kDivKZ>, dim3(nb), dim3(kDivTX * kDivTY), 0, st, g, V, r, partials, nbx, nby);
   return hipGetLastError();
 }
