@@ -29,7 +29,8 @@ __host__ __device__ constexpr long conv_wf_elems(int cout, int cin) {
 // FP32; the input is the masked output gradient passed as `b`.
 hipError_t nn_conv(int layer, bool backward, const bf16* a, const bf16* b, const bf16* wt, const float* bias, void* out,
                    int D, int H, int W, hipStream_t st);
-// per-block partial weight gradients of layer `layer` ([nblk][27][cout][cin])
+// per-block partial weight gradients of layer `layer` ([nblk][27][cout][cin]), nblk <= nn_wgrad_bricks()
+long nn_wgrad_bricks(int D, int H, int W);
 hipError_t nn_wgrad(int layer, const bf16* a, const bf16* b, const bf16* dy, float* part, int nblk, int D, int H, int W,
                     hipStream_t st);
 hipError_t nn_wgrad_reduce(const float* part, float* grad, int nblk, int cout, int cin, int cin_real, hipStream_t st);

@@ -274,83 +274,130 @@ __global__ __launch_bounds__(kBlock) void k_conv_rows(const bf16* __restrict__ s
 }
 
 // --------------------------------------------------------------- weight gradient
-// part[blk][tap][co][CIN] = sum over the block's voxels p of dy[p][co] X_tap[p][ci],
-// X_tap[p] = input at p + offset(tap) (zero outside), sources as in k_conv.
-// Grid (nblk, 27).  Each wave reduces over 32-voxel slices (MFMA k = voxel), the
-// four waves of a block are summed in LDS; the host sums the blocks in order.
-template <int CIN, int COUT, int CA>
-__global__ __launch_bounds__(kBlock) void k_wgrad(const bf16* __restrict__ srcA, const bf16* __restrict__ srcB,
-                                                  const bf16* __restrict__ dy, float* __restrict__ part, int D, int H,
-                                                  int W, long vox_per_block) {
-  constexpr int MB = COUT / 16;
-  constexpr int NC = (CIN + 15) / 16;
-  constexpr int CB = CIN - CA;
-  __shared__ float red[4][MB * NC * 256];
-  const long P = (long)D * H * W;
-  const int tap = blockIdx.y;
-  const int dz = tap / 9 - 1, ddy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-  const int wave = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63;
-  const int g = lane >> 4;
-  const int r16 = lane & 15;
+// part[blk][tap][co][CIN] = sum over the block's voxels q of dy[q - offset(tap)][co] X[q][ci] (zero outside the
+// grid), sources as in k_conv: on the matrix cores a product of dy^T and X with 32 voxels of a row as the
+// contracted index.  A block loops over bricks of 32 x 4 x 2 voxels: the rows of X and, with a halo, of dy
+// are staged channel-major in LDS, so that a lane's eight consecutive voxels of one channel are one
+// 16-byte read (the first version gathered them as 2-byte loads, one block per tap: 288 us for the 48 -> 16
+// layer at 64^3, 237 us for 8 -> 16).  Wave dz + 1 does the nine taps of its dz: it reads a row of X once, the
+// three rows of dy its taps meet it with once each, and makes the two shifts along x from registers.
+// Grid (nblk, COUT / 16 x CIN tiles / NCS): a block does 16 output channels and NCS tiles of 16 input
+// channels (9 NCS accumulators).
+constexpr int kWGX = 32, kWGY = 4, kWGZ = 2;
+constexpr int kWGRow = 48;  // dy row in LDS: 8 voxels left of the brick (two used), 32, 8 right (two used)
+
+template <int CIN, int COUT, int CA, int NCS>
+__global__ __launch_bounds__(192) void k_wgrad(const bf16* __restrict__ srcA, const bf16* __restrict__ srcB,
+                                               const bf16* __restrict__ dy, float* __restrict__ part, int D, int H,
+                                               int W) {
+  constexpr int NC = (CIN + 15) / 16, CB = CIN - CA, NT = 192;
+  static_assert(NC % NCS == 0 && COUT % 16 == 0 && CIN % 8 == 0, "channel tiles");
+  __shared__ __attribute__((aligned(16))) bf16 xs[kWGZ * kWGY][NCS * 16][kWGX];
+  __shared__ __attribute__((aligned(16))) bf16 ds[(kWGZ + 2) * (kWGY + 2)][16][kWGRow];
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15;
+  const int dz = (tid >> 6) - 1;
+  const int co0 = (blockIdx.y % (COUT / 16)) * 16, ci0 = (blockIdx.y / (COUT / 16)) * (NCS * 16);
   const int H2 = H >> 1, W2 = W >> 1;
-  const long p_begin = (long)blockIdx.x * vox_per_block;
-  const long p_end = p_begin + vox_per_block < P ? p_begin + vox_per_block : P;
-  floatx4 acc[MB][NC];
+  const int nbx = (W + kWGX - 1) / kWGX, nby = (H + kWGY - 1) / kWGY, nbz = (D + kWGZ - 1) / kWGZ;
+  floatx4 acc[9][NCS];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int nc = 0; nc < NC; ++nc) acc[mb][nc] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (long p0 = p_begin + 32 * wave; p0 < p_end; p0 += 128) {
-    bf16x8 a[MB], b[NC];
+    for (int c = 0; c < NCS; ++c) acc[t][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const bf16x8 zero = {};
+  // two voxels of eight channels as eight pairs, one per channel
+  auto put_pairs = [](bf16* row0, int rstride, bf16x8 a, bf16x8 b) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const long p = p0 + 8 * g + j;
-      const bool vin = p < p_end;
-      const long q = vin ? p : p_begin;
-      const int x = (int)(q % W), y = (int)((q / W) % H), z = (int)(q / ((long)W * H));
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const bf16 v = dy[q * COUT + mb * 16 + r16];
-        a[mb][j] = vin ? v : f2bf(0.f);
+    for (int c = 0; c < 8; ++c) {
+      typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+      *reinterpret_cast<bf16x2*>(row0 + c * rstride) = bf16x2{a[c], b[c]};
+    }
+  };
+  for (int br = blockIdx.x; br < nbx * nby * nbz; br += gridDim.x) {
+    const int x0 = (br % nbx) * kWGX, y0 = ((br / nbx) % nby) * kWGY, z0 = (br / (nbx * nby)) * kWGZ;
+    // (a row of odd length, at quarter resolution, ends in half a pair)
+    for (int e = tid; e < kWGZ * kWGY * (kWGX / 2) * (NCS * 2); e += NT) {
+      const int xp = e % (kWGX / 2), row = (e / (kWGX / 2)) % (kWGZ * kWGY), c8 = e / (kWGX / 2 * kWGZ * kWGY);
+      const int x = x0 + 2 * xp, y = y0 + row % kWGY, z = z0 + row / kWGY, ci = ci0 + 8 * c8;
+      bf16x8 a = zero, b = zero;
+      if (x < W && y < H && z < D && ci < CIN) {
+        if (CA > 0 && ci < CA) {
+          a = *reinterpret_cast<const bf16x8*>(srcA + (((long)(z >> 1) * H2 + (y >> 1)) * W2 + (x >> 1)) * CA + ci);
+          b = a;  // one half-resolution voxel under both
+        } else {
+          const bf16* p = srcB + (((long)z * H + y) * W + x) * CB + (ci - CA);
+          a = *reinterpret_cast<const bf16x8*>(p);
+          if (x + 1 < W) b = *reinterpret_cast<const bf16x8*>(p + CB);
+        }
       }
-      const int zz = z + dz, yy = y + ddy, xx = x + dx;
-      const bool ok = vin && (unsigned)zz < (unsigned)D && (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W;
-      const int zc = ok ? zz : 0, yc = ok ? yy : 0, xc = ok ? xx : 0;
+      put_pairs(&xs[row][8 * c8][2 * xp], kWGX, a, b);
+    }
+    constexpr int DP = kWGX / 2 + 2;  // pairs of a dy row, one beyond the brick on either side
+    for (int e = tid; e < (kWGZ + 2) * (kWGY + 2) * DP * 2; e += NT) {
+      const int xp = e % DP, row = (e / DP) % ((kWGZ + 2) * (kWGY + 2)), c8 = e / (DP * (kWGZ + 2) * (kWGY + 2));
+      const int x = x0 - 2 + 2 * xp, y = y0 - 1 + row % (kWGY + 2), z = z0 - 1 + row / (kWGY + 2);
+      bf16x8 a = zero, b = zero;
+      if ((unsigned)x < (unsigned)W && (unsigned)y < (unsigned)H && (unsigned)z < (unsigned)D) {
+        const bf16* p = dy + (((long)z * H + y) * W + x) * COUT + co0 + 8 * c8;
+        a = *reinterpret_cast<const bf16x8*>(p);
+        if (x + 1 < W) b = *reinterpret_cast<const bf16x8*>(p + COUT);
+      }
+      put_pairs(&ds[row][8 * c8][6 + 2 * xp], kWGRow, a, b);
+    }
+    __syncthreads();
+    for (int row = 0; row < kWGZ * kWGY; ++row) {
+      const int ty = row % kWGY, tz = row / kWGY;
+      bf16x8 x[NCS];
 #pragma unroll
-      for (int nc = 0; nc < NC; ++nc) {
-        const int ci = nc * 16 + r16;
-        const bool cok = ok && ci < CIN;
-        const int cc = ci < CIN ? ci : 0;
-        const bf16* ptr;
-        if (CA > 0 && cc < CA)
-          ptr = srcA + (((long)(zc >> 1) * H2 + (yc >> 1)) * W2 + (xc >> 1)) * CA + cc;
-        else
-          ptr = srcB + (((long)zc * H + yc) * W + xc) * CB + (cc - CA);
-        const bf16 v = *ptr;
-        b[nc][j] = cok ? v : f2bf(0.f);
+      for (int c = 0; c < NCS; ++c) x[c] = *reinterpret_cast<const bf16x8*>(&xs[row][c * 16 + r16][8 * g]);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {  // offset d - 1 along y: dy rows y - (d - 1), z - dz
+        const bf16* p = &ds[(tz - dz + 1) * (kWGY + 2) + ty - (d - 1) + 1][r16][8 + 8 * g];
+        const u32x4 m = *reinterpret_cast<const u32x4*>(p);
+        const unsigned lo = *reinterpret_cast<const unsigned*>(p - 2), hi = *reinterpret_cast<const unsigned*>(p + 8);
+        // the row shifted one voxel up (x - 1 at x) and down (x + 1 at x)
+        const u32x4 up = {(m.x << 16) | (lo >> 16), (m.y << 16) | (m.x >> 16), (m.z << 16) | (m.y >> 16),
+                          (m.w << 16) | (m.z >> 16)};
+        const u32x4 dn = {(m.x >> 16) | (m.y << 16), (m.y >> 16) | (m.z << 16), (m.z >> 16) | (m.w << 16),
+                          (m.w >> 16) | (hi << 16)};
+        const bf16x8 f[3] = {__builtin_bit_cast(bf16x8, dn), __builtin_bit_cast(bf16x8, m),
+                             __builtin_bit_cast(bf16x8, up)};  // offsets -1, 0, +1 along x
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+          for (int c = 0; c < NCS; ++c)
+            acc[3 * d + t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t], x[c], acc[3 * d + t][c], 0, 0, 0);
       }
     }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nc = 0; nc < NC; ++nc) acc[mb][nc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mb], b[nc], acc[mb][nc], 0, 0, 0);
+    __syncthreads();
   }
-  // result tile (mb, nc): lane holds rows co = mb*16 + 4g + j, column ci = nc*16 + r16
+  // a lane holds rows co = co0 + 4g + j, column ci = ci0 + 16 c + r16
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int t = 0; t < 9; ++t) {
+    float* dst = part + ((long)blockIdx.x * 27 + (dz + 1) * 9 + t) * COUT * CIN;
 #pragma unroll
-    for (int nc = 0; nc < NC; ++nc)
+    for (int c = 0; c < NCS; ++c) {
+      const int ci = ci0 + 16 * c + r16;
+      if (ci >= CIN) continue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) red[wave][(mb * NC + nc) * 256 + (4 * g + j) * 16 + r16] = acc[mb][nc][j];
-  __syncthreads();
-  float* dst = part + ((long)blockIdx.x * 27 + tap) * COUT * CIN;
-  for (int e = threadIdx.x; e < MB * NC * 256; e += kBlock) {
-    const int tile = e >> 8, within = e & 255;
-    const int mb = tile / NC, nc = tile % NC;
-    const int co = mb * 16 + (within >> 4), ci = nc * 16 + (within & 15);
-    if (ci < CIN) dst[co * CIN + ci] = red[0][e] + red[1][e] + red[2][e] + red[3][e];
+      for (int j = 0; j < 4; ++j) dst[(co0 + 4 * g + j) * CIN + ci] = acc[t][c][j];
+    }
   }
+}
+
+// s + x[0] + x[stride] + ... + x[(n - 1) stride], in this order, with kSumAhead terms in flight.
+constexpr int kSumAhead = 16;
+__device__ __forceinline__ float sum_strided(const float* __restrict__ x, long stride, int n, float s) {
+  int b = 0;
+  for (; b + kSumAhead <= n; b += kSumAhead) {
+    float v[kSumAhead];
+#pragma unroll
+    for (int q = 0; q < kSumAhead; ++q) v[q] = x[(long)(b + q) * stride];
+#pragma unroll
+    for (int q = 0; q < kSumAhead; ++q) s += v[q];
+  }
+  for (; b < n; ++b) s += x[(long)b * stride];
+  return s;
 }
 
 // grad[(co*27 + tap)*cin_real + ci] = sum_b part[b][tap][co][ci] (fixed order)
@@ -361,36 +408,42 @@ __global__ void k_wgrad_reduce(const float* __restrict__ part, float* __restrict
   const int ci = e % cin_real;
   const int tap = (e / cin_real) % 27;
   const int co = e / (cin_real * 27);
-  float s = 0.f;
-  for (int b = 0; b < nblk; ++b) s += part[(((long)b * 27 + tap) * cout + co) * cin + ci];
-  grad[e] = s;
+  grad[e] = sum_strided(part + ((long)tap * cout + co) * cin + ci, 27L * cout * cin, nblk, 0.f);
 }
 
-// per-block channel sums of a [P][C] BF16 tensor (C divides 256)
+// per-block channel sums of a [P][C] BF16 tensor (C a multiple of 8 that divides 2048), eight channels
+// of a voxel per thread and load
 __global__ __launch_bounds__(kBlock) void k_colsum(const bf16* __restrict__ x, float* __restrict__ part, long P, int C,
                                                    long vox_per_block) {
-  __shared__ float sm[kBlock];
-  const long e0 = (long)blockIdx.x * vox_per_block * C;
-  long e1 = e0 + vox_per_block * C;
-  if (e1 > P * C) e1 = P * C;
-  float s = 0.f;
-  for (long e = e0 + threadIdx.x; e < e1; e += kBlock) s += bf2f(x[e]);
-  sm[threadIdx.x] = s;
+  __shared__ float sm[8][kBlock];
+  const long e0 = (long)blockIdx.x * vox_per_block * (C / 8), n8 = P * (C / 8);
+  const long e1 = e0 + vox_per_block * (C / 8) < n8 ? e0 + vox_per_block * (C / 8) : n8;
+  float s[8] = {};
+  for (long e = e0 + threadIdx.x; e < e1; e += kBlock) {
+    const bf16x8 v = *reinterpret_cast<const bf16x8*>(x + 8 * e);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) s[c] += bf2f(v[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) sm[c][threadIdx.x] = s[c];
   __syncthreads();
+  // thread t held channels 8 (t % (C / 8)) .. + 7 (the block size and e0 are multiples of C / 8)
   if ((int)threadIdx.x < C) {
+    const int grp = threadIdx.x / 8, c = threadIdx.x % 8;
     float t = 0.f;
-    for (int q = threadIdx.x; q < kBlock; q += C) t += sm[q];
+    for (int q = grp; q < kBlock; q += C / 8) t += sm[c][q];
     part[(long)blockIdx.x * C + threadIdx.x] = t;
   }
 }
 
-// dst[c] = sum_b part[b][c]
-__global__ void k_part_reduce(const float* __restrict__ part, float* __restrict__ dst, int nblk, int C) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
-  float s = 0.f;
-  for (int b = 0; b < nblk; ++b) s += part[(long)b * C + c];
-  dst[c] = s;
+// dst[c] = sum_b part[b][c], c < C <= 64: one block, its four waves take every fourth block's sums
+__global__ __launch_bounds__(256) void k_part_reduce(const float* __restrict__ part, float* __restrict__ dst, int nblk,
+                                                     int C) {
+  __shared__ float sm[4][64];
+  const int c = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (c < C) sm[w][c] = sum_strided(part + (long)w * C + c, 4L * C, (nblk - w + 3) / 4, 0.f);
+  __syncthreads();
+  if (w == 0 && c < C) dst[c] = (sm[0][c] + sm[1][c]) + (sm[2][c] + sm[3][c]);
 }
 
 // ------------------------------------------------------------ pooling, skips
@@ -721,18 +774,21 @@ hipError_t nn_conv(int layer, bool backward, const bf16* a, const bf16* b, const
   return hipGetLastError();
 }
 
+long nn_wgrad_bricks(int D, int H, int W) {
+  return (long)((W + kWGX - 1) / kWGX) * ((H + kWGY - 1) / kWGY) * ((D + kWGZ - 1) / kWGZ);
+}
+
 hipError_t nn_wgrad(int layer, const bf16* a, const bf16* b, const bf16* dy, float* part, int nblk, int D, int H, int W,
                     hipStream_t st) {
-  const long P = (long)D * H * W;
-  const long vpb = ((P + nblk - 1) / nblk + 31) / 32 * 32;
-  const dim3 grid(nblk, 27), blk(kBlock);
-#define WG(CIN, COUT, CA) hipLaunchKernelGGL((k_wgrad<CIN, COUT, CA>), grid, blk, 0, st, a, b, dy, part, D, H, W, vpb)
+#define WG(CIN, COUT, CA, NCS)                                                                               \
+  hipLaunchKernelGGL((k_wgrad<CIN, COUT, CA, NCS>), dim3(nblk, COUT / 16 * ((CIN + 15) / 16) / NCS), dim3(192), 0, \
+                     st, a, b, dy, part, D, H, W)
   switch (layer) {
-    case 0: WG(8, 16, 0); break;
-    case 1: WG(16, 32, 0); break;
-    case 2: WG(32, 64, 0); break;
-    case 3: WG(96, 32, 64); break;
-    case 4: WG(48, 16, 32); break;
+    case 0: WG(8, 16, 0, 1); break;
+    case 1: WG(16, 32, 0, 1); break;
+    case 2: WG(32, 64, 0, 2); break;
+    case 3: WG(96, 32, 64, 3); break;
+    case 4: WG(48, 16, 32, 3); break;
     default: return hipErrorInvalidValue;
   }
 #undef WG
@@ -748,7 +804,7 @@ hipError_t nn_wgrad_reduce(const float* part, float* grad, int nblk, int cout, i
 hipError_t nn_colsum(const bf16* x, float* part, float* dst, long P, int C, int nblk, hipStream_t st) {
   const long vpb = (P + nblk - 1) / nblk;
   hipLaunchKernelGGL(k_colsum, dim3(nblk), dim3(kBlock), 0, st, x, part, P, C, vpb);
-  hipLaunchKernelGGL(k_part_reduce, dim3(1), dim3(64), 0, st, part, dst, nblk, C);
+  hipLaunchKernelGGL(k_part_reduce, dim3(1), dim3(256), 0, st, part, dst, nblk, C);
   return hipGetLastError();
 }
 
@@ -784,7 +840,7 @@ hipError_t nn_loss(const float* y, const float* t, float* dy, double* part, int 
 hipError_t nn_head_bwd(const bf16* d1, const float* wb, const float* dy, bf16* dd1, float* part, float* gdst, int nblk,
                        long P, hipStream_t st) {
   hipLaunchKernelGGL(k_head_bwd, dim3(nblk), dim3(kBlock), 0, st, d1, wb, dy, dd1, part, P);
-  hipLaunchKernelGGL(k_part_reduce, dim3(1), dim3(64), 0, st, part, gdst, nblk, 17);
+  hipLaunchKernelGGL(k_part_reduce, dim3(1), dim3(256), 0, st, part, gdst, nblk, 17);
   return hipGetLastError();
 }
 

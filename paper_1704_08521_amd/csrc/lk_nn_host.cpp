@@ -5,6 +5,7 @@
 // SIMPLE loop with its least-squares scaling and plain fallback.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -25,7 +26,7 @@ struct LayerDesc {
 constexpr LayerDesc kLayers[6] = {{4, 8, 16, 27},   {16, 16, 32, 27}, {32, 32, 64, 27},
                                   {96, 96, 32, 27}, {48, 48, 16, 27}, {16, 16, 1, 1}};
 constexpr int kPartBlocks = 256;   // partial-sum blocks of the small reductions
-constexpr int kWgradBlocks = 128;  // voxel chunks of the weight gradient
+constexpr int kWgradBlocks = 128;  // blocks over the voxels of the weight gradient (partial sums)
 
 long woff(int l) {
   long o = 0;
@@ -165,12 +166,13 @@ int backward(lc_net* n, int D, int H, int W, double* loss, hipStream_t st) {
   NCHK(n, nn_head_bwd(n->d1, n->w + woff(5), n->dy, n->dd1, n->part, g + woff(5), nb, P, st));
   auto wg = [&](int l, const bf16* a, const bf16* b, const bf16* dy, int d, int h, int w_) -> int {
     const long Pl = (long)d * h * w_;
-    long nbw = (Pl + 255) / 256;
-    if (nbw > kWgradBlocks) nbw = kWgradBlocks;
     const LayerDesc& L = kLayers[l];
+    // blocks of the weight gradient: one per brick up to a chip's worth (the layers of 16 output
+    // channels have one block per brick, the others one per brick and channel tile)
+    const long nbw = std::min<long>(nn_wgrad_bricks(d, h, w_), L.cout == 16 ? 2 * kWgradBlocks : kWgradBlocks);
     NCHK(n, nn_wgrad(l, a, b, dy, n->part, (int)nbw, d, h, w_, st));
     NCHK(n, nn_wgrad_reduce(n->part, g + woff(l), (int)nbw, L.cout, L.cinp, L.cin, st));
-    NCHK(n, nn_colsum(dy, n->part, g + boff(l), Pl, L.cout, small_blocks(Pl), st));
+    NCHK(n, nn_colsum(dy, n->part, g + boff(l), Pl, L.cout, (int)std::min<long>((Pl + 127) / 128, kPartBlocks), st));
     return LC_OK;
   };
   int rc;
