@@ -91,11 +91,11 @@ double now_ms() {
 }
 
 // Where the terms of slot `slot` go: to the host when it adds them itself, else to the device scratch.
-static double* parts_of(lc_ctx* c, int slot, int nparts) {
+double* parts_of(lc_ctx* c, int slot, int nparts) {
   return nparts <= kHostParts ? c->hsum_d + kSumSlots + (size_t)slot * kHostParts : c->partials;
 }
 
-static int finish_queue(lc_ctx* c, int slot, int nparts) {
+int finish_queue(lc_ctx* c, int slot, int nparts) {
   c->pending[slot] = nparts <= kHostParts ? nparts : 0;
   if (nparts > kHostParts) KLAUNCH(c, LC_K_REDUCE, launch_sum(c->partials, nparts, c->hsum_d + slot, c->stream));
   return LC_OK;
@@ -308,7 +308,7 @@ void init_dims(lc_ctx* c, int nx, int ny, int nz) {
   c->nvel = vel_layout(nx, ny, nz).total();
   c->ncell = (size_t)nx * ny * nz;
   c->max_parts = (int)((c->ncell + kReduceBlock - 1) / kReduceBlock) + kGsBlocks * kGsChunk;
-  c->max_parts = std::max(c->max_parts, divergence_parts(nx, ny, nz));
+  c->max_parts = std::max({c->max_parts, divergence_parts(nx, ny, nz), correct_div_parts(nx, ny, nz)});
 }
 
 // The context's device buffers, in a fixed order.  With a caller workspace (or a dry run)
@@ -317,7 +317,7 @@ void init_dims(lc_ctx* c, int nx, int ny, int nz) {
 // Krylov vectors get the remainder.
 bool carve_all(lc_ctx* c) {
   bool ok = dalloc(c, &c->U, c->nvel) == hipSuccess && dalloc(c, &c->w, c->nvel) == hipSuccess &&
-            dalloc(c, &c->r, c->ncell) == hipSuccess && dalloc(c, &c->phi, c->ncell) == hipSuccess &&
+            dalloc(c, &c->r, c->ncell) == hipSuccess && dalloc(c, &c->phi, c->ncell + 1) == hipSuccess &&
             dalloc(c, &c->t1, c->ncell) == hipSuccess && dalloc(c, &c->t2, c->ncell) == hipSuccess &&
             dalloc(c, &c->r32, c->ncell) == hipSuccess && dalloc(c, &c->t1_32, c->ncell) == hipSuccess &&
             dalloc(c, &c->t2_32, c->ncell) == hipSuccess && dalloc(c, &c->partials, c->max_parts) == hipSuccess &&
@@ -640,7 +640,13 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   auto pass = [&](bool accumulate) -> int {
     int e = poisson(c, c->r, c->phi, pass_precision);
     if (e) return e;
-    KLAUNCH(c, LC_K_CORRECT, launch_correct(c->g, w, c->phi, v, p, accumulate, c->stream));
+    if (!accumulate) {
+      const int np = correct_div_parts(c->nx, c->ny, c->nz);
+      KLAUNCH(c, LC_K_CORRECT,
+              launch_correct_div(c->g, w, c->phi, v, p, keep_r ? c->r : nullptr, parts_of(c, 1, np), c->stream));
+      return finish_queue(c, 1, np);
+    }
+    KLAUNCH(c, LC_K_CORRECT, launch_correct(c->g, w, c->phi, v, p, true, c->stream));
     return div_queue(c, v, keep_r ? c->r : nullptr, 1);
   };
   // The first pass does not depend on |D w|, so without a guess it is queued behind it and both norms

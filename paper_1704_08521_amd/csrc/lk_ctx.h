@@ -83,7 +83,7 @@ struct lc_ctx {
   double* U = nullptr;   // base flow (velocity)
   double* w = nullptr;   // momentum work vector (velocity)
   double* r = nullptr;   // divergence (cell)
-  double* phi = nullptr; // correction (cell)
+  double* phi = nullptr; // correction (cell, and one value more: see launch_correct_div)
   double* t1 = nullptr;  // transform temporaries (cell)
   double* t2 = nullptr;
   float *r32 = nullptr, *t1_32 = nullptr, *t2_32 = nullptr;
@@ -171,6 +171,9 @@ int reduce_max_to_host(lc_ctx* c, int nparts, double* out);
 int div_queue(lc_ctx* c, const double* v, double* r, int slot);
 int dot_queue(lc_ctx* c, const double* a, const double* b, int slot);
 int sums_wait(lc_ctx* c);
+// where the terms of a slot go (nparts of them), and the end of the queueing
+double* parts_of(lc_ctx* c, int slot, int nparts);
+int finish_queue(lc_ctx* c, int slot, int nparts);
 double sum_of(const lc_ctx* c, int slot);
 // |D v|_V (r receives D v when not null)
 int vnorm_div(lc_ctx* c, const double* v, double* r, double* out);

@@ -59,6 +59,12 @@ hipError_t launch_divergence(const GridDev& g, const double* v, double* r, doubl
 hipError_t launch_correct(const GridDev& g, const double* w, const double* phi, double* v,
                           double* p, bool accumulate, hipStream_t st);
 
+// launch_correct (not accumulating; w and v distinct) with r = D v (may be null) and the
+// correct_div_parts() partial sums of V (D v)^2 into `partials`.  phi must be readable one value past its end.
+int correct_div_parts(int nx, int ny, int nz);
+hipError_t launch_correct_div(const GridDev& g, const double* w, const double* phi, double* v, double* p, double* r,
+                              double* partials, hipStream_t st);
+
 // Fixed-order sum of n partials into out[0] (one block).
 hipError_t launch_sum(const double* partials, int n, double* out, hipStream_t st);
 

@@ -50,6 +50,20 @@ typedef double D2 __attribute__((ext_vector_type(2)));
 typedef unsigned U2 __attribute__((ext_vector_type(2)));
 typedef unsigned U4 __attribute__((ext_vector_type(4)));
 
+// Each lane's pair to byte s2 past byte `so` of q and, where rows end with half a pair (`one`), its first
+// value to byte s1; offsets past `bytes` (0: no store) store nothing.  A 16-byte store with a scalar register
+// for its offset may still be reading its data when the next instruction overwrites it, and the compiler
+// puts a wait state only behind those with a constant offset: seen on gfx950, where the second value
+// of lanes 12 to 15 of every 16 now and then was the next instruction's result.  The s_nop has the data as its
+// operand, so nothing overwrites it before.
+__device__ __forceinline__ void store_pair(D2 x, double* q, unsigned bytes, unsigned s2, unsigned s1, bool one,
+                                           unsigned so) {
+  const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(q, (short)0, (int)bytes, 0x00020000);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, x), b, (int)s2, (int)so, 0);
+  asm volatile("s_nop 1" ::"v"(x) : "memory");
+  if (one) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, x.x), b, (int)s1, (int)so, 0);
+}
+
 // x of the next lower / higher position of a pair (undefined in the wave's first / last lane,
 // whose results are halo).
 template <int CTRL>
@@ -185,10 +199,9 @@ __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const do
   const unsigned sto[3] = {store_offset(0, true), store_offset(1, true), store_offset(2, true)};
   const unsigned sto1[3] = {store_offset(0, false), store_offset(1, false), store_offset(2, false)};
   auto put = [&](D2 x, int c, int k, bool in) {
-    const unsigned m = -(unsigned)in, so = (unsigned)k * plane[c] & m;
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, x), buffer(out, c, m), (int)sto[c], (int)so, 0);
-    if ((c == 0) != ODD)
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, x.x), buffer(out, c, m), (int)sto1[c], (int)so, 0);
+    const unsigned m = -(unsigned)in;
+    store_pair(x, out + (c == 0 ? 0 : c == 1 ? nu : nu + nv), nbytes[c] & m, sto[c], sto1[c], (c == 0) != ODD,
+               (unsigned)k * plane[c] & m);
   };
 
   // carried from the plane below: own values (and v of the row above), z fluxes, and what the
@@ -365,8 +378,9 @@ __global__ void __launch_bounds__(kDivTX* kDivTY) k_divergence(GridDev g, Vel V,
     double wlo = V.W(k0, j, i);
     for (int k = k0; k < k1; ++k) {
       const double whi = V.W(k + 1, j, i);
-      const double dv = (V.U(k, j, i + 1) - V.U(k, j, i)) * rdx + (V.V(k, j + 1, i) - V.V(k, j, i)) * rdy +
-                        (whi - wlo) * g.z.rd[k];
+      // (the order of the sum is that of k_correct_div)
+      const double dv = fma(g.z.rd[k], whi - wlo, fma(rdy, V.V(k, j + 1, i) - V.V(k, j, i),
+                                                      (V.U(k, j, i + 1) - V.U(k, j, i)) * rdx));
       if (r) r[((size_t)k * ny + j) * nx + i] = dv;
       contrib += dxy * g.z.d[k] * dv * dv;
       wlo = whi;
@@ -381,6 +395,7 @@ __global__ void __launch_bounds__(kDivTX* kDivTY) k_divergence(GridDev g, Vel V,
 // ---------------------------------------------------------------- correction
 // One thread per (i, j) face column marching over KZ planes (phi of the plane
 // below carried in a register); tiles grouped per XCD.
+constexpr int kCdMaxChunk = 8;
 constexpr int kCorTX = 64, kCorTY = 4, kCorKZ = 2;
 
 template <int KZ>
@@ -427,6 +442,124 @@ __global__ void __launch_bounds__(kCorTX* kCorTY) k_correct(GridDev g, const dou
     }
     pb = pc;
   }
+}
+
+// --------------------------------------------- correction with its certificate
+// The first pass of a projection: v = w - G phi, p = phi, and D v with the partial sums of V (D v)^2, in one
+// kernel.  The rows, lanes and pairs of the momentum stencil: a lane corrects its pair of u, v and w faces,
+// and the faces its cells share with others - u of the next lane, v of the next row, w of the next
+// plane - are corrected again with the same operations on the same values (the input is not the
+// output), so D v is that of the stored field to the bit and no value passes between waves.  A
+// block marches over a chunk of planes with the next plane's loads in flight.
+// HBM bound: 2 F_u + 2 F_p, 514 MB at 200^3, where a separate certificate read v again (193 MB).
+// 200^3: 130 us (4.0 TB/s; the misses of the L2 are 604 MB) against 109 + 55 for the two kernels;
+// 100^3 17 / 14 + 9; 256^3 250 / 226 + 111; 97 x 121 x 65 15 / 13 + 8.
+template <bool ODD>
+__global__ void __launch_bounds__(64 * kMomWY, 4) k_correct_div(GridDev g, const double* __restrict__ w,
+                                                                const double* __restrict__ phi,
+                                                                double* __restrict__ v, double* __restrict__ p,
+                                                                double* __restrict__ r, double* __restrict__ partials,
+                                                                int kchunk, int nbx, int nby) {
+  constexpr int L = kMomL, TX = kMomTX, TY = kMomTY;
+  constexpr unsigned kGhost = 1u << 31;
+  const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int bx = tile % nbx, by = (tile / nbx) % nby, bz = tile / (nbx * nby);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane % L, j = by * TY + wave * (64 / L) + lane / L;
+  const int i = bx * TX + 2 * li - 2;  // the lane's faces and cells are i and i + 1
+  const int kb = bz * kchunk, ke = min(kb + kchunk, nz);
+  const size_t nu = (size_t)(nx + 1) * ny * nz, nv = (size_t)nx * (ny + 1) * nz, nc = (size_t)nx * ny * nz;
+  const unsigned ubytes = (unsigned)(8 * nu), vbytes = (unsigned)(8 * nv), wbytes = (unsigned)(8 * (nc + (size_t)nx * ny));
+  const unsigned cbytes = (unsigned)(8 * nc);
+  auto buffer = [&](const double* q, unsigned bytes, unsigned in) {  // raw buffer (stride 0), 32-bit data format
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(q), (short)0, (int)(bytes & in), 0x00020000);
+  };
+  const bool u0 = i > 0 && i < nx, u1 = i + 1 > 0 && i + 1 < nx;
+  const bool c0 = i >= 0 && i < nx, c1 = i + 1 >= 0 && i + 1 < nx;
+  const bool row = j < ny, own = li >= 1 && li <= TX / 2;
+  const unsigned urow = 8u * (nx + 1), crow = 8u * nx;
+  const unsigned uplane = urow * ny, vplane = crow * (ny + 1), cplane = crow * ny;
+  auto at = [&](bool in, int jj, unsigned rb) { return in ? jj * rb + 8u * i : kGhost; };
+  const bool c = c0 || c1;
+  const unsigned lu = at((u0 || u1) && row, j, urow), lv0 = at(c && j > 0 && row, j, crow), lv1 = at(c && j + 1 < ny, j + 1, crow);
+  const unsigned lc = at(c && row, j, crow), lcm = at(c && j > 0 && row, j - 1, crow), lcp = at(c && j + 1 < ny, j + 1, crow);
+  // whole pairs, and the single entry that ends a row of odd length
+  auto whole = [&](int n) { return own && i + 1 < n; };
+  auto half = [&](int n) { return own && i + 1 == n; };
+  const unsigned su = at(whole(nx + 1) && row, j, urow), su1 = at(half(nx + 1) && row, j, urow);
+  const unsigned sv = at(whole(nx) && j <= ny, j, crow), sv1 = at(half(nx) && j <= ny, j, crow);
+  const unsigned sc = at(whole(nx) && row, j, crow), sc1 = at(half(nx) && row, j, crow);
+  struct Plane {
+    D2 p0, pm, pp, u, v0, v1, w;
+  };
+  auto get = [&](const __amdgpu_buffer_rsrc_t& b, unsigned ofs, unsigned so) {
+    return __builtin_bit_cast(D2, __builtin_amdgcn_raw_buffer_load_b128(b, (int)ofs, (int)so, 0));
+  };
+  auto fetch = [&](Plane& P, int k) {
+    // cells and the faces u, v of plane k < ke; w and the phi it needs also on the level ke
+    const unsigned in = -(unsigned)(k < ke), inp = -(unsigned)((k <= ke) & (k < nz)),
+                   inw = -(unsigned)((k <= ke) & (k > 0) & (k < nz));
+    // (phi is followed by at least one more value: a half pair reads past its last one)
+    const __amdgpu_buffer_rsrc_t bp = buffer(phi, cbytes + 8, inp), bq = buffer(phi, cbytes + 8, in),
+                                 bv = buffer(w + nu, vbytes, in);
+    P.p0 = get(bp, lc, (unsigned)k * cplane & inp);
+    P.pm = get(bq, lcm, (unsigned)k * cplane & in);
+    P.pp = get(bq, lcp, (unsigned)k * cplane & in);
+    P.u = get(buffer(w, ubytes, in), lu, (unsigned)k * uplane & in);
+    P.v0 = get(bv, lv0, (unsigned)k * vplane & in);
+    P.v1 = get(bv, lv1, (unsigned)k * vplane & in);
+    P.w = get(buffer(w + nu + nv, wbytes, inw), lc, (unsigned)k * cplane & inw);
+  };
+  auto put = [&](D2 x, double* q, unsigned bytes, unsigned plane, unsigned s2, unsigned s1, bool one, int k, bool in) {
+    const unsigned m = -(unsigned)in;
+    store_pair(x, q, bytes & m, s2, s1, one, (unsigned)k * plane & m);
+  };
+  Plane N;
+  fetch(N, kb);
+  // phi below the first plane; metrics
+  const unsigned inb = -(unsigned)(kb > 0);
+  D2 pb = get(buffer(phi, cbytes + 8, inb), lc, (unsigned)(kb - 1) * cplane & inb);
+  const int ic = max(0, min(i, nx - 1)), ic1 = max(0, min(i + 1, nx - 1)), xf = max(0, min(i, nx)), xf1 = max(0, min(i + 1, nx));
+  const D2 rdx = {g.x.rd[ic], g.x.rd[ic1]}, rddx = {g.x.rdd[xf], g.x.rdd[xf1]};
+  const int jc = min(j, ny - 1), jf = min(j, ny), jf1 = min(j + 1, ny);
+  const double rdy = g.y.rd[jc], rddy0 = g.y.rdd[jf], rddy1 = g.y.rdd[jf1];
+  const bool cell = own && row;
+  const D2 dxy = {cell && c0 ? g.x.d[ic] * g.y.d[jc] : 0.0, cell && c1 ? g.x.d[ic1] * g.y.d[jc] : 0.0};
+  const int zl = min(kb + lane, nz);
+  const double zrd = g.z.rd[min(zl, nz - 1)], zd = g.z.d[min(zl, nz - 1)], zrdd = g.z.rdd[zl];
+  double sum = 0.0;
+  D2 s = 0.0, wp = 0.0;
+  for (int k = kb; k <= ke; ++k) {
+    const Plane P = N;
+    fetch(N, k + 1);
+    const int l = k - kb;
+    // w on the level z_k, and with it the divergence of the cells below
+    const bool wi = k > 0 && k < nz;
+    const D2 dw = P.p0 - pb;
+    const double rddz = lane_value(zrdd, l);
+    const D2 wk = {wi && c0 ? fma(-dw.x, rddz, P.w.x) : 0.0, wi && c1 ? fma(-dw.y, rddz, P.w.y) : 0.0};
+    put(wk, v + nu + nv, wbytes, cplane, sc, sc1, ODD, k, (k < ke) | (k == nz));
+    const double rdz = lane_value(zrd, max(l - 1, 0)), dz = lane_value(zd, max(l - 1, 0));
+    const D2 dv = fma2(rdz, wk - wp, s);
+    const double t = dz * fma(dxy.x * dv.x, dv.x, dxy.y * dv.y * dv.y);
+    sum += k > kb ? t : 0.0;
+    put(dv, r, r ? cbytes : 0, cplane, sc, sc1, ODD, k - 1, k > kb);
+    // u, v and p of plane k
+    const D2 du = P.p0 - below(P.p0), d0 = P.p0 - P.pm, d1 = P.pp - P.p0;
+    const D2 u = {u0 ? fma(-du.x, rddx.x, P.u.x) : 0.0, u1 ? fma(-du.y, rddx.y, P.u.y) : 0.0};
+    const bool vi = j > 0 && j < ny, vi1 = j + 1 < ny;
+    const D2 v0 = {vi && c0 ? fma(-d0.x, rddy0, P.v0.x) : 0.0, vi && c1 ? fma(-d0.y, rddy0, P.v0.y) : 0.0};
+    const D2 v1 = {vi1 && c0 ? fma(-d1.x, rddy1, P.v1.x) : 0.0, vi1 && c1 ? fma(-d1.y, rddy1, P.v1.y) : 0.0};
+    put(u, v, ubytes, uplane, su, su1, !ODD, k, k < ke);
+    put(v0, v + nu, vbytes, vplane, sv, sv1, ODD, k, k < ke);
+    put(P.p0, p, p ? cbytes : 0, cplane, sc, sc1, ODD, k, k < ke);
+    s = fma2(rdy, v1 - v0, (above(u) - u) * rdx);
+    wp = wk;
+    pb = P.p0;
+  }
+  const double total = block_sum(sum);
+  if (threadIdx.x == 0) partials[blockIdx.x] = total;
 }
 
 }  // namespace
@@ -495,6 +628,33 @@ hipError_t launch_correct(const GridDev& g, const double* w, const double* phi, 
   const unsigned nb = (unsigned)(nbx * nby * (int)blocks_for(nz + 1, kCorKZ));
   hipLaunchKernelGGL(k_correct<kCorKZ>, dim3(nb), dim3(kCorTX * kCorTY), 0, st, g, w, phi, v, p, accumulate ? 1 : 0, nbx,
                      nby);
+  return hipGetLastError();
+}
+
+// Planes per chunk of k_correct_div: a chunk reads one level of phi and w more than its planes, and
+// longer chunks read what neighbouring blocks share at more different times (200^3: 5 planes
+// 131 us, 8 130 us, 16 and 25 142 us; 256^3 253 / 251 / 259 / 285).  Grids that would not fill the chip
+// with chunks of eight (four blocks per CU, 2 kMomSlots) take shorter ones.
+static int correct_chunk(int nx, int ny, int nz) {
+  const long tiles = (long)blocks_for(nx + 1, kMomTX) * blocks_for(ny + 1, kMomTY);
+  const long most = std::max<long>(1, 2 * kMomSlots / tiles);
+  return (int)std::min<long>(kCdMaxChunk, std::max<long>(2, blocks_for(nz, (unsigned)most)));
+}
+
+int correct_div_parts(int nx, int ny, int nz) {
+  return (int)(blocks_for(nx + 1, kMomTX) * blocks_for(ny + 1, kMomTY) * blocks_for(nz, correct_chunk(nx, ny, nz)));
+}
+
+hipError_t launch_correct_div(const GridDev& g, const double* w, const double* phi, double* v, double* p, double* r,
+                              double* partials, hipStream_t st) {
+  const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
+  const int nbx = (int)blocks_for(nx + 1, kMomTX), nby = (int)blocks_for(ny + 1, kMomTY);
+  const dim3 grid((unsigned)correct_div_parts(nx, ny, nz)), block(64 * kMomWY);
+  const int kchunk = correct_chunk(nx, ny, nz);
+  if (nx & 1)
+    hipLaunchKernelGGL(k_correct_div<true>, grid, block, 0, st, g, w, phi, v, p, r, partials, kchunk, nbx, nby);
+  else
+    hipLaunchKernelGGL(k_correct_div<false>, grid, block, 0, st, g, w, phi, v, p, r, partials, kchunk, nbx, nby);
   return hipGetLastError();
 }
 
