@@ -13,7 +13,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblidkrylov.so")
-SOURCES = ["lk_stencil.hip", "lk_transform.hip", "lk_mx.hip", "lk_kernels.hip", "lk_nn.hip", "lk_api.cpp", "lk_krylov.cpp",
+SOURCES = ["lk_stencil.hip", "lk_transform.hip", "lk_m4.hip", "lk_mx.hip", "lk_kernels.hip", "lk_nn.hip", "lk_api.cpp", "lk_krylov.cpp",
            "lk_linalg.cpp", "lk_nn_host.cpp", "lk_planes.hip", "lk_planes_host.cpp",
            "lk_tpt.hip", "lk_modes.cpp", "lk_stokes.cpp", "lk_noalloc.hip"]
 ARCH = os.environ.get("LK_OFFLOAD_ARCH", "gfx950")

@@ -200,11 +200,14 @@ int upload_grid(lc_ctx* c) {
   return LC_OK;
 }
 
+// the pressure solve ends in tridiagonal solves along x (else in a division by sums of eigenvalues)
+static bool uses_tridiag(const lc_ctx* c) { return c->poisson_method == LC_POISSON_TPT && c->nx <= tridiag_x_max(); }
+
 // (D G) phi = r by the tensor-product solve.  TPT: transforms with S^T M along y and z, one tridiagonal
 // solve per x-line, transforms back with S.  TPF: transforms along x, y and z and a division by
 // the sums of the axis eigenvalues (constant mode set to zero).
-template <typename T>
-int tp_solve(lc_ctx* c, const T* r, T* phi, T* t1, T* t2) {
+template <typename T, typename F>
+int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2) {
   const int nx = c->nx, ny = c->ny, nz = c->nz;
   const AxisModes &X = c->modes[0], &Y = c->modes[1], &Z = c->modes[2];
   auto lams = [](const AxisModes& M) { return M.sym ? M.lam_s : M.lam; };
@@ -212,7 +215,7 @@ int tp_solve(lc_ctx* c, const T* r, T* phi, T* t1, T* t2) {
   const int pl = nx * ny;
   const Columns cy{nx * nz, nx, pl, nx, c->ncell}, cz{pl, pl, 0, pl, c->ncell};
   const LineScale none;
-  if (c->poisson_method == LC_POISSON_TPT && nx <= tridiag_x_max()) {
+  if (uses_tridiag(c)) {
     KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, r, t1, none, s));
     KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t1, t2, none, s));
     KLAUNCH(c, LC_K_TRIDIAG,
@@ -221,18 +224,23 @@ int tp_solve(lc_ctx* c, const T* r, T* phi, T* t1, T* t2) {
     KLAUNCH(c, LC_K_TP_Y, left_backward<T>(Y, ny, cy, t2, phi, none, s));
     return LC_OK;
   }
-  const LineScale sc{lams(Z), lams(Y), lams(X), nx, c->zero_mode[2], c->zero_mode[1], c->zero_mode[0]};
-  KLAUNCH(c, LC_K_TP_X, right_forward<T>(X, nx, ny * nz, r, t1, s));
-  KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, t1, t2, none, s));
-  KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t2, t1, sc, s));
-  KLAUNCH(c, LC_K_TP_Z, left_backward<T>(Z, nz, cz, t1, t2, sc, s));
-  KLAUNCH(c, LC_K_TP_Y, left_backward<T>(Y, ny, cy, t2, t1, none, s));
-  KLAUNCH(c, LC_K_TP_X, right_backward<T>(X, nx, ny * nz, t1, phi, s));
-  return LC_OK;
+  if constexpr (sizeof(F) == sizeof(T)) {
+    const LineScale sc{lams(Z), lams(Y), lams(X), nx, c->zero_mode[2], c->zero_mode[1], c->zero_mode[0]};
+    KLAUNCH(c, LC_K_TP_X, right_forward<T>(X, nx, ny * nz, r, t1, s));
+    KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, t1, t2, none, s));
+    KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t2, t1, sc, s));
+    KLAUNCH(c, LC_K_TP_Z, left_backward<T>(Z, nz, cz, t1, t2, sc, s));
+    KLAUNCH(c, LC_K_TP_Y, left_backward<T>(Y, ny, cy, t2, t1, none, s));
+    KLAUNCH(c, LC_K_TP_X, right_backward<T>(X, nx, ny * nz, t1, phi, s));
+    return LC_OK;
+  }
+  return fail(c, LC_ESTATE, "FP64 field in an FP32 solve along x (internal)");
 }
 
 int poisson(lc_ctx* c, const double* r, double* phi, int precision) {
   if (precision == LC_FP64) return tp_solve<double>(c, r, phi, c->t1, c->t2);
+  // FP32: where the first and the last transform read and write FP64 fields there are no casts
+  if (uses_tridiag(c) && c->modes[1].mf) return tp_solve<float>(c, r, phi, c->t1_32, c->t2_32);
   KLAUNCH(c, LC_K_CAST, launch_d2f(c->ncell, r, c->r32, c->stream));
   int rc = tp_solve<float>(c, c->r32, c->r32, c->t1_32, c->t2_32);
   if (rc) return rc;

@@ -48,10 +48,11 @@ struct AxisModes {
   float* h32[8] = {};
   // matrix-core fragment packs of Ae, Ao, Se, So (he <= kMfMaxHalf)
   bool mf = false;
-  // (x64: the FP64 left transforms' pieces, forward and backward; p64: the FP64 right transforms')
+  // (x64, x32: the left transforms' pieces, forward and backward; p64, p32: the right transforms')
   double* x64[2] = {};
   double* p64[4] = {};
   float* p32[4] = {};
+  float* x32[2] = {};
 };
 
 }  // namespace lk

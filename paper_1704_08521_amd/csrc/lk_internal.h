@@ -120,14 +120,13 @@ hipError_t launch_tpf_right(int n, int Mlines, const T* A, const T* Be, const T*
 template <typename T>
 hipError_t launch_tpu_right(int n, int Mlines, const T* A, const T* SeT, const T* SoT, T* C, hipStream_t st);
 
-// The same four transforms on the matrix cores, for he = ceil(n/2) <= 128 (kMfMaxHalf).
-// The half matrices are passed as fragment packs: Pe, Po packs of Ae, Ao (forward), Pse,
-// Pso packs of Se, So (backward), for the left and the right kernels alike
-// (fragment (kq, t, l) = Mat[16 t + l % 16][4 kq + l / 16], RT = ceil(he / 16),
-// kq < mf_steps(he), zero outside the matrix: the contraction steps of 4 are padded to a
-// multiple of the kernels' prefetch depth kMfPD; layout mf_pack_index).  Here the eigenvalue scaling (lm, ly,
-// lx, zero mode) belongs to the backward left transform: its input modes are scaled on
-// load.
+// The transforms on the matrix cores, for he = ceil(n/2) <= 128 (kMfMaxHalf).  Along x (right): the half
+// matrices are passed as fragment packs, Pe, Po packs of Ae, Ao (forward), Pse, Pso packs of Se, So
+// (backward); fragment (kq, t, l) = Mat[16 t + l % 16][4 kq + l / 16], RT = ceil(he / 16), kq <
+// mf_steps(he), zero outside the matrix: the contraction steps of 4 are padded to a multiple of the
+// kernels' prefetch depth kMfPD; layout mf_pack_index.  Along the strided axes (left) they are passed as one
+// array of pieces per direction, and the eigenvalue scaling (lm, ly, lx, zero mode) belongs to the backward
+// transform: its input modes are scaled on load.
 constexpr int kMfMaxHalf = 128;
 constexpr int kMfPD = 1;
 __host__ __device__ constexpr int mf_steps(int he, int pd = kMfPD) { return ((he + 3) / 4 + pd - 1) / pd * pd; }
@@ -140,13 +139,6 @@ __host__ __device__ constexpr long mf_pack_index(int kq, int t, int lane, int RT
 __host__ __device__ constexpr long mf_pack_size(int he, int fg) {
   return (long)mf_steps(he) * mf_tile_groups((he + 15) / 16, fg) * 64 * fg;
 }
-template <typename T>
-hipError_t launch_mff_left(int n, int N, const T* Pe, const T* Po, const T* B, T* C, int nseg, long seg_stride,
-                           long kstride, hipStream_t st);
-template <typename T>
-hipError_t launch_mfu_left(int n, int N, const T* Pse, const T* Pso, const T* B, T* C, int nseg, long seg_stride,
-                           long kstride, const double* lm, const double* ly, const double* lx, int nxs, int zm, int zj,
-                           int zi, hipStream_t st);
 // FP64 left transforms (lk_mx.hip): both half matrices as 4 x 4 pieces, [step of 4 contracted
 // indices][group of 4 rows][16 values][even, odd]: value (o, k) of one parity at mx_pack_index, zero outside
 // the matrix.  `elems` values in the field (below 2^31 bytes); scaling as above.
@@ -157,6 +149,20 @@ __host__ __device__ constexpr long mx_pack_size(int he) { return (long)((he + 3)
 hipError_t launch_mxf_left(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
                            long seg_stride, long kstride, hipStream_t st);
 hipError_t launch_mxu_left(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
+                           long seg_stride, long kstride, const double* lm, const double* ly, const double* lx, int nxs,
+                           int zm, int zj, int zi, hipStream_t st);
+// FP32 left transforms (lk_m4.hip), the outer field FP32 or FP64: both half matrices as [group of 4 rows][32
+// contracted indices][even, odd][8 indices][4 rows][four steps of 8], value (o, k) of one parity at
+// m4_pack_index, zero outside the matrix.
+__host__ __device__ constexpr long m4_pack_index(int o, int k, int he, int odd) {
+  return (((long)(o / 4) * ((he + 31) / 32) + k / 32) * 64 + odd * 32 + k % 8 * 4 + o % 4) * 4 + k / 8 % 4;
+}
+__host__ __device__ constexpr long m4_pack_size(int he) { return (long)((he + 3) / 4) * ((he + 31) / 32) * 256; }
+template <typename IN>
+hipError_t launch_m4f_left(int n, int N, const float* P, const IN* B, float* C, size_t elems, int nseg,
+                           long seg_stride, long kstride, hipStream_t st);
+template <typename OUT>
+hipError_t launch_m4u_left(int n, int N, const float* P, const float* B, OUT* C, size_t elems, int nseg,
                            long seg_stride, long kstride, const double* lm, const double* ly, const double* lx, int nxs,
                            int zm, int zj, int zi, hipStream_t st);
 template <typename T>

@@ -44,38 +44,45 @@ const T* mode_pack(const AxisModes& M, int which) {
   else return M.p32[which];
 }
 
-template <typename T>
-hipError_t left_forward(const AxisModes& M, int n, const Columns& q, const T* in, T* out, const LineScale& s,
+// The field on the outer side (IN, OUT) may be FP64 with FP32 transforms (T) if the axis is on the matrix cores.
+template <typename T, typename IN>
+hipError_t left_forward(const AxisModes& M, int n, const Columns& q, const IN* in, T* out, const LineScale& s,
                         hipStream_t st) {
   if (M.mf) {
     if constexpr (sizeof(T) == sizeof(double))
       return launch_mxf_left(n, q.count, M.x64[0], in, out, q.elems, q.nseg, q.seg_stride, q.kstride, st);
     else
-      return launch_mff_left(n, q.count, M.p32[0], M.p32[1], in, out, q.nseg, q.seg_stride, q.kstride, st);
+      return launch_m4f_left<IN>(n, q.count, M.x32[0], in, out, q.elems, q.nseg, q.seg_stride, q.kstride, st);
   }
-  if (M.sym)
-    return launch_tpf_left<T>(n, q.count, mode_half<T>(M, 0), mode_half<T>(M, 1), in, out, q.nseg, q.seg_stride,
-                              q.kstride, s.lm, s.ly, s.lx, s.nxs, s.zm, s.zj, s.zi, st);
-  return launch_tp_left<T>(n, q.count, n, mode_full<T>(M, 0), in, out, q.nseg, q.seg_stride, q.kstride, s.lm, s.ly,
-                           s.lx, s.nxs, s.zm, s.zj, s.zi, st);
+  if constexpr (sizeof(T) != sizeof(IN)) return hipErrorInvalidValue;
+  else {
+    if (M.sym)
+      return launch_tpf_left<T>(n, q.count, mode_half<T>(M, 0), mode_half<T>(M, 1), in, out, q.nseg, q.seg_stride,
+                                q.kstride, s.lm, s.ly, s.lx, s.nxs, s.zm, s.zj, s.zi, st);
+    return launch_tp_left<T>(n, q.count, n, mode_full<T>(M, 0), in, out, q.nseg, q.seg_stride, q.kstride, s.lm, s.ly,
+                             s.lx, s.nxs, s.zm, s.zj, s.zi, st);
+  }
 }
 
-template <typename T>
-hipError_t left_backward(const AxisModes& M, int n, const Columns& q, const T* in, T* out, const LineScale& s,
+template <typename T, typename OUT>
+hipError_t left_backward(const AxisModes& M, int n, const Columns& q, const T* in, OUT* out, const LineScale& s,
                          hipStream_t st) {
   if (M.mf) {
     if constexpr (sizeof(T) == sizeof(double))
       return launch_mxu_left(n, q.count, M.x64[1], in, out, q.elems, q.nseg, q.seg_stride, q.kstride, s.lm,
                              s.ly, s.lx, s.nxs, s.zm, s.zj, s.zi, st);
     else
-      return launch_mfu_left(n, q.count, M.p32[2], M.p32[3], in, out, q.nseg, q.seg_stride, q.kstride, s.lm, s.ly,
-                             s.lx, s.nxs, s.zm, s.zj, s.zi, st);
+      return launch_m4u_left<OUT>(n, q.count, M.x32[1], in, out, q.elems, q.nseg, q.seg_stride, q.kstride, s.lm, s.ly,
+                                  s.lx, s.nxs, s.zm, s.zj, s.zi, st);
   }
-  if (M.sym)
-    return launch_tpu_left<T>(n, q.count, mode_half<T>(M, 2), mode_half<T>(M, 3), in, out, q.nseg, q.seg_stride,
-                              q.kstride, st);
-  return launch_tp_left<T>(n, q.count, n, mode_full<T>(M, 1), in, out, q.nseg, q.seg_stride, q.kstride, nullptr, nullptr,
-                           nullptr, 1, 0, 0, 0, st);
+  if constexpr (sizeof(T) != sizeof(OUT)) return hipErrorInvalidValue;
+  else {
+    if (M.sym)
+      return launch_tpu_left<T>(n, q.count, mode_half<T>(M, 2), mode_half<T>(M, 3), in, out, q.nseg, q.seg_stride,
+                                q.kstride, st);
+    return launch_tp_left<T>(n, q.count, n, mode_full<T>(M, 1), in, out, q.nseg, q.seg_stride, q.kstride, nullptr,
+                             nullptr, nullptr, 1, 0, 0, 0, st);
+  }
 }
 
 template <typename T>

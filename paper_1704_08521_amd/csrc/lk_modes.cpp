@@ -27,7 +27,7 @@ size_t mode_bytes(int n) {
   return 2 * n * sizeof(double) + 4 * nn * sizeof(double) + 4 * nn * sizeof(float) +
          3 * nn * (sizeof(double) + sizeof(float)) +
          4 * (mf_pack_size(he, 2) * sizeof(double) + mf_pack_size(he, 4) * sizeof(float)) +
-         2 * mx_pack_size(he) * sizeof(double) +
+         2 * (mx_pack_size(he) * sizeof(double) + m4_pack_size(he) * sizeof(float)) +
          64 * 16;  // alignment padding (at most 15 bytes for each of an operator's <= 36 arrays)
 }
 
@@ -136,11 +136,15 @@ void place_modes(const ModeHost& H, AxisModes& M, Stager& st) {
     M.p32[q] = st.put_f(P4);
   }
   for (int b = 0; b < 2; ++b) {
-    std::vector<double> X(mx_pack_size(he), 0.0);
+    std::vector<double> X(mx_pack_size(he), 0.0), X4(m4_pack_size(he), 0.0);
     for (int q = 2 * b; q < 2 * b + 2; ++q)
       for (int o = 0; o < rows[q]; ++o)
-        for (int k = 0; k < cols[q]; ++k) X[mx_pack_index(o, k, he, q % 2)] = h[q][(size_t)o * cols[q] + k];
+        for (int k = 0; k < cols[q]; ++k) {
+          X[mx_pack_index(o, k, he, q % 2)] = h[q][(size_t)o * cols[q] + k];
+          X4[m4_pack_index(o, k, he, q % 2)] = h[q][(size_t)o * cols[q] + k];
+        }
     M.x64[b] = st.put_d(X);
+    M.x32[b] = st.put_f(X4);
   }
 }
 
