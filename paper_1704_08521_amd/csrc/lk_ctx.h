@@ -48,6 +48,7 @@ struct AxisModes {
   float* h32[8] = {};
   // matrix-core fragment packs of Ae, Ao, Se, So (he <= kMfMaxHalf)
   bool mf = false;
+  bool full64 = false;  // not symmetric, FP64 left transforms with the full matrix on the matrix cores (x64)
   // (x64, x32: the left transforms' pieces, forward and backward; p64, p32: the right transforms')
   double* x64[2] = {};
   double* p64[4] = {};

@@ -151,6 +151,12 @@ hipError_t launch_mxf_left(int n, int N, const double* P, const double* B, doubl
 hipError_t launch_mxu_left(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
                            long seg_stride, long kstride, const double* lm, const double* ly, const double* lx, int nxs,
                            int zm, int zj, int zi, hipStream_t st);
+// The same with the full matrix of any axis of n <= 2 kMfMaxHalf points, forward or backward: rows below he as
+// "even", rows he + o as "odd", n contracted indices.
+__host__ __device__ constexpr long mx_full_size(int n) { return (long)((n + 3) / 4) * (((n + 1) / 2 + 3) / 4) * 32; }
+hipError_t launch_mx_full_left(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
+                               long seg_stride, long kstride, const double* lm, const double* ly, const double* lx,
+                               int nxs, int zm, int zj, int zi, hipStream_t st);
 // FP32 left transforms (lk_m4.hip), the outer field FP32 or FP64: both half matrices as [group of 4 rows][32
 // contracted indices][even, odd][8 indices][4 rows][four steps of 8], value (o, k) of one parity at
 // m4_pack_index, zero outside the matrix.

@@ -1,6 +1,7 @@
 // Transforms of every grid line along one axis with the axis's factors, in the variant that suits the axis: FP64 and
-// FP32 matrix cores (mirror-symmetric, half length <= kMfMaxHalf), folded vector-FMA kernels (longer
-// mirror-symmetric axes) or the full mode matrix.
+// FP32 matrix cores (mirror-symmetric, half length <= kMfMaxHalf; FP64 along a strided axis also without the
+// symmetry, with the full matrix), folded vector-FMA kernels (longer mirror-symmetric axes) or the full
+// mode matrix on the vector units.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -56,6 +57,10 @@ hipError_t left_forward(const AxisModes& M, int n, const Columns& q, const IN* i
   }
   if constexpr (sizeof(T) != sizeof(IN)) return hipErrorInvalidValue;
   else {
+    if constexpr (sizeof(T) == sizeof(double))
+      if (M.full64)
+        return launch_mx_full_left(n, q.count, M.x64[0], in, out, q.elems, q.nseg, q.seg_stride, q.kstride, nullptr,
+                                   nullptr, nullptr, 1, 0, 0, 0, st);
     if (M.sym)
       return launch_tpf_left<T>(n, q.count, mode_half<T>(M, 0), mode_half<T>(M, 1), in, out, q.nseg, q.seg_stride,
                                 q.kstride, s.lm, s.ly, s.lx, s.nxs, s.zm, s.zj, s.zi, st);
@@ -77,6 +82,10 @@ hipError_t left_backward(const AxisModes& M, int n, const Columns& q, const T* i
   }
   if constexpr (sizeof(T) != sizeof(OUT)) return hipErrorInvalidValue;
   else {
+    if constexpr (sizeof(T) == sizeof(double))
+      if (M.full64)
+        return launch_mx_full_left(n, q.count, M.x64[1], in, out, q.elems, q.nseg, q.seg_stride, q.kstride, s.lm, s.ly,
+                                   s.lx, s.nxs, s.zm, s.zj, s.zi, st);
     if (M.sym)
       return launch_tpu_left<T>(n, q.count, mode_half<T>(M, 2), mode_half<T>(M, 3), in, out, q.nseg, q.seg_stride,
                                 q.kstride, st);

@@ -27,7 +27,7 @@ size_t mode_bytes(int n) {
   return 2 * n * sizeof(double) + 4 * nn * sizeof(double) + 4 * nn * sizeof(float) +
          3 * nn * (sizeof(double) + sizeof(float)) +
          4 * (mf_pack_size(he, 2) * sizeof(double) + mf_pack_size(he, 4) * sizeof(float)) +
-         2 * (mx_pack_size(he) * sizeof(double) + m4_pack_size(he) * sizeof(float)) +
+         (he <= kMfMaxHalf ? 2 * (mx_full_size(n) * sizeof(double) + m4_pack_size(he) * sizeof(float)) : 0) +
          64 * 16;  // alignment padding (at most 15 bytes for each of an operator's <= 36 arrays)
 }
 
@@ -72,8 +72,17 @@ void place_modes(const ModeHost& H, AxisModes& M, Stager& st) {
   const int he = (n + 1) / 2, ho = n / 2;
   M.sym = H.sym;
   M.mf = false;
+  M.full64 = !H.sym && he <= kMfMaxHalf;
   M.he = he;
   M.ho = ho;
+  if (M.full64)
+    for (int b = 0; b < 2; ++b) {
+      std::vector<double> X(mx_full_size(n), 0.0);
+      const std::vector<double>& A = b ? H.S : H.Wf;
+      for (int o = 0; o < n; ++o)
+        for (int k = 0; k < n; ++k) X[mx_pack_index(o < he ? o : o - he, k, he, o >= he)] = A[(size_t)o * n + k];
+      M.x64[b] = st.put_d(X);
+    }
   if (!H.sym) return;
   // parity-sorted modes: the he even ones (ascending), then the odd ones
   const double r2 = std::sqrt(0.5);

@@ -1,8 +1,9 @@
-// FP64 line transforms of a mirror-symmetric axis on the matrix cores, along a strided axis ("left": every
-// column of the field is multiplied by the mode matrix), in the folded half-size form of
+// FP64 line transforms on the matrix cores, along a strided axis ("left": every column of the field is multiplied
+// by the mode matrix).  A mirror-symmetric axis has the folded half-size form of
 // lk_transform.hip: forward, the line is folded on load (f_k + f_{n-1-k}, f_k - f_{n-1-k}) and contracted
 // with the even and the odd half matrix; backward, the even and the odd modes are contracted and
-// the result is unfolded on store.
+// the result is unfolded on store.  Any other axis has the full matrix, its lower and its upper rows in the
+// places of the even and the odd half matrix and the same data for both.
 //
 // The contraction uses v_mfma_f64_4x4x4 (four independent 4 x 4 blocks), which runs at 67-75 TFLOP/s here
 // against 32-46 TFLOP/s of v_mfma_f64_16x16x4 (a register-only loop of each, one to four waves per SIMD).
@@ -13,7 +14,7 @@
 //
 // A matrix piece feeds only 16 columns, so the pieces come from LDS and each is used for W column tiles of
 // the wave.  A block keeps the pieces of GT row groups (of four rows), each with those of the
-// other parity beside it so that one 16-byte read fetches both; an axis
+// other half matrix beside it so that one 16-byte read fetches both; an axis
 // with more groups is split into classes of GT, neighbouring blocks of the same XCD doing the classes of the
 // same columns.  The columns' values are loaded PD steps ahead into a register ring; with the
 // pieces in LDS these are the only vector-memory loads of the loop, so they are waited for one step at a time.
@@ -47,7 +48,9 @@ struct MxScale {  // backward only: modes divided by lm[mode] + ly[col / nxs] + 
   int nxs, zm, zj, zi;
 };
 
-template <int GT, int W, int PD, int CHP, bool FOLD, bool SCALE, int MAXW, int OCC>
+enum MxForm { kFold, kUnfold, kFull };
+
+template <int GT, int W, int PD, int CHP, MxForm FORM, bool SCALE, int MAXW, int OCC>
 __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int ho, int N, const double* __restrict__ P,
                                                             int G, int classes,
                                                             const double* __restrict__ B, double* __restrict__ C,
@@ -56,7 +59,8 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
   // pieces [KQ][GT][16], (even, odd) pairs, and a step of padding; with SCALE the eigenvalues [2][4 KQ]
   extern __shared__ D2 lds[];
   constexpr unsigned kGhost = 1u << 31;  // an offset past the field: loads give 0, stores are dropped
-  const int KQ = (he + 3) / 4;
+  constexpr bool FOLD = FORM == kFold, FULL = FORM == kFull;
+  const int K = FULL ? n : he, KQ = (K + 3) / 4;  // contracted indices, and steps of four
   const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // tiles: classes of the same columns next to each other on one XCD
@@ -83,18 +87,18 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
     }
   }
   // element k of a column: forward the pair k, n - 1 - k (the middle row once), backward the even mode k
-  // and the odd mode k
+  // and the odd mode k, full the value k
   double x1[PD][W], x2[PD][W];
   auto load = [&](int u, int kq) {
     const int k = 4 * kq + g, k2 = FOLD ? n - 1 - k : he + k;
-    const bool in1 = k < he, in2 = FOLD ? k < he && k2 != k : k < ho;
+    const bool in1 = k < K, in2 = FOLD ? k < he && k2 != k : k < ho;
     const unsigned o1 = (unsigned)k * (8u * kstride), o2 = (unsigned)k2 * (8u * kstride);
 #pragma unroll
     for (int c = 0; c < W; ++c) {
       const unsigned a1 = in1 && base[c] != kGhost ? base[c] + o1 : kGhost;
       const unsigned a2 = in2 && base[c] != kGhost ? base[c] + o2 : kGhost;
       x1[u][c] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rin, (int)a1, 0, 0));
-      x2[u][c] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rin, (int)a2, 0, 0));
+      if (!FULL) x2[u][c] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rin, (int)a2, 0, 0));
     }
   };
 #pragma unroll
@@ -120,8 +124,8 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
   double* lam = (double*)(lds + (KQ + 1) * GT * 16);
   if (SCALE)
     for (int k = tid; k < 4 * KQ; k += blockDim.x) {
-      lam[k] = k < he ? sc.lm[k] : 1.0;
-      lam[4 * KQ + k] = k < ho ? sc.lm[he + k] : 1.0;
+      lam[k] = k < K ? sc.lm[k] : 1.0;
+      if (!FULL) lam[4 * KQ + k] = k < ho ? sc.lm[he + k] : 1.0;
     }
   __syncthreads();
   if (col0 >= N) return;
@@ -151,11 +155,11 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
         s[c] = x1[u][c] + x2[u][c];
         d[c] = x1[u][c] - x2[u][c];
       } else if (SCALE) {  // padding and the constant mode stay exactly zero (no 0 / 0)
-        s[c] = (k >= he || (zc[c] && k == sc.zm)) ? 0.0 : mx_div(x1[u][c], lam[k] + sxy[c]);
-        d[c] = (k >= ho || (zc[c] && he + k == sc.zm)) ? 0.0 : mx_div(x2[u][c], lam[4 * KQ + k] + sxy[c]);
+        s[c] = (k >= K || (zc[c] && k == sc.zm)) ? 0.0 : mx_div(x1[u][c], lam[k] + sxy[c]);
+        d[c] = FULL ? s[c] : (k >= ho || (zc[c] && he + k == sc.zm)) ? 0.0 : mx_div(x2[u][c], lam[4 * KQ + k] + sxy[c]);
       } else {
         s[c] = x1[u][c];
-        d[c] = x2[u][c];
+        d[c] = FULL ? s[c] : x2[u][c];
       }
     }
 #pragma unroll
@@ -196,20 +200,21 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
   for (int t = 0; t < GT; ++t) {
     const int o = 4 * (g0 + t) + g;
     const bool in1 = o < he, in2 = o < ho;
-    const unsigned o1 = (unsigned)o * (8u * kstride), o2 = (unsigned)(FOLD ? he + o : n - 1 - o) * (8u * kstride);
+    const unsigned o1 = (unsigned)o * (8u * kstride), o2 = (unsigned)(FORM == kUnfold ? n - 1 - o : he + o) * (8u * kstride);
 #pragma unroll
     for (int c = 0; c < W; ++c) {
       const bool ok = base[c] != kGhost;
-      put(FOLD ? ae[t][c] : ae[t][c] + ao[t][c], ok && in1 ? base[c] + o1 : kGhost);
-      put(FOLD ? ao[t][c] : ae[t][c] - ao[t][c], ok && in2 ? base[c] + o2 : kGhost);
+      put(FORM == kUnfold ? ae[t][c] + ao[t][c] : ae[t][c], ok && in1 ? base[c] + o1 : kGhost);
+      put(FORM == kUnfold ? ae[t][c] - ao[t][c] : ao[t][c], ok && in2 ? base[c] + o2 : kGhost);
     }
   }
 }
 
-template <int GT, int W, int PD, int CH, int MAXW, int OCC, bool FOLD>
+template <int GT, int W, int PD, int CH, int MAXW, int OCC, MxForm FORM>
 hipError_t mx_launch(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
                      long seg_stride, long kstride, const MxScale* sc, hipStream_t st) {
-  const int he = (n + 1) / 2, ho = n / 2, KQ = (he + 3) / 4, G = KQ, classes = (G + GT - 1) / GT;
+  const int he = (n + 1) / 2, ho = n / 2, G = (he + 3) / 4, classes = (G + GT - 1) / GT;
+  const int KQ = FORM == kFull ? (n + 3) / 4 : G;
   const size_t lds = (size_t)(2 * (KQ + 1) * GT * 16 + (sc ? 8 * KQ : 0)) * sizeof(double);
   const long tiles = (N + 16 * W - 1) / (16 * W);
   // one block per CU where the waves of all classes fit the chip, else blocks of the full size
@@ -224,12 +229,12 @@ hipError_t mx_launch(int n, int N, const double* P, const double* B, double* C, 
                        (unsigned)seg_stride, (unsigned)kstride, sc ? *sc : MxScale{});
     return hipGetLastError();
   };
-  if constexpr (!FOLD)
-    if (sc) return run(k_mx_left<GT, W, PD, CH, false, true, MAXW, OCC>);
-  return run(k_mx_left<GT, W, PD, CH, FOLD, false, MAXW, OCC>);
+  if constexpr (FORM != kFold)
+    if (sc) return run(k_mx_left<GT, W, PD, CH, FORM, true, MAXW, OCC>);
+  return run(k_mx_left<GT, W, PD, CH, FORM, false, MAXW, OCC>);
 }
 
-template <bool FOLD>
+template <MxForm FORM>
 hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
                    long seg_stride, long kstride, const MxScale* sc, hipStream_t st) {
   const int G = ((n + 1) / 2 + 3) / 4;
@@ -240,12 +245,23 @@ hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, si
   // their registers for the accumulators: W = 2 halves the LDS reads, which else bound them (200^3
   // 42 against 45 us), at three waves per SIMD (n <= 208) or two (256^3: 92 us; narrower classes 97-125).
 #define MX(GT, W, PD, CH, MAXW, OCC) \
-  return mx_launch<GT, W, PD, CH, MAXW, OCC, FOLD>(n, N, P, B, C, elems, nseg, seg_stride, kstride, sc, st)
-  if (G <= 8) MX(4, 1, 4, 4, 4, 4);
-  if (G <= 15) MX(5, 1, 4, 5, 4, 4);
-  if (G <= 20) MX(10, 1, 4, 4, 12, 3);
-  if (G <= 26) MX(13, 2, 2, 4, 12, 3);
-  MX(16, 2, 2, 4, 8, 2);
+  return mx_launch<GT, W, PD, CH, MAXW, OCC, FORM>(n, N, P, B, C, elems, nseg, seg_stride, kstride, sc, st)
+  if constexpr (FORM == kFull) {
+    // Twice the products of the folded form, so the matrix cores bound it (97 x 121 x 65: 10.6 us a
+    // transform against 23 and 15 us on the vector units).  The same reasons choose the variant: few
+    // columns up to n = 136 (cubes of 100 and 130: 12 and 25 us; 5 groups of 2 tiles 11 and 29), then two
+    // tiles a wave (160^3 36 us, 200^3 87; one tile 43 and 112), and at the end half as many classes
+    // (256^3 197 us; 5 groups 225).
+    if (G <= 17) MX(4, 1, 4, 4, 4, 4);
+    if (G <= 26) MX(5, 2, 4, 5, 8, 3);
+    MX(8, 2, 4, 4, 8, 2);
+  } else {
+    if (G <= 8) MX(4, 1, 4, 4, 4, 4);
+    if (G <= 15) MX(5, 1, 4, 5, 4, 4);
+    if (G <= 20) MX(10, 1, 4, 4, 12, 3);
+    if (G <= 26) MX(13, 2, 2, 4, 12, 3);
+    MX(16, 2, 2, 4, 8, 2);
+  }
 #undef MX
 }
 
@@ -253,14 +269,21 @@ hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, si
 
 hipError_t launch_mxf_left(int n, int N, const double* P, const double* B, double* C, size_t elems,
                            int nseg, long seg_stride, long kstride, hipStream_t st) {
-  return mx_pick<true>(n, N, P, B, C, elems, nseg, seg_stride, kstride, nullptr, st);
+  return mx_pick<kFold>(n, N, P, B, C, elems, nseg, seg_stride, kstride, nullptr, st);
 }
 
 hipError_t launch_mxu_left(int n, int N, const double* P, const double* B, double* C, size_t elems,
                            int nseg, long seg_stride, long kstride, const double* lm, const double* ly, const double* lx,
                            int nxs, int zm, int zj, int zi, hipStream_t st) {
   const MxScale sc{lm, ly, lx, nxs, zm, zj, zi};
-  return mx_pick<false>(n, N, P, B, C, elems, nseg, seg_stride, kstride, lm ? &sc : nullptr, st);
+  return mx_pick<kUnfold>(n, N, P, B, C, elems, nseg, seg_stride, kstride, lm ? &sc : nullptr, st);
+}
+
+hipError_t launch_mx_full_left(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
+                               long seg_stride, long kstride, const double* lm, const double* ly, const double* lx,
+                               int nxs, int zm, int zj, int zi, hipStream_t st) {
+  const MxScale sc{lm, ly, lx, nxs, zm, zj, zi};
+  return mx_pick<kFull>(n, N, P, B, C, elems, nseg, seg_stride, kstride, lm ? &sc : nullptr, st);
 }
 
 }  // namespace lk

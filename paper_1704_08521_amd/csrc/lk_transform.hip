@@ -1,6 +1,6 @@
 // Tensor-product transforms of the pressure-correction solve: every grid line
 // along one axis is multiplied by the same n x n mode matrix (S^T M forward, S
-// backward).  Both kernels are register-tiled dense contractions on the vector
+// backward), where the kernels of lk_mx.hip and lk_m4.hip do not apply.  Both kernels are register-tiled dense contractions on the vector
 // FMA units with LDS staging; one block owns the whole transformed dimension
 // (up to 16*TM rows), so each data tile is read from HBM once.
 #include <hip/hip_runtime.h>
@@ -813,15 +813,21 @@ template <typename T>
 hipError_t launch_tp_left(int M, int N, int K, const T* A, const T* B, T* C, int nseg, long seg_stride,
                           long kstride, const double* lm, const double* ly, const double* lx, int nxs, int zm, int zj,
                           int zi, hipStream_t st) {
-  switch (pick_tile(M)) {
-    case 1: return left_launch<T, 1>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
-    case 2: return left_launch<T, 2>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
-    case 4: return left_launch<T, 4>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
-    case 8: return left_launch<T, 8>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
-    case 7: return left_launch<T, 7>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
-    case 10: return left_launch<T, 10>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
-    case 13: return left_launch<T, 13>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
-    default: return left_launch<T, 16>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+  if constexpr (sizeof(T) == sizeof(double)) {
+    // FP64 lines of up to 2 kMfMaxHalf points have the matrix cores
+    if (M <= 2 * kMfMaxHalf) return hipErrorInvalidValue;
+    return left_launch<T, 16>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+  } else {
+    switch (pick_tile(M)) {
+      case 1: return left_launch<T, 1>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+      case 2: return left_launch<T, 2>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+      case 4: return left_launch<T, 4>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+      case 8: return left_launch<T, 8>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+      case 7: return left_launch<T, 7>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+      case 10: return left_launch<T, 10>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+      case 13: return left_launch<T, 13>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+      default: return left_launch<T, 16>(M, N, K, A, B, C, nseg, seg_stride, kstride, lm, ly, lx, nxs, zm, zj, zi, st);
+    }
   }
 }
 
