@@ -315,7 +315,7 @@ void init_dims(lc_ctx* c, int nx, int ny, int nz) {
   c->nz = nz;
   c->nvel = vel_layout(nx, ny, nz).total();
   c->ncell = (size_t)nx * ny * nz;
-  c->max_parts = (int)((c->ncell + kReduceBlock - 1) / kReduceBlock) + kGsBlocks * kGsChunk;
+  c->max_parts = (int)((c->ncell + kReduceBlock - 1) / kReduceBlock) + kGsBlocks * kGsVectors;
   c->max_parts = std::max({c->max_parts, divergence_parts(nx, ny, nz), correct_div_parts(nx, ny, nz)});
 }
 

@@ -60,9 +60,6 @@ struct AxisModes {
 
 namespace lk {
 constexpr int kSumSlots = 3;
-// Sums of at most this many terms are added by the host: a reduction kernel costs a launch of about 4 us, the
-// terms about 1 us on their way and in the sum (a 64^3 Krylov vector has 256 of them, 100^3 1250).
-constexpr int kHostParts = 1024;
 }  // namespace lk
 
 struct lc_ctx {

@@ -218,12 +218,19 @@ hipError_t launch_plane_correct(const GridDev& g, int P, const double* vel, cons
 hipError_t launch_plane_potential(const GridDev& g, int P, const double* vel, double* psi, hipStream_t st);
 
 constexpr int kReduceBlock = 256;
+// Sums of at most this many terms are added by the host: a reduction kernel costs a launch of about 4 us, the
+// terms about 1 us on their way and in the sum (a 64^3 Krylov vector has 256 of them, 100^3 1250).
+constexpr int kHostParts = 1024;
 // Classical Gram-Schmidt: h[i] = V_i . w (i < nv; basis vectors ld apart; h on the device,
-// fixed-order sums), then w -= sum_i h[i] V_i.  partials holds kGsBlocks * kGsChunk doubles.
-constexpr int kGsBlocks = 2048, kGsChunk = 8;
+// fixed-order sums), with `norm` also h[nv] = w . w; then w -= sum_i h[i] V_i and the gs_update_parts() partial
+// sums of the new w . w.  The dot products take kGsVectors vectors per launch, kGsChunk per block;
+// their partials are kGsBlocks * kGsVectors doubles.
+constexpr int kGsBlocks = 512, kGsChunk = 8, kGsVectors = 32;
 // host_h (may be null) receives h as well.
-hipError_t launch_gs_dot(const double* V, long ld, int nv, const double* w, size_t n, double* partials,
+hipError_t launch_gs_dot(const double* V, long ld, int nv, bool norm, const double* w, size_t n, double* partials,
                          double* h, double* host_h, hipStream_t st);
-hipError_t launch_gs_update(const double* V, long ld, int nv, const double* h, double* w, size_t n, hipStream_t st);
+int gs_update_parts(size_t n);  // at most kHostParts
+hipError_t launch_gs_update(const double* V, long ld, int nv, const double* h, double* w, size_t n, double* partials,
+                            hipStream_t st);
 
 }  // namespace lk

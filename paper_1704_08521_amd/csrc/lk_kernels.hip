@@ -149,29 +149,57 @@ __global__ void __launch_bounds__(256) k_combine(const double* __restrict__ V, l
     if (c < nc) out[(size_t)c * ldo + q] = acc[c];
 }
 
-// Classical Gram-Schmidt in two streaming passes.  Block dot products of NB basis
-// vectors with w (w read once per NB vectors): per-block partial sums, stored
-// partials[i * nblocks + block] for vector i of the chunk.
+// Values two at a time; vectors are 8-byte aligned (16-byte loads need no more).
+typedef double D2 __attribute__((ext_vector_type(2)));
+struct __attribute__((packed, aligned(8))) D2u {
+  D2 x;
+};
+__device__ __forceinline__ D2 load2(const double* p) { return ((const D2u*)p)->x; }
+__device__ __forceinline__ void store2(double* p, D2 x) { ((D2u*)p)->x = x; }
+
+// Gram-Schmidt dot products, HBM bound on reading the basis: chunk blockIdx.y of NB of the vectors V_0 .. V_{nv-1}, w
+// (the last one gives w . w), each against w.  partials[i][blockIdx.x].  One launch takes all vectors: 64^3,
+// 20 vectors 16 us (8 TB/s out of the Infinity Cache) where a launch of 8 vectors with 8-byte loads took 15 and
+// its reduction 4.
 template <int NB>
-__global__ void __launch_bounds__(kReduceBlock) k_block_dot(const double* __restrict__ V, long ld, int cnt,
+__global__ void __launch_bounds__(kReduceBlock) k_block_dot(const double* __restrict__ V, long ld, int nv, int total,
                                                             const double* __restrict__ w, size_t n,
                                                             double* __restrict__ partials) {
-  double t[NB];
+  __shared__ double red[NB][kReduceBlock / 64];
+  const int i0 = blockIdx.y * NB, cnt = min(NB, total - i0);
+  const double* p[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {  // (a repeated vector's sum is not stored)
+    const int q = i0 + min(i, cnt - 1);
+    p[i] = q < nv ? V + (size_t)q * ld : w;
+  }
+  D2 t[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) t[i] = 0.0;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride) {
-    const double x = w[q];
+  const size_t stride = 2 * (size_t)gridDim.x * kReduceBlock;
+  size_t q = 2 * ((size_t)blockIdx.x * kReduceBlock + threadIdx.x);
+  for (; q + 1 < n; q += stride) {
+    const D2 x = load2(w + q);
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-      if (i < cnt) t[i] = fma(V[(size_t)i * ld + q], x, t[i]);
+    for (int i = 0; i < NB; ++i) {
+      const D2 y = load2(p[i] + q);
+      t[i] = D2{fma(y.x, x.x, t[i].x), fma(y.y, x.y, t[i].y)};
+    }
   }
+  if (q < n)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) t[i].x = fma(p[i][q], w[q], t[i].x);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    if (i >= cnt) break;
-    const double s = block_sum(t[i]);
-    if (threadIdx.x == 0) partials[(size_t)i * gridDim.x + blockIdx.x] = s;
-    __syncthreads();  // block_sum's shared scratch is reused by the next sum
+    const double s = wave_sum(t[i].x + t[i].y);
+    if (lane == 0) red[i][wave] = s;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < cnt) {
+    double s = 0.0;
+    for (int k = 0; k < kReduceBlock / 64; ++k) s += red[threadIdx.x][k];
+    partials[(size_t)(i0 + threadIdx.x) * gridDim.x + blockIdx.x] = s;
   }
 }
 
@@ -194,14 +222,34 @@ __global__ void __launch_bounds__(1024) k_sum_segments(const double* __restrict_
   }
 }
 
-// w -= sum_i h[i] V[i] (i < nv, coefficients from device memory, summed in order i)
-__global__ void __launch_bounds__(256) k_gs_update(const double* __restrict__ V, long ld, int nv,
-                                                   const double* __restrict__ h, double* __restrict__ w, size_t n) {
-  const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
-  double acc = 0.0;
-  for (int i = 0; i < nv; ++i) acc = fma(V[(size_t)i * ld + q], h[i], acc);
-  w[q] -= acc;
+// w -= sum_i h[i] V[i] (i < nv, coefficients from device memory, summed in order i), and the partial sums of
+// w . w, which a pass of its own read w for.
+__global__ void __launch_bounds__(kReduceBlock) k_gs_update(const double* __restrict__ V, long ld, int nv,
+                                                            const double* __restrict__ h, double* __restrict__ w,
+                                                            size_t n, double* __restrict__ partials) {
+  const size_t stride = 2 * (size_t)gridDim.x * kReduceBlock;
+  double sum = 0.0;
+  for (size_t q = 2 * ((size_t)blockIdx.x * kReduceBlock + threadIdx.x); q < n; q += stride) {
+    if (q + 1 < n) {
+      D2 acc = 0.0;
+#pragma unroll 8
+      for (int i = 0; i < nv; ++i) {
+        const D2 y = load2(V + (size_t)i * ld + q);
+        acc = D2{fma(y.x, h[i], acc.x), fma(y.y, h[i], acc.y)};
+      }
+      const D2 x = load2(w + q) - acc;
+      store2(w + q, x);
+      sum = fma(x.x, x.x, fma(x.y, x.y, sum));
+    } else {
+      double acc = 0.0;
+      for (int i = 0; i < nv; ++i) acc = fma(V[(size_t)i * ld + q], h[i], acc);
+      const double x = w[q] - acc;
+      w[q] = x;
+      sum = fma(x, x, sum);
+    }
+  }
+  sum = block_sum(sum);
+  if (threadIdx.x == 0) partials[blockIdx.x] = sum;
 }
 
 }  // namespace
@@ -237,22 +285,29 @@ hipError_t launch_combine(const double* V, long ld, int nv, const double* Q, int
   return hipGetLastError();
 }
 
-hipError_t launch_gs_dot(const double* V, long ld, int nv, const double* w, size_t n, double* partials,
+hipError_t launch_gs_dot(const double* V, long ld, int nv, bool norm, const double* w, size_t n, double* partials,
                          double* h, double* host_h, hipStream_t st) {
-  unsigned nb = blocks_for(n, kReduceBlock);
-  if (nb > (unsigned)kGsBlocks) nb = kGsBlocks;
-  for (int i0 = 0; i0 < nv; i0 += kGsChunk) {
-    const int cnt = nv - i0 < kGsChunk ? nv - i0 : kGsChunk;
-    hipLaunchKernelGGL(k_block_dot<kGsChunk>, dim3(nb), dim3(kReduceBlock), 0, st, V + (size_t)i0 * ld, ld, cnt, w,
-                       n, partials);
+  const unsigned nb = std::min(blocks_for((n + 1) / 2, kReduceBlock), (unsigned)kGsBlocks);
+  const int total = nv + (norm ? 1 : 0);
+  for (int i0 = 0; i0 < total; i0 += kGsVectors) {
+    const int cnt = std::min(kGsVectors, total - i0);
+    hipLaunchKernelGGL(k_block_dot<kGsChunk>, dim3(nb, (cnt + kGsChunk - 1) / kGsChunk), dim3(kReduceBlock), 0, st,
+                       V + (size_t)i0 * ld, ld, nv - i0, cnt, w, n, partials);
     hipLaunchKernelGGL(k_sum_segments, dim3(cnt), dim3(1024), 0, st, partials, (int)nb, h + i0,
                        host_h ? host_h + i0 : nullptr);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_gs_update(const double* V, long ld, int nv, const double* h, double* w, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(k_gs_update, dim3(blocks_for(n, 256)), dim3(256), 0, st, V, ld, nv, h, w, n);
+// blocks of equal numbers of rounds, at most kHostParts of them
+int gs_update_parts(size_t n) {
+  const size_t blocks = ((n + 1) / 2 + kReduceBlock - 1) / kReduceBlock, rounds = (blocks + kHostParts - 1) / kHostParts;
+  return (int)((blocks + rounds - 1) / rounds);
+}
+
+hipError_t launch_gs_update(const double* V, long ld, int nv, const double* h, double* w, size_t n, double* partials,
+                            hipStream_t st) {
+  hipLaunchKernelGGL(k_gs_update, dim3(gs_update_parts(n)), dim3(kReduceBlock), 0, st, V, ld, nv, h, w, n, partials);
   return hipGetLastError();
 }
 

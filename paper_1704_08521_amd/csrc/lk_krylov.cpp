@@ -105,14 +105,15 @@ int mgs(lc_ctx* c, const Basis& V, int nv, double* w, double* h) {
   double before = 0.0, after = 0.0;
   for (int pass = 0; pass < 2; ++pass) {
     // the norm before, the projections and the norm after come with one wait
-    if (pass == 0 && (rc = dot_queue(c, w, w, 0))) return rc;
     KLAUNCH(c, LC_K_VECTOR,
-            launch_gs_dot(V.at(0), V.ld, nv, w, c->nvel, c->partials, c->dsmall, c->hsmall_d, c->stream));
-    KLAUNCH(c, LC_K_VECTOR, launch_gs_update(V.at(0), V.ld, nv, c->dsmall, w, c->nvel, c->stream));
-    if ((rc = dot_queue(c, w, w, 1)) || (rc = sums_wait(c))) return rc;
-    if (pass == 0) before = vnorm(sum_of(c, 0));
+            launch_gs_dot(V.at(0), V.ld, nv, pass == 0, w, c->nvel, c->partials, c->dsmall, c->hsmall_d, c->stream));
+    const int np = gs_update_parts(c->nvel);
+    KLAUNCH(c, LC_K_VECTOR,
+            launch_gs_update(V.at(0), V.ld, nv, c->dsmall, w, c->nvel, parts_of(c, 0, np), c->stream));
+    if ((rc = finish_queue(c, 0, np)) || (rc = sums_wait(c))) return rc;
+    if (pass == 0) before = vnorm(c->hsmall[nv]);
     for (int i = 0; i < nv; ++i) h[i] += c->hsmall[i];
-    after = vnorm(sum_of(c, 1));
+    after = vnorm(sum_of(c, 0));
     if (!(after < 0.7071067811865476 * before)) break;
     before = after;
   }
