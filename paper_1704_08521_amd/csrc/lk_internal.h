@@ -128,6 +128,8 @@ hipError_t launch_tpu_right(int n, int Mlines, const T* A, const T* SeT, const T
 // array of pieces per direction, and the eigenvalue scaling (lm, ly, lx, zero mode) belongs to the backward
 // transform: its input modes are scaled on load.
 constexpr int kMfMaxHalf = 128;
+// FP64 transforms along x of symmetric axes up to this half length go by the left kernels
+constexpr int kMxXHalf = 104;
 constexpr int kMfPD = 1;
 __host__ __device__ constexpr int mf_steps(int he, int pd = kMfPD) { return ((he + 3) / 4 + pd - 1) / pd * pd; }
 // Fragments are grouped fg = 16 / sizeof(element) per lane (one 16-byte load fetches fg

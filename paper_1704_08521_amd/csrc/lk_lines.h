@@ -1,5 +1,5 @@
 // Transforms of every grid line along one axis with the axis's factors, in the variant that suits the axis: FP64 and
-// FP32 matrix cores (mirror-symmetric, half length <= kMfMaxHalf; FP64 along a strided axis also without the
+// FP32 matrix cores (mirror-symmetric, half length <= kMfMaxHalf; FP64 also without the
 // symmetry, with the full matrix), folded vector-FMA kernels (longer mirror-symmetric axes) or the full
 // mode matrix on the vector units.
 #pragma once
@@ -94,8 +94,20 @@ hipError_t left_backward(const AxisModes& M, int n, const Columns& q, const T* i
   }
 }
 
+// Along x the FP64 left kernels serve too, a line being a column whose rows are neighbours: their reads and writes are
+// 32-byte pieces, but their matrix instructions twice as fast as those of the kernels below (100^3 12.3 us a
+// transform against 14.3, 150^3 24.5 / 31.5, 200^3 59 / 63, full matrix 100^3 15.6 / 27.5, 256^3 211 / 261).
+// Symmetric axes past kMxXHalf, where their data is read twice, keep the others (256^3 131 / 119), and so does FP32
+// (150^3 29 / 23).
+template <typename T>
+inline bool right_by_left(const AxisModes& M) {
+  return sizeof(T) == sizeof(double) && (M.full64 || (M.mf && M.he <= kMxXHalf));
+}
+inline Columns lines_as_columns(int n, int lines) { return Columns{lines, 1, n, 1, (size_t)n * lines}; }
+
 template <typename T>
 hipError_t right_forward(const AxisModes& M, int n, int lines, const T* in, T* out, hipStream_t st) {
+  if (right_by_left<T>(M)) return left_forward<T>(M, n, lines_as_columns(n, lines), in, out, LineScale{}, st);
   if (M.mf) return launch_mff_right<T>(n, lines, in, mode_pack<T>(M, 0), mode_pack<T>(M, 1), out, st);
   if (M.sym) return launch_tpf_right<T>(n, lines, in, mode_half<T>(M, 4), mode_half<T>(M, 5), out, st);
   return launch_tp_right<T>(lines, n, n, in, mode_full<T>(M, 2), out, st);
@@ -103,6 +115,7 @@ hipError_t right_forward(const AxisModes& M, int n, int lines, const T* in, T* o
 
 template <typename T>
 hipError_t right_backward(const AxisModes& M, int n, int lines, const T* in, T* out, hipStream_t st) {
+  if (right_by_left<T>(M)) return left_backward<T>(M, n, lines_as_columns(n, lines), in, out, LineScale{}, st);
   if (M.mf) return launch_mfu_right<T>(n, lines, in, mode_pack<T>(M, 2), mode_pack<T>(M, 3), out, st);
   if (M.sym) return launch_tpu_right<T>(n, lines, in, mode_half<T>(M, 6), mode_half<T>(M, 7), out, st);
   return launch_tp_right<T>(lines, n, n, in, mode_full<T>(M, 3), out, st);

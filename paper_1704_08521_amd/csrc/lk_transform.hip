@@ -833,15 +833,20 @@ hipError_t launch_tp_left(int M, int N, int K, const T* A, const T* B, T* C, int
 
 template <typename T>
 hipError_t launch_tp_right(int M, int N, int K, const T* A, const T* B, T* C, hipStream_t st) {
-  switch (pick_tile(N)) {
-    case 1: return right_launch<T, 1>(M, N, K, A, B, C, st);
-    case 2: return right_launch<T, 2>(M, N, K, A, B, C, st);
-    case 4: return right_launch<T, 4>(M, N, K, A, B, C, st);
-    case 8: return right_launch<T, 8>(M, N, K, A, B, C, st);
-    case 7: return right_launch<T, 7>(M, N, K, A, B, C, st);
-    case 10: return right_launch<T, 10>(M, N, K, A, B, C, st);
-    case 13: return right_launch<T, 13>(M, N, K, A, B, C, st);
-    default: return right_launch<T, 16>(M, N, K, A, B, C, st);
+  if constexpr (sizeof(T) == sizeof(double)) {
+    if (N <= 2 * kMfMaxHalf) return hipErrorInvalidValue;  // (as on the left)
+    return right_launch<T, 16>(M, N, K, A, B, C, st);
+  } else {
+    switch (pick_tile(N)) {
+      case 1: return right_launch<T, 1>(M, N, K, A, B, C, st);
+      case 2: return right_launch<T, 2>(M, N, K, A, B, C, st);
+      case 4: return right_launch<T, 4>(M, N, K, A, B, C, st);
+      case 8: return right_launch<T, 8>(M, N, K, A, B, C, st);
+      case 7: return right_launch<T, 7>(M, N, K, A, B, C, st);
+      case 10: return right_launch<T, 10>(M, N, K, A, B, C, st);
+      case 13: return right_launch<T, 13>(M, N, K, A, B, C, st);
+      default: return right_launch<T, 16>(M, N, K, A, B, C, st);
+    }
   }
 }
 
@@ -1003,13 +1008,16 @@ LK_TPF_INST(float)
 // kernels with 8 row tiles (n > 224), which spill at 3.
 constexpr int kMfW = 1;
 template <typename T, int RT>
+constexpr bool mf_used() { return sizeof(T) == sizeof(float) || 16 * RT > kMxXHalf; }  // (shorter FP64 lines: lk_mx.hip)
+template <typename T, int RT>
 constexpr int mf_lb() { return sizeof(T) == sizeof(double) && RT < 8 ? 3 : 2; }
 
 template <typename T>
 hipError_t launch_mff_right(int n, int Mlines, const T* A, const T* Pe, const T* Po, T* C, hipStream_t st) {
   const int he = (n + 1) / 2, ho = n / 2;
+  if (sizeof(T) == sizeof(double) && he <= kMxXHalf) return hipErrorInvalidValue;
   const dim3 grid(blocks_for(blocks_for(Mlines, 16 * kMfW), 4));
-#define BODY(RT) hipLaunchKernelGGL((k_mff_right<T, RT, kMfW, kMfPD, mf_lb<T, RT>()>), grid, dim3(256), 0, st, n, he, ho, Mlines, A, Pe, Po, C);
+#define BODY(RT) if constexpr (mf_used<T, RT>()) hipLaunchKernelGGL((k_mff_right<T, RT, kMfW, kMfPD, mf_lb<T, RT>()>), grid, dim3(256), 0, st, n, he, ho, Mlines, A, Pe, Po, C);
   LK_MF_SWITCH((he + 15) / 16, BODY)
 #undef BODY
   return hipGetLastError();
@@ -1018,8 +1026,9 @@ hipError_t launch_mff_right(int n, int Mlines, const T* A, const T* Pe, const T*
 template <typename T>
 hipError_t launch_mfu_right(int n, int Mlines, const T* A, const T* Pse, const T* Pso, T* C, hipStream_t st) {
   const int he = (n + 1) / 2, ho = n / 2;
+  if (sizeof(T) == sizeof(double) && he <= kMxXHalf) return hipErrorInvalidValue;
   const dim3 grid(blocks_for(blocks_for(Mlines, 16 * kMfW), 4));
-#define BODY(RT) hipLaunchKernelGGL((k_mfu_right<T, RT, kMfW, kMfPD, mf_lb<T, RT>()>), grid, dim3(256), 0, st, n, he, ho, Mlines, A, Pse, Pso, C);
+#define BODY(RT) if constexpr (mf_used<T, RT>()) hipLaunchKernelGGL((k_mfu_right<T, RT, kMfW, kMfPD, mf_lb<T, RT>()>), grid, dim3(256), 0, st, n, he, ho, Mlines, A, Pse, Pso, C);
   LK_MF_SWITCH((he + 15) / 16, BODY)
 #undef BODY
   return hipGetLastError();
