@@ -12,7 +12,7 @@
 namespace lk {
 
 // Division by lm[mode] + ly[j] + lx[i] between a forward and a backward left transform (column = j * nxs + i), the mode
-// (zm, zj, zi) set to zero (negative: none).  The vector-FMA kernels divide in the forward
+// (zm, zj, zi) set to zero (zm negative: none).  The vector-FMA kernels divide in the forward
 // transform, the matrix-core ones in the backward one; both calls of a pair get the same scale.
 struct LineScale {
   const double *lm = nullptr, *ly = nullptr, *lx = nullptr;
@@ -103,6 +103,10 @@ template <typename T>
 inline bool right_by_left(const AxisModes& M) {
   return sizeof(T) == sizeof(double) && (M.full64 || (M.mf && M.he <= kMxXHalf));
 }
+// The FP64 matrix-core backward transform takes a scale with ly or lx null (adding nothing) and zj or zi negative (any
+// column); the other kernels do not.
+inline bool scale_may_omit(const AxisModes& M) { return M.mf || M.full64; }
+
 inline Columns lines_as_columns(int n, int lines) { return Columns{lines, 1, n, 1, (size_t)n * lines}; }
 
 template <typename T>

@@ -43,7 +43,9 @@ __device__ __forceinline__ double mx_div(double v, double a) {
   return fma(fma(-a, q, v), y, q);
 }
 
-struct MxScale {  // backward only: modes divided by lm[mode] + ly[col / nxs] + lx[col % nxs], the mode (zm, zj, zi) zeroed
+// backward only: modes divided by lm[mode] + ly[col / nxs] + lx[col % nxs] (ly, lx may be null: 0), the mode
+// (zm, zj, zi) zeroed (zm negative: none; zj, zi negative: any)
+struct MxScale {
   const double *lm, *ly, *lx;
   int nxs, zm, zj, zi;
 };
@@ -82,8 +84,8 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
     base[c] = col < N ? 8u * ((unsigned)(col / nseg) * seg_stride + (unsigned)(col % nseg)) : kGhost;
     if (SCALE) {
       const int jj = col < N ? col / sc.nxs : 0, ii = col < N ? col % sc.nxs : 0;
-      sxy[c] = sc.ly[jj] + sc.lx[ii];
-      zc[c] = jj == sc.zj && ii == sc.zi;
+      sxy[c] = (sc.ly ? sc.ly[jj] : 0.0) + (sc.lx ? sc.lx[ii] : 0.0);
+      zc[c] = (sc.zj < 0 || jj == sc.zj) && (sc.zi < 0 || ii == sc.zi);
     }
   }
   // element k of a column: forward the pair k, n - 1 - k (the middle row once), backward the even mode k

@@ -22,36 +22,41 @@ struct Keep {
   static constexpr bool u = P != 2, v = P != 1, w = P != 3;
 };
 
-// r = D2 b, one thread per cell (grid: x tiles of the row, y = j, z = k): b is the input
-// with the dropped component and the wall-normal faces set to zero.
+// r = D2 b, one thread per cell in memory order (rows of any length leave no lanes idle): b is the input
+// with the dropped component and the wall-normal faces set to zero.  Every load from an in-range position, the
+// walls selected afterwards, so that they are in flight together.  HBM bound (81 MB at 150^3, 14 us):
+// 19 to 23 us against 23 to 25 with a block per row (neighbouring rows on one XCD: 20 to 24).
 template <int P>
 __global__ void __launch_bounds__(kPlaneBlock) k_plane_rhs(GridDev g, const double* __restrict__ vel,
                                                             double* __restrict__ r) {
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
-  const int i = blockIdx.x * kPlaneBlock + threadIdx.x, j = blockIdx.y, k = blockIdx.z;
-  if (i >= nx) return;
-  const Idx I{nx, ny, nz};
+  const unsigned q = blockIdx.x * kPlaneBlock + threadIdx.x;  // (a field holds fewer than 2^28 values)
+  if (q >= (unsigned)nx * ny * nz) return;
+  const unsigned row = q / (unsigned)nx, k = row / (unsigned)ny;
+  const int i = (int)(q - row * nx), j = (int)(row - k * ny);
   const size_t nu = (size_t)(nx + 1) * ny * nz, nv = (size_t)nx * (ny + 1) * nz;
   double s = 0.0;
   if (Keep<P>::u) {
-    const double ue = (i + 1 < nx) ? vel[I.u(k, j, i + 1)] : 0.0, uw = (i > 0) ? vel[I.u(k, j, i)] : 0.0;
-    s += (ue - uw) * g.x.rd[i];
+    const double* u = vel + q + row;
+    const double uw = u[0], ue = u[1];
+    s += ((i + 1 < nx ? ue : 0.0) - (i > 0 ? uw : 0.0)) * g.x.rd[i];
   }
   if (Keep<P>::v) {
-    const double vn = (j + 1 < ny) ? vel[nu + I.v(k, j + 1, i)] : 0.0, vs = (j > 0) ? vel[nu + I.v(k, j, i)] : 0.0;
-    s += (vn - vs) * g.y.rd[j];
+    const double* v = vel + nu + q + (size_t)k * nx;
+    const double vs = v[0], vn = v[nx];
+    s += ((j + 1 < ny ? vn : 0.0) - (j > 0 ? vs : 0.0)) * g.y.rd[j];
   }
   if (Keep<P>::w) {
-    const double wt = (k + 1 < nz) ? vel[nu + nv + I.w(k + 1, j, i)] : 0.0;
-    const double wb = (k > 0) ? vel[nu + nv + I.w(k, j, i)] : 0.0;
-    s += (wt - wb) * g.z.rd[k];
+    const double* w = vel + nu + nv + q;
+    const double wb = w[0], wt = w[(size_t)nx * ny];
+    s += (((int)k + 1 < nz ? wt : 0.0) - (k > 0 ? wb : 0.0)) * g.z.rd[k];
   }
-  r[I.c(k, j, i)] = s;
+  r[q] = s;
 }
 
 // Mode space: t /= (lx[i] + ly[j] + lz[k]) over the two in-plane axes (the normal
 // axis's array is null and contributes nothing); the modes whose in-plane indices are
-// both zero modes (one per plane: the plane's constant) are set to zero.  A negative
+// both zero modes (one per plane: the plane's constant) are set to zero.  (Matrix-core transforms divide on load.)  A negative
 // zero-mode index stands for the normal axis, where every index matches.  Grid as the
 // right side.
 __global__ void __launch_bounds__(kPlaneBlock) k_plane_scale(double* __restrict__ t, int nx, int ny,
@@ -98,9 +103,30 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_correct(GridDev g, const 
   }
 }
 
+// Inclusive prefix sum over the wave: within rows of 16 lanes by row shifts, then the totals of the rows
+// before (broadcasts of lane 15 and lane 31 of the vector unit).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double x) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xf, false);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xf, false);
+  return x + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_scan(double x) {
+  x = dpp_add<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8 (lanes without a source add 0)
+  x = dpp_add<0x112, 0xf>(x);
+  x = dpp_add<0x114, 0xf>(x);
+  x = dpp_add<0x118, 0xf>(x);
+  x = dpp_add<0x142, 0xa>(x);  // lane 15 of each row to the next: rows 1 and 3
+  x = dpp_add<0x143, 0xc>(x);  // lane 31 to rows 2 and 3
+  return x;
+}
+
 // Row prefix sums for the potentials of P = 1 and P = 3: one wave per row of n source
 // values src[row][i]; psi[row][0] = 0 and psi[row][i + 1] = psi[row][i] + sgn d[i] src[row][i].
-// The wave scans 64 values at a time (shuffle scan) and carries the running total.
+// The wave scans 64 values at a time and carries the running total; kRowBatch of them are
+// loaded together.  150^3 (54 MB): 13 us; with a load, a wait and a scan through LDS permutes at a time 15.5.
+constexpr int kRowBatch = 4;
 __global__ void __launch_bounds__(kPlaneBlock) k_row_scan(const double* __restrict__ src, const double* __restrict__ d,
                                                            double sgn, int n, long rows, double* __restrict__ psi) {
   const int lane = (int)(threadIdx.x % 64);
@@ -110,16 +136,21 @@ __global__ void __launch_bounds__(kPlaneBlock) k_row_scan(const double* __restri
   double* o = psi + (size_t)row * (n + 1);
   if (lane == 0) o[0] = 0.0;
   double carry = 0.0;
-  for (int base = 0; base < n; base += 64) {
-    const int i = base + lane;
-    double x = (i < n) ? sgn * d[i] * s[i] : 0.0;
-    for (int off = 1; off < 64; off <<= 1) {
-      const double y = __shfl_up(x, off);
-      if (lane >= off) x += y;
+  for (int base = 0; base < n; base += 64 * kRowBatch) {
+    double x[kRowBatch];
+#pragma unroll
+    for (int t = 0; t < kRowBatch; ++t) {
+      const int i = min(base + 64 * t + lane, n - 1);
+      x[t] = sgn * d[i] * s[i];
     }
-    x += carry;
-    if (i < n) o[i + 1] = x;
-    carry = __shfl(x, 63);
+#pragma unroll
+    for (int t = 0; t < kRowBatch; ++t) {
+      const int i = base + 64 * t + lane;
+      if (base + 64 * t >= n) break;
+      const double y = carry + wave_scan(i < n ? x[t] : 0.0);
+      if (i < n) o[i + 1] = y;
+      carry = __shfl(y, 63);
+    }
   }
 }
 
@@ -127,10 +158,13 @@ __global__ void __launch_bounds__(kPlaneBlock) k_row_scan(const double* __restri
 // psi[k][0][i] = 0, psi[k][j + 1][i] = psi[k][j][i] - dy[j] w[k][j][i].
 // Block: 64 columns i x kColSeg segments of the j range (one wave per segment); each
 // wave sums its segment, the segment offsets go through LDS, then each wave writes its
-// running sums.  Loads are batched kColBatch at a time, each from an in-range row (the
-// segment's last for the batch's surplus), so a batch's loads are in flight together.
-constexpr int kColSeg = 8, kColBatch = 8;
+// running sums.  Loads are batched NB at a time, each from an in-range row (the
+// segment's last for the batch's surplus), so a batch's loads are in flight together; a segment of one
+// batch (ONCE) keeps its values in registers for the second part, a longer one reads them again.
+// 150^3 (54 MB): 16.5 us, 21.6 with batches of 8 read twice.
+constexpr int kColSeg = 8;
 
+template <int NB, bool ONCE>
 __global__ void __launch_bounds__(64 * kColSeg) k_col_scan(const double* __restrict__ w,
                                                             const double* __restrict__ dy, int nx, int ny,
                                                             double* __restrict__ psi) {
@@ -141,19 +175,21 @@ __global__ void __launch_bounds__(64 * kColSeg) k_col_scan(const double* __restr
   const bool col = i < nx;
   const double* src = w + (size_t)k * ny * nx + (col ? i : 0);
   double* dst = psi + (size_t)k * (ny + 1) * nx + (col ? i : 0);
-  double s = 0.0;
-  for (int jb = j0; jb < j1; jb += kColBatch) {
-    double x[kColBatch];
+  double x[NB];
+  auto load = [&](int jb) {
 #pragma unroll
-    for (int t = 0; t < kColBatch; ++t) {
-      // in range, and masked by a product rather than a select (a select of a loaded value
-      // is turned back into a branch around the load): the batch's loads all go out
-      // before the sum waits
-      const int jr = min(jb + t, j1 - 1);
-      x[t] = dy[jr] * src[(size_t)jr * nx] * ((col && jb + t < j1) ? 1.0 : 0.0);
+    for (int t = 0; t < NB; ++t) {
+      // in range (a segment without rows re-reads the column's last one), and masked by a product rather
+      // than a select (a select of a loaded value is turned back into a branch around the load)
+      const int jr = max(min(jb + t, j1 - 1), 0);
+      x[t] = dy[jr] * src[(size_t)jr * nx] * ((jb + t < j1) ? 1.0 : 0.0);
     }
+  };
+  double s = 0.0;
+  for (int jb = j0; jb < (ONCE ? j0 + 1 : j1); jb += NB) {
+    load(jb);
 #pragma unroll
-    for (int t = 0; t < kColBatch; ++t) s += x[t];
+    for (int t = 0; t < NB; ++t) s += x[t];
   }
   part[seg][lane] = s;
   __syncthreads();
@@ -161,15 +197,10 @@ __global__ void __launch_bounds__(64 * kColSeg) k_col_scan(const double* __restr
   for (int t = 0; t < seg; ++t) acc += part[t][lane];
   if (!col) return;
   if (seg == 0) dst[0] = 0.0;
-  for (int jb = j0; jb < j1; jb += kColBatch) {
-    double x[kColBatch];
+  for (int jb = j0; jb < j1; jb += NB) {
+    if (!ONCE) load(jb);
 #pragma unroll
-    for (int t = 0; t < kColBatch; ++t) {
-      const int jr = min(jb + t, j1 - 1);
-      x[t] = dy[jr] * src[(size_t)jr * nx] * ((jb + t < j1) ? 1.0 : 0.0);
-    }
-#pragma unroll
-    for (int t = 0; t < kColBatch; ++t) {
+    for (int t = 0; t < NB; ++t) {
       acc += x[t];
       if (jb + t < j1) dst[(size_t)(jb + t + 1) * nx] = -acc;
     }
@@ -179,7 +210,7 @@ __global__ void __launch_bounds__(64 * kColSeg) k_col_scan(const double* __restr
 }  // namespace
 
 hipError_t launch_plane_rhs(const GridDev& g, int P, const double* vel, double* r, hipStream_t st) {
-  const dim3 grid(blocks_for(g.x.n, kPlaneBlock), g.y.n, g.z.n), block(kPlaneBlock);
+  const dim3 grid(blocks_for((size_t)g.x.n * g.y.n * g.z.n, kPlaneBlock)), block(kPlaneBlock);
   if (P == 1)
     hipLaunchKernelGGL(k_plane_rhs<1>, grid, block, 0, st, g, vel, r);
   else if (P == 2)
@@ -212,8 +243,16 @@ hipError_t launch_plane_potential(const GridDev& g, int P, const double* vel, do
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
   const VelLayout L = vel_layout(nx, ny, nz);
   if (P == 2) {  // Psi_x from w2, columns in y, planes k = 0..nz
-    hipLaunchKernelGGL(k_col_scan, dim3(blocks_for(nx, 64), nz + 1), dim3(64 * kColSeg), 0, st, vel + L.ow(), g.y.d,
-                       nx, ny, psi);
+    const dim3 grid(blocks_for(nx, 64), nz + 1), block(64 * kColSeg);
+    const int len = (ny + kColSeg - 1) / kColSeg;
+    if (len <= 8)
+      hipLaunchKernelGGL((k_col_scan<8, true>), grid, block, 0, st, vel + L.ow(), g.y.d, nx, ny, psi);
+    else if (len <= 20)
+      hipLaunchKernelGGL((k_col_scan<20, true>), grid, block, 0, st, vel + L.ow(), g.y.d, nx, ny, psi);
+    else if (len <= 32)
+      hipLaunchKernelGGL((k_col_scan<32, true>), grid, block, 0, st, vel + L.ow(), g.y.d, nx, ny, psi);
+    else
+      hipLaunchKernelGGL((k_col_scan<8, false>), grid, block, 0, st, vel + L.ow(), g.y.d, nx, ny, psi);
   } else {  // Psi_y from w1 (rows (k, j), k up to nz) or Psi_z from v3 (rows (k, j), j up to ny)
     const long rows = (P == 1) ? (long)(nz + 1) * ny : (long)nz * (ny + 1);
     const double* src = (P == 1) ? vel + L.ow() : vel + L.ov();

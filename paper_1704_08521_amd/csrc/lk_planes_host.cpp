@@ -15,7 +15,7 @@ namespace {
 // One transform pass along `axis` (0 x, 1 y, 2 z), forward (S^T M) or backward (S).  Left transforms: y runs over columns
 // (k, i) with rows nx apart in segments of nx columns, one plane apart; z over the columns of a
 // plane with rows a plane apart.
-int axis_pass(lc_ctx* c, int axis, bool fwd, const double* in, double* out) {
+int axis_pass(lc_ctx* c, int axis, bool fwd, const double* in, double* out, const LineScale& sc = LineScale{}) {
   const int nx = c->nx, ny = c->ny, nz = c->nz, pl = nx * ny;
   const AxisModes& M = c->modes[axis];
   hipStream_t s = c->stream;
@@ -26,8 +26,8 @@ int axis_pass(lc_ctx* c, int axis, bool fwd, const double* in, double* out) {
   }
   const Columns q = axis == 1 ? Columns{nx * nz, nx, pl, nx, c->ncell} : Columns{pl, pl, 0, pl, c->ncell};
   const int kid = axis == 1 ? LC_K_TP_Y : LC_K_TP_Z, n = axis == 1 ? ny : nz;
-  if (fwd) KLAUNCH(c, kid, left_forward<double>(M, n, q, in, out, LineScale{}, s));
-  else KLAUNCH(c, kid, left_backward<double>(M, n, q, in, out, LineScale{}, s));
+  if (fwd) KLAUNCH(c, kid, left_forward<double>(M, n, q, in, out, sc, s));
+  else KLAUNCH(c, kid, left_backward<double>(M, n, q, in, out, sc, s));
   return LC_OK;
 }
 
@@ -71,9 +71,14 @@ extern "C" int lc_plane_project(lc_ctx* c, const double* v, int which, double* o
     lam[ax] = ax == nrm ? nullptr : (M.sym ? M.lam_s : M.lam);
     zm[ax] = ax == nrm ? -1 : c->zero_mode[ax];
   }
-  KLAUNCH(c, LC_K_PLANES,
-          launch_plane_scale(c->t2, c->nx, c->ny, c->nz, lam[0], lam[1], lam[2], zm[0], zm[1], zm[2], s));
-  rc = axis_pass(c, b, false, c->t2, c->t1);
+  if (scale_may_omit(c->modes[b])) {  // the backward transform along b divides on load
+    const int o = b == 1 ? 2 : 1;     // the outer axis of its columns
+    rc = axis_pass(c, b, false, c->t2, c->t1, LineScale{lam[b], lam[o], lam[0], c->nx, zm[b], zm[o], zm[0]});
+  } else {
+    KLAUNCH(c, LC_K_PLANES,
+            launch_plane_scale(c->t2, c->nx, c->ny, c->nz, lam[0], lam[1], lam[2], zm[0], zm[1], zm[2], s));
+    rc = axis_pass(c, b, false, c->t2, c->t1);
+  }
   if (!rc) rc = axis_pass(c, a, false, c->t1, c->phi);
   if (rc) return rc;
   KLAUNCH(c, LC_K_PLANES, launch_plane_correct(c->g, which, v, c->phi, out, s));
