@@ -40,8 +40,8 @@ __device__ __forceinline__ int xcd_tile(int bid, int nb) {
 // fields and writing one reaches), issues about 60 us of vector instructions at two waves per
 // SIMD, and its loads and stores take the address unit about 35 us (16 cycles per load
 // instruction of a CU whether a lane asks for 8 or 16 bytes, hence the pairs).  Measured, against
-// 16 x 8 tiles whose threads each took one face and all neighbours from LDS: 16^3 14 against 32 us,
-// 64^3 18 / 28, 100^3 24 / 35, 150^3 69 / 88, 200^3 153 / 181 (3.8 TB/s of 3 fields), 256^3 283 / 354;
+// 16 x 8 tiles whose threads each took one face and all neighbours from LDS: 16^3 11 against 32 us,
+// 64^3 17 / 28, 100^3 24 / 35, 150^3 69 / 88, 200^3 153 / 181 (3.8 TB/s of 3 fields), 256^3 283 / 354;
 // 97 x 121 x 65 22 / 32.  Rows of 64 lanes leave more of them idle (150^3 85 us), rows of 16 do
 // more halo work (200^3 163 us); everything in registers with no LDS (8-byte loads of every
 // neighbouring row) is bound by the address unit: 189 us with two rows per wave, 218 us with one.
@@ -570,15 +570,15 @@ __global__ void __launch_bounds__(64 * kMomWY, 4) k_correct_div(GridDev g, const
 // blocks, each as long as a chunk's planes and its start-up, end soonest.  Chunks stay short
 // because neighbouring blocks then read their common rows and planes at about the same time, from
 // the L2: at 256^3 13 planes 283 us, 16 to 20 292-304 us, 34 323 us; at 200^3 12 to 20 150-155 us, 34 177 us.
+// Small grids take chunks down to one plane (16^3 6.8 us, three planes 10.6; 64^3 14.1 / 15.9).
 constexpr int kMomSlots = 512;
 
 int momentum_chunk(int nx, int ny, int nz) {
   const long tiles = (long)blocks_for(nx + 1, kMomTX) * blocks_for(ny + 1, kMomTY);
   int best = 0;
   double least = 0.0;
-  for (int nch = 1; nch <= std::max(1, (nz + 1) / 3); ++nch) {
-    const int planes = (int)blocks_for(nz + 1, nch);
-    if (planes > kMomMaxChunk) continue;
+  for (int most = kMomMaxChunk; most >= 1; --most) {
+    const int planes = (int)blocks_for(nz + 1, blocks_for(nz + 1, most));  // chunks of equal length
     const long rounds = blocks_for((size_t)tiles * blocks_for(nz + 1, planes), kMomSlots);
     const double cost = rounds * (planes + 2.5);
     if (!best || cost < least) best = planes, least = cost;
@@ -638,7 +638,7 @@ hipError_t launch_correct(const GridDev& g, const double* w, const double* phi, 
 static int correct_chunk(int nx, int ny, int nz) {
   const long tiles = (long)blocks_for(nx + 1, kMomTX) * blocks_for(ny + 1, kMomTY);
   const long most = std::max<long>(1, 2 * kMomSlots / tiles);
-  return (int)std::min<long>(kCdMaxChunk, std::max<long>(2, blocks_for(nz, (unsigned)most)));
+  return (int)std::min<long>(kCdMaxChunk, std::max<long>(1, blocks_for(nz, (unsigned)most)));
 }
 
 int correct_div_parts(int nx, int ny, int nz) {
