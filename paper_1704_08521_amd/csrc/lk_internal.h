@@ -234,5 +234,11 @@ hipError_t launch_gs_dot(const double* V, long ld, int nv, bool norm, const doub
 int gs_update_parts(size_t n);  // at most kHostParts
 hipError_t launch_gs_update(const double* V, long ld, int nv, const double* h, double* w, size_t n, double* partials,
                             hipStream_t st);
+// The same update for 1 to kGsFused vectors with h2[i] = V_i . w of the new w; gs_update_dot_parts() partial sums of
+// the norm; dots holds kGsBlocks * kGsVectors doubles.
+constexpr int kGsFused = 48;
+int gs_update_dot_parts(size_t n, int nv);  // at most kHostParts
+hipError_t launch_gs_update_dot(const double* V, long ld, int nv, const double* h, double* w, size_t n,
+                                double* partials, double* dots, double* h2, double* host_h2, hipStream_t st);
 
 }  // namespace lk

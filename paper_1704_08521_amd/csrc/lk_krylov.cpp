@@ -103,16 +103,29 @@ int mgs(lc_ctx* c, const Basis& V, int nv, double* w, double* h) {
   std::fill(h, h + nv + 1, 0.0);
   int rc;
   double before = 0.0, after = 0.0;
+  // up to kGsFused vectors: the first update also leaves the projections of a second pass, in the upper halves
+  const bool fused = nv >= 1 && nv <= kGsFused;
+  const int h2 = fused ? kSmall / 2 : 0;
   for (int pass = 0; pass < 2; ++pass) {
     // the norm before, the projections and the norm after come with one wait
-    KLAUNCH(c, LC_K_VECTOR,
-            launch_gs_dot(V.at(0), V.ld, nv, pass == 0, w, c->nvel, c->partials, c->dsmall, c->hsmall_d, c->stream));
-    const int np = gs_update_parts(c->nvel);
-    KLAUNCH(c, LC_K_VECTOR,
-            launch_gs_update(V.at(0), V.ld, nv, c->dsmall, w, c->nvel, parts_of(c, 0, np), c->stream));
+    if (pass == 0 || !fused)
+      KLAUNCH(c, LC_K_VECTOR,
+              launch_gs_dot(V.at(0), V.ld, nv, pass == 0, w, c->nvel, c->partials, c->dsmall, c->hsmall_d, c->stream));
+    const double* hp = c->dsmall + (pass ? h2 : 0);
+    int np;
+    if (pass == 0 && fused) {
+      np = gs_update_dot_parts(c->nvel, nv);
+      KLAUNCH(c, LC_K_VECTOR,
+              launch_gs_update_dot(V.at(0), V.ld, nv, hp, w, c->nvel, parts_of(c, 0, np), c->partials, c->dsmall + h2,
+                                   c->hsmall_d + h2, c->stream));
+    } else {
+      np = gs_update_parts(c->nvel);
+      KLAUNCH(c, LC_K_VECTOR,
+              launch_gs_update(V.at(0), V.ld, nv, hp, w, c->nvel, parts_of(c, 0, np), c->stream));
+    }
     if ((rc = finish_queue(c, 0, np)) || (rc = sums_wait(c))) return rc;
     if (pass == 0) before = vnorm(c->hsmall[nv]);
-    for (int i = 0; i < nv; ++i) h[i] += c->hsmall[i];
+    for (int i = 0; i < nv; ++i) h[i] += c->hsmall[(pass ? h2 : 0) + i];
     after = vnorm(sum_of(c, 0));
     if (!(after < 0.7071067811865476 * before)) break;
     before = after;
