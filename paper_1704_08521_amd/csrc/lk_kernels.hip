@@ -159,8 +159,8 @@ __device__ __forceinline__ void store2(double* p, D2 x) { ((D2u*)p)->x = x; }
 
 // Gram-Schmidt dot products, HBM bound on reading the basis: chunk blockIdx.y of NB of the vectors V_0 .. V_{nv-1}, w
 // (the last one gives w . w), each against w.  partials[i][blockIdx.x].  One launch takes all vectors: 64^3,
-// 20 vectors 16 us (8 TB/s out of the Infinity Cache) where a launch of 8 vectors with 8-byte loads took 15 and
-// its reduction 4.
+// 20 vectors 21.5 us (6 TB/s, mostly out of the Infinity Cache) and one reduction of 4 us, where each launch of 8
+// vectors with 8-byte loads took 15 and a reduction of its own.
 template <int NB>
 __global__ void __launch_bounds__(kReduceBlock) k_block_dot(const double* __restrict__ V, long ld, int nv, int total,
                                                             const double* __restrict__ w, size_t n,
