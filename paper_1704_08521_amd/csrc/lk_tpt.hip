@@ -56,13 +56,14 @@ __device__ __forceinline__ float rcpx(float a) {
   return fmaf(fmaf(-a, y, 1.0f), y, y);
 }
 
-// x of the lane D below (UP) or above within the LPW lanes of a line; 0 or any other lane's value past their ends
+// x of the lane D below (UP) or above within the LPW lanes of a line; past their ends 0 or the lane's own (never another
+// line's: what is not finite stays in its line)
 template <int LPW, int D, bool UP>
 __device__ __forceinline__ float lane_shift(float x) {
   if constexpr (LPW == 16)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), (UP ? 0x110 : 0x100) + D,
                                                                  0xf, 0xf, true));
-  else return UP ? __shfl_up(x, D) : __shfl_down(x, D);
+  else return UP ? __shfl_up(x, D, LPW) : __shfl_down(x, D, LPW);
 }
 template <int LPW, int D, bool UP>
 __device__ __forceinline__ double lane_shift(double x) {
@@ -73,7 +74,7 @@ __device__ __forceinline__ double lane_shift(double x) {
     const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), ctrl, 0xf, 0xf, true);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
   } else {
-    return UP ? __shfl_up(x, D) : __shfl_down(x, D);
+    return UP ? __shfl_up(x, D, LPW) : __shfl_down(x, D, LPW);
   }
 }
 

@@ -40,3 +40,27 @@ def test_tridiagonal_pass(dims):
         phi = c.poisson_solve(rd, precision=prec).cpu().numpy().reshape(ref.shape)
         err = np.max(np.abs(phi - ref)) / np.max(np.abs(ref))
         assert err < bound, (dims, prec, err)
+
+
+@pytest.mark.parametrize("n", [40, 230, 300, 600])
+def test_lines_do_not_reach_each_other(n):
+    # the lines of a wave belong to neighbouring planes y = const of the plane projection: a value that is not
+    # finite in one plane leaves the others as they are without it
+    import torch
+
+    import paper_1704_08521_amd as lk
+    dims = (n, 6, 4)
+    print(f"[case] {dims}", flush=True)
+    c = lk.Context(*dims)
+    c.set_stretching("tanh", 4.0)
+    v = synth.random_velocity(*dims, 77)
+    bad = v.copy()
+    u = bad[:(n + 1) * 6 * 4].reshape(4, 6, n + 1)
+    u[2, 3, n // 2] = np.nan
+    ref, got = (c.plane_project(torch.from_numpy(f).cuda(), 1)[0].cpu().numpy() for f in (v, bad))
+    for off, shape in ((0, (4, 6, n + 1)), ((n + 1) * 24 + n * 28, (5, 6, n))):
+        size = int(np.prod(shape))
+        a, b = (f[off:off + size].reshape(shape) for f in (ref, got))
+        keep = [0, 1, 2, 4, 5]
+        assert np.array_equal(a[:, keep], b[:, keep])
+    assert np.isnan(got).any()
