@@ -27,8 +27,7 @@
  * from a caller-owned block sized by lc_workspace_query.
  *
  * Return codes: LC_OK = 0; LC_ENOTCONV = 1 (outputs valid, tolerance not met);
- * negative values are errors, the message is in lc_last_error(); device outputs are undefined after
- * an error found in the data (a non-finite input).
+ * negative values are errors, the message is in lc_last_error().
  */
 #ifndef LIDKRYLOV_H
 #define LIDKRYLOV_H

@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -85,10 +86,15 @@ int krylov_ws(lc_ctx* c, int nvec, double** p, long* ld) {
   return LC_OK;
 }
 
+// What a watched sum's place holds until the device has written it: a NaN that no arithmetic makes.
+constexpr uint64_t kUnset = 0x7ff8a5c3e1d2b497ull;
+
 double now_ms() {
   using namespace std::chrono;
   return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
 }
+
+double* terms_of(const lc_ctx* c, int slot) { return c->hsum + kSumSlots + (size_t)slot * kHostParts; }
 
 // Where the terms of slot `slot` go: to the host when it adds them itself, else to the device scratch.
 double* parts_of(lc_ctx* c, int slot, int nparts) {
@@ -101,8 +107,12 @@ int finish_queue(lc_ctx* c, int slot, int nparts) {
   return LC_OK;
 }
 
-int div_queue(lc_ctx* c, const double* v, double* r, int slot) {
+int div_queue(lc_ctx* c, const double* v, double* r, int slot, bool watch) {
   const int np = divergence_parts(c->nx, c->ny, c->nz);
+  if (watch) {
+    uint64_t* const u = (uint64_t*)(np <= kHostParts ? terms_of(c, slot) : c->hsum + slot);
+    std::fill(u, u + (np <= kHostParts ? np : 1), kUnset);
+  }
   KLAUNCH(c, LC_K_DIVERGENCE, launch_divergence(c->g, v, r, parts_of(c, slot, np), c->stream));
   return finish_queue(c, slot, np);
 }
@@ -111,6 +121,21 @@ int dot_queue(lc_ctx* c, const double* a, const double* b, int slot) {
   int np = dot_parts(c->nvel);
   KLAUNCH(c, LC_K_VECTOR, launch_dot_partials(a, b, c->nvel, parts_of(c, slot, np), &np, c->stream));
   return finish_queue(c, slot, np);
+}
+
+int watched_wait(lc_ctx* c, int slot) {
+  const int n = c->pending[slot];
+  const uint64_t* const u = (const uint64_t*)(n ? terms_of(c, slot) : c->hsum + slot);
+  unsigned turns = 0;
+  for (int i = 0; i < (n ? n : 1); ++i)
+    while (__atomic_load_n(u + i, __ATOMIC_ACQUIRE) == kUnset)
+      if (++turns % (1u << 20) == 0) {  // a stream that has ended leaves nothing to wait for
+        const hipError_t e = hipStreamQuery(c->stream);
+        if (e == hipSuccess) return LC_OK;
+        (void)hipGetLastError();  // (not ready is no error of the next launch)
+        if (e != hipErrorNotReady) HIPCHK(c, e);
+      }
+  return LC_OK;
 }
 
 int sums_wait(lc_ctx* c) {
@@ -124,7 +149,7 @@ double sum_of(const lc_ctx* c, int slot) {
   if (!n) return c->hsum[slot];
   static_assert(kHostParts <= 1024, "one term per thread of the reduction kernel");
   double t[kHostParts];
-  std::memcpy(t, c->hsum + kSumSlots + (size_t)slot * kHostParts, n * sizeof(double));
+  std::memcpy(t, terms_of(c, slot), n * sizeof(double));
   int m = n;
   for (int w = 512; w > 0; w >>= 1) {
     for (int i = 0; i + w < m; ++i) t[i] += t[i + w];
@@ -207,7 +232,7 @@ static bool uses_tridiag(const lc_ctx* c) { return c->poisson_method == LC_POISS
 // solve per x-line, transforms back with S.  TPF: transforms along x, y and z and a division by
 // the sums of the axis eigenvalues (constant mode set to zero).
 template <typename T, typename F>
-int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2) {
+int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2, const std::function<int()>& after_first) {
   const int nx = c->nx, ny = c->ny, nz = c->nz;
   const AxisModes &X = c->modes[0], &Y = c->modes[1], &Z = c->modes[2];
   auto lams = [](const AxisModes& M) { return M.sym ? M.lam_s : M.lam; };
@@ -217,6 +242,8 @@ int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2) {
   const LineScale none;
   if (uses_tridiag(c)) {
     KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, r, t1, none, s));
+    if (after_first)
+      if (const int rc = after_first()) return rc;
     KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t1, t2, none, s));
     KLAUNCH(c, LC_K_TRIDIAG,
             launch_tridiag_x<T>(c->g, lams(Y), lams(Z), c->zero_mode[1], c->zero_mode[2], t2, t1, s));
@@ -227,6 +254,8 @@ int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2) {
   if constexpr (sizeof(F) == sizeof(T)) {
     const LineScale sc{lams(Z), lams(Y), lams(X), nx, c->zero_mode[2], c->zero_mode[1], c->zero_mode[0]};
     KLAUNCH(c, LC_K_TP_X, right_forward<T>(X, nx, ny * nz, r, t1, s));
+    if (after_first)
+      if (const int rc = after_first()) return rc;
     KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, t1, t2, none, s));
     KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t2, t1, sc, s));
     KLAUNCH(c, LC_K_TP_Z, left_backward<T>(Z, nz, cz, t1, t2, sc, s));
@@ -237,12 +266,12 @@ int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2) {
   return fail(c, LC_ESTATE, "FP64 field in an FP32 solve along x (internal)");
 }
 
-int poisson(lc_ctx* c, const double* r, double* phi, int precision) {
-  if (precision == LC_FP64) return tp_solve<double>(c, r, phi, c->t1, c->t2);
+int poisson(lc_ctx* c, const double* r, double* phi, int precision, const std::function<int()>& after_first) {
+  if (precision == LC_FP64) return tp_solve<double>(c, r, phi, c->t1, c->t2, after_first);
   // FP32: where the first and the last transform read and write FP64 fields there are no casts
-  if (uses_tridiag(c) && c->modes[1].mf) return tp_solve<float>(c, r, phi, c->t1_32, c->t2_32);
+  if (uses_tridiag(c) && c->modes[1].mf) return tp_solve<float>(c, r, phi, c->t1_32, c->t2_32, after_first);
   KLAUNCH(c, LC_K_CAST, launch_d2f(c->ncell, r, c->r32, c->stream));
-  int rc = tp_solve<float>(c, c->r32, c->r32, c->t1_32, c->t2_32);
+  int rc = tp_solve<float>(c, c->r32, c->r32, c->t1_32, c->t2_32, after_first);
   if (rc) return rc;
   KLAUNCH(c, LC_K_CAST, launch_f2d(c->ncell, c->r32, phi, false, c->stream));
   return LC_OK;
@@ -375,8 +404,8 @@ int create(lc_ctx** out, int nx, int ny, int nz, void* ws, size_t ws_bytes, void
     return fail(nullptr, LC_ENOMEM, "device allocation failed for %dx%dx%d", nx, ny, nz);
   }
   ok = hipHostMalloc((void**)&c->hsmall, kSmall * sizeof(double), hipHostMallocDefault) == hipSuccess &&
-       hipHostMalloc((void**)&c->hsum, kSumSlots * (1 + kHostParts) * sizeof(double), hipHostMallocDefault) ==
-           hipSuccess &&
+       hipHostMalloc((void**)&c->hsum, kSumSlots * (1 + kHostParts) * sizeof(double),
+                     hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
        hipHostGetDevicePointer((void**)&c->hsmall_d, c->hsmall, 0) == hipSuccess &&
        hipHostGetDevicePointer((void**)&c->hsum_d, c->hsum, 0) == hipSuccess;
   if (!ok) {
@@ -645,8 +674,8 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   // keep D v from the certificate.
   const int pass_precision = precision == LC_LEARNED ? LC_MIXED : precision;
   const bool keep_r = pass_precision != LC_FP64;
-  auto pass = [&](bool accumulate) -> int {
-    int e = poisson(c, c->r, c->phi, pass_precision);
+  auto pass = [&](bool accumulate, const std::function<int()>& after_first = {}) -> int {
+    int e = poisson(c, c->r, c->phi, pass_precision, after_first);
     if (e) return e;
     if (!accumulate) {
       const int np = correct_div_parts(c->nx, c->ny, c->nz);
@@ -657,12 +686,31 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
     KLAUNCH(c, LC_K_CORRECT, launch_correct(c->g, w, c->phi, v, p, true, c->stream));
     return div_queue(c, v, keep_r ? c->r : nullptr, 1);
   };
-  // The first pass does not depend on |D w|, so without a guess it is queued behind it and both norms
-  // come with one wait.
+  // |D w| decides whether there is a pass at all, and v and p stay as they are if it is not finite.  Without a
+  // guess it is read while the pass's first transform runs, which needs D w but not its norm and writes
+  // nothing of the caller's, so that the GPU does not wait for the host here.
+  double n0 = 0.0;
+  auto read_norm = [&]() -> int {
+    n0 = std::sqrt(sum_of(c, 0));
+    return std::isfinite(n0) ? LC_OK : fail(c, LC_EINVAL, "non-finite input");
+  };
   const bool ahead = precision != LC_LEARNED;
-  if ((rc = div_queue(c, w, c->r, 0)) || (ahead && (rc = pass(false))) || (rc = sums_wait(c))) return rc;
-  const double n0 = std::sqrt(sum_of(c, 0));
-  if (!std::isfinite(n0)) return fail(c, LC_EINVAL, "non-finite input");
+  if ((rc = div_queue(c, w, c->r, 0, ahead))) return rc;
+  if (ahead) {
+    constexpr int kNoPass = 2;
+    rc = pass(false, [&]() -> int {
+      if (const int e = watched_wait(c, 0)) return e;
+      if (const int e = read_norm()) {
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        return e;
+      }
+      return n0 == 0.0 ? kNoPass : LC_OK;
+    });
+    if (rc == LC_OK) rc = sums_wait(c);
+    if (rc && rc != kNoPass) return rc;
+  } else if ((rc = sums_wait(c)) || (rc = read_norm())) {
+    return rc;
+  }
   S.rho0 = n0;
   if (n0 == 0.0) {
     // already divergence-free: v = w (walls zeroed), p = 0

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -167,17 +168,21 @@ int reduce_max_to_host(lc_ctx* c, int nparts, double* out);
 // Sums in two halves, so that several wait together: queue the kernels of slot `slot` (0 .. kSumSlots - 1),
 // wait for the stream, read the slot.  div_queue: sum V (D v)^2 (r receives D v when not null);
 // dot_queue: a . b.
-int div_queue(lc_ctx* c, const double* v, double* r, int slot);
+// With `watch`, watched_wait returns as soon as the slot can be read, whatever the stream has queued behind it.
+int div_queue(lc_ctx* c, const double* v, double* r, int slot, bool watch = false);
+int watched_wait(lc_ctx* c, int slot);
 int dot_queue(lc_ctx* c, const double* a, const double* b, int slot);
 int sums_wait(lc_ctx* c);
-// where the terms of a slot go (nparts of them), and the end of the queueing
+// the host's place of a slot's terms; where the terms of a slot go (nparts of them), and the end of the queueing
+double* terms_of(const lc_ctx* c, int slot);
 double* parts_of(lc_ctx* c, int slot, int nparts);
 int finish_queue(lc_ctx* c, int slot, int nparts);
 double sum_of(const lc_ctx* c, int slot);
 // |D v|_V (r receives D v when not null)
 int vnorm_div(lc_ctx* c, const double* v, double* r, double* out);
-// pressure-correction solve in the given precision
-int poisson(lc_ctx* c, const double* r, double* phi, int precision);
+// pressure-correction solve in the given precision; after_first (may be empty) is called when its first transform
+// is queued, and ends it by returning nonzero
+int poisson(lc_ctx* c, const double* r, double* phi, int precision, const std::function<int()>& after_first = {});
 // Euclidean dot product / max |x| of velocity vectors, host results
 int vdot(lc_ctx* c, const double* a, const double* b, double* out);
 int vmaxabs(lc_ctx* c, const double* a, double* out);
