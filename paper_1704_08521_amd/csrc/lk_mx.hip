@@ -240,12 +240,17 @@ template <MxForm FORM>
 hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
                    long seg_stride, long kstride, const MxScale* sc, hipStream_t st) {
   const int G = ((n + 1) / 2 + 3) / 4;
-  // Groups per class, column tiles and ring by the number of row groups G (of n = 8 G points).  Up to n = 120
-  // the columns of a cube are few: narrow waves and more classes fill the chip (100^3: 7.3 us a
-  // transform; 13 groups in one class of 2 tiles 12).  From there the data is read once or
-  // twice and wider waves save reads of the pieces (150^3: 16 us; 3 classes 18).  The last two need
-  // their registers for the accumulators: W = 2 halves the LDS reads, which else bound them (200^3
-  // 42 against 45 us), at three waves per SIMD (n <= 208) or two (256^3: 92 us; narrower classes 97-125).
+  // Groups per class, column tiles and ring by the number of row groups G (of n = 8 G points) and the columns.  Up
+  // to n = 120 the columns of a cube are few: narrow waves and more classes fill the chip (100^3: 7.3 us a
+  // transform; 13 groups in one class of 2 tiles 12), and so they do for any length with up to about 10000 columns
+  // (64, 2500 and 10000 columns of 200: 12, 11 and 22 us; the wide variant 26, 28 and 26; of 256: 13, 18 and 32
+  // against 37, 42 and 35; 16384 columns of 200 and 256: 26 and 43 against 27 and 36).  At n = 128 two
+  // classes of 8 groups (128^3 14.4 and 18.2 us along y and z, 10 groups 15.7 and 19.6).  From there the data is read
+  // once or twice and wider waves save reads of the pieces (150^3: 16 us; 3 classes 18); blocks of up to 16
+  // waves, four per SIMD, hold all of 160^3 at once (27 and 30 us; blocks of 12, whose last few
+  // made a second round, 36 and 41).  The last two need their registers for the accumulators: W = 2 halves the
+  // LDS reads, which else bound them (200^3 42 against 45 us), at three waves per SIMD (n <= 208) or two (256^3: 92 us;
+  // narrower classes 97-125).
 #define MX(GT, W, PD, CH, MAXW, OCC) \
   return mx_launch<GT, W, PD, CH, MAXW, OCC, FORM>(n, N, P, B, C, elems, nseg, seg_stride, kstride, sc, st)
   if constexpr (FORM == kFull) {
@@ -259,8 +264,9 @@ hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, si
     MX(8, 2, 4, 4, 8, 2);
   } else {
     if (G <= 8) MX(4, 1, 4, 4, 4, 4);
-    if (G <= 15) MX(5, 1, 4, 5, 4, 4);
-    if (G <= 20) MX(10, 1, 4, 4, 12, 3);
+    if (G <= 15 || N <= 10000) MX(5, 1, 4, 5, 4, 4);
+    if (G <= 16) MX(8, 1, 4, 4, 4, 4);
+    if (G <= 20) MX(10, 1, 4, 4, 16, 4);
     if (G <= 26) MX(13, 2, 2, 4, 12, 3);
     MX(16, 2, 2, 4, 8, 2);
   }
