@@ -248,9 +248,11 @@ hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, si
   // classes of 8 groups (128^3 14.4 and 18.2 us along y and z, 10 groups 15.7 and 19.6).  From there the data is read
   // once or twice and wider waves save reads of the pieces (150^3: 16 us; 3 classes 18); blocks of up to 16
   // waves, four per SIMD, hold all of 160^3 at once (27 and 30 us; blocks of 12, whose last few
-  // made a second round, 36 and 41).  The last two need their registers for the accumulators: W = 2 halves the
-  // LDS reads, which else bound them (200^3 42 against 45 us), at three waves per SIMD (n <= 208) or two (256^3: 92 us;
-  // narrower classes 97-125).
+  // made a second round, 36 and 41).  The last three need their registers for the accumulators: W = 2 halves the
+  // LDS reads, which else bound them (200^3 42 against 45 us), at three waves per SIMD (n <= 208; classes of 11 groups up to 176, where
+  // two of 13 have more rows to spare: 176^3 29 and 34 us against 33 and 37) or two (256^3: 92 us; narrower
+  // classes 97-125).  With 13 groups one to three vector registers are spilled; smaller chunks of pieces change neither
+  // that nor the time.
 #define MX(GT, W, PD, CH, MAXW, OCC) \
   return mx_launch<GT, W, PD, CH, MAXW, OCC, FORM>(n, N, P, B, C, elems, nseg, seg_stride, kstride, sc, st)
   if constexpr (FORM == kFull) {
@@ -267,6 +269,7 @@ hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, si
     if (G <= 15 || N <= 10000) MX(5, 1, 4, 5, 4, 4);
     if (G <= 16) MX(8, 1, 4, 4, 4, 4);
     if (G <= 20) MX(10, 1, 4, 4, 16, 4);
+    if (G <= 22) MX(11, 2, 2, 4, 12, 3);
     if (G <= 26) MX(13, 2, 2, 4, 12, 3);
     MX(16, 2, 2, 4, 8, 2);
   }

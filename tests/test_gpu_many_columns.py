@@ -1,7 +1,7 @@
 """FP64 left transforms of more than 10000 columns, through the pressure solve on both routes.
 
 Lines of more than 120 points go by the number of columns too: up to 10000 one variant serves every length,
-beyond it there is one each up to n = 128, 160, 208 and 256.  Lengths on both sides of these limits, odd and even
+beyond it there is one each up to n = 128, 160, 176, 208 and 256.  Lengths on both sides of these limits, odd and even
 ones, with 9999, 10000 and 10100 columns on y (segmented) and on z.  Tolerance as for the other transform
 instances, 1e-13 n.
 """
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("axis", [1, 2])
-@pytest.mark.parametrize("n", [120, 121, 127, 128, 129, 159, 160, 161, 207, 208, 209, 255, 256])
+@pytest.mark.parametrize("n", [120, 121, 127, 128, 129, 159, 160, 161, 176, 177, 207, 208, 209, 255, 256])
 def test_left_transforms_of_many_columns(n, axis):
     import torch
 
