@@ -128,8 +128,17 @@ hipError_t launch_tpu_right(int n, int Mlines, const T* A, const T* SeT, const T
 // array of pieces per direction, and the eigenvalue scaling (lm, ly, lx, zero mode) belongs to the backward
 // transform: its input modes are scaled on load.
 constexpr int kMfMaxHalf = 128;
-// FP64 transforms along x of symmetric axes up to this half length go by the left kernels
-constexpr int kMxXHalf = 104;
+// FP64 transforms along x of a mirror-symmetric axis of n points go by the left kernels (a line being a column whose
+// rows are neighbours), else by the kernels for lines.  The left kernels' matrix instructions are twice as
+// fast, but their reads and writes are 32-byte pieces: us a transform of a cube, left / lines, 64^3 7.6 / 9.0, 80^3
+// 10.1 / 11.5, 100^3 12.2 / 15.6, 120^3 16.7 / 18.1, 136^3 22 / 28, 150^3 25 / 31, 200^3 58 / 62, 201^3 61 / 67.
+// Lines that start on 128-byte boundaries all meet the same few places of the caches: 96^3 16 / 14, 112^3 20 / 16,
+// 128^3 21 / 17, 176^3 41 / 36, 208^3 70 / 68 (32^3 to 80^3 as the others).  From 161 to 192 points the
+// kernels for lines have no idle rows (161^3 33 / 33, 176^3 41 / 36, 190^3 51 / 48, 192^3 56 / 48), and past 208 the
+// left kernels read their data twice (256^3 131 / 119).
+__host__ __device__ constexpr bool mx_along_x(int n) {
+  return (n <= 160 || (n > 192 && n <= 208)) && (n < 96 || n % 16 != 0);
+}
 constexpr int kMfPD = 1;
 __host__ __device__ constexpr int mf_steps(int he, int pd = kMfPD) { return ((he + 3) / 4 + pd - 1) / pd * pd; }
 // Fragments are grouped fg = 16 / sizeof(element) per lane (one 16-byte load fetches fg

@@ -94,14 +94,12 @@ hipError_t left_backward(const AxisModes& M, int n, const Columns& q, const T* i
   }
 }
 
-// Along x the FP64 left kernels serve too, a line being a column whose rows are neighbours: their reads and writes are
-// 32-byte pieces, but their matrix instructions twice as fast as those of the kernels below (100^3 12.3 us a
-// transform against 14.3, 150^3 24.5 / 31.5, 200^3 59 / 63, full matrix 100^3 15.6 / 27.5, 256^3 211 / 261).
-// Symmetric axes past kMxXHalf, where their data is read twice, keep the others (256^3 131 / 119), and so does FP32
+// Along x the FP64 left kernels serve too, on mirror-symmetric axes by the rule of mx_along_x, else with the full
+// matrix (100^3 15.6 us a transform against 27.5, 256^3 211 / 261).  FP32 keeps the kernels for lines
 // (150^3 29 / 23).
 template <typename T>
 inline bool right_by_left(const AxisModes& M) {
-  return sizeof(T) == sizeof(double) && (M.full64 || (M.mf && M.he <= kMxXHalf));
+  return sizeof(T) == sizeof(double) && (M.full64 || (M.mf && mx_along_x(M.he + M.ho)));
 }
 // The FP64 matrix-core backward transform takes a scale with ly or lx null (adding nothing) and zj or zi negative (any
 // column); the other kernels do not.

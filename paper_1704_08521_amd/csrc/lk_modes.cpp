@@ -141,7 +141,7 @@ void place_modes(const ModeHost& H, AxisModes& M, Stager& st) {
             P4[mf_pack_index(kq, t, l, RT, 4)] = v;
           }
         }
-    if (he > kMxXHalf) M.p64[q] = st.put_d(P2);
+    if (!mx_along_x(n)) M.p64[q] = st.put_d(P2);
     M.p32[q] = st.put_f(P4);
   }
   for (int b = 0; b < 2; ++b) {

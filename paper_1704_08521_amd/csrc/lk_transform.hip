@@ -1008,14 +1008,14 @@ LK_TPF_INST(float)
 // kernels with 8 row tiles (n > 224), which spill at 3.
 constexpr int kMfW = 1;
 template <typename T, int RT>
-constexpr bool mf_used() { return sizeof(T) == sizeof(float) || 16 * RT > kMxXHalf; }  // (shorter FP64 lines: lk_mx.hip)
+constexpr bool mf_used() { return sizeof(T) == sizeof(float) || RT >= 3; }  // (the other FP64 lines: mx_along_x)
 template <typename T, int RT>
 constexpr int mf_lb() { return sizeof(T) == sizeof(double) && RT < 8 ? 3 : 2; }
 
 template <typename T>
 hipError_t launch_mff_right(int n, int Mlines, const T* A, const T* Pe, const T* Po, T* C, hipStream_t st) {
   const int he = (n + 1) / 2, ho = n / 2;
-  if (sizeof(T) == sizeof(double) && he <= kMxXHalf) return hipErrorInvalidValue;
+  if (sizeof(T) == sizeof(double) && mx_along_x(n)) return hipErrorInvalidValue;
   const dim3 grid(blocks_for(blocks_for(Mlines, 16 * kMfW), 4));
 #define BODY(RT) if constexpr (mf_used<T, RT>()) hipLaunchKernelGGL((k_mff_right<T, RT, kMfW, kMfPD, mf_lb<T, RT>()>), grid, dim3(256), 0, st, n, he, ho, Mlines, A, Pe, Po, C);
   LK_MF_SWITCH((he + 15) / 16, BODY)
@@ -1026,7 +1026,7 @@ hipError_t launch_mff_right(int n, int Mlines, const T* A, const T* Pe, const T*
 template <typename T>
 hipError_t launch_mfu_right(int n, int Mlines, const T* A, const T* Pse, const T* Pso, T* C, hipStream_t st) {
   const int he = (n + 1) / 2, ho = n / 2;
-  if (sizeof(T) == sizeof(double) && he <= kMxXHalf) return hipErrorInvalidValue;
+  if (sizeof(T) == sizeof(double) && mx_along_x(n)) return hipErrorInvalidValue;
   const dim3 grid(blocks_for(blocks_for(Mlines, 16 * kMfW), 4));
 #define BODY(RT) if constexpr (mf_used<T, RT>()) hipLaunchKernelGGL((k_mfu_right<T, RT, kMfW, kMfPD, mf_lb<T, RT>()>), grid, dim3(256), 0, st, n, he, ho, Mlines, A, Pse, Pso, C);
   LK_MF_SWITCH((he + 15) / 16, BODY)
