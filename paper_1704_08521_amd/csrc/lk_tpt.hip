@@ -12,7 +12,7 @@
 // transform route does.  The plane projections use the same pass with one shift array
 // null (adding nothing) and a negative zero-mode index matching every index.
 //
-// Few lanes with many rows each: a row costs about 18 instructions, a step of the reduction about 45, so 16 lanes
+// Few lanes with many rows each, as long as there are lines to fill the chip: a row costs about 18 instructions, a step of the reduction about 45, so 16 lanes
 // (four steps, their neighbours reached by row shifts of the vector unit) do a third of the work of 64 lanes
 // (six steps through LDS permutes) and leave fewer lanes idle.  A segment is 13 values at 200 cells, which
 // the lanes could only read and write piecemeal; so the lines of a wave, one contiguous piece of the field, are
@@ -256,8 +256,12 @@ hipError_t launch_tridiag_x(const GridDev& g, const double* ly, const double* lz
   const int n = g.x.n, ny = g.y.n, nz = g.z.n;
   const long lines = (long)ny * nz;
   const double *rd = g.x.rd, *rdd = g.x.rdd, *dx = g.x.d;
-  // rows per lane: the smallest instance that covers the line with 16 lanes; from 208 cells on the 16 rows that this
-  // would take leave no registers for the next group's loads in FP64 (256^3 69 us, 8 rows on 32 lanes 63)
+  // Rows per lane: the smallest instance that covers the line with 16 lanes; from 208 cells on the 16 rows that this
+  // would take leave no registers for the next group's loads in FP64 (256^3 69 us, 8 rows on 32 lanes 63).  Where
+  // there are few lines, a wave's own chain of rows and steps is all that counts, and that is shortest with all 64 lanes
+  // on a line: 200 cells, 1024 lines 7.0 us against 10.4 (2500 lines 10.7 / 10.9, 4096 13.2 / 11.9), 128 cells 6.3
+  // / 8.3 (2000 lines 8.8 / 8.4); up to 64 cells no difference.  Past 256 cells 16 rows are a long chain for longer: 512
+  // cells, 1024 lines 9.2 / 16, 10000 25.8 / 31.8, 20480 43 / 47, but 300 cells, 40000 lines 67 / 59.
 #define TRI(M, LPW)                                                                                                  \
   {                                                                                                                  \
     const long groups = (lines + 64 / LPW - 1) / (64 / LPW);                                                         \
@@ -265,7 +269,11 @@ hipError_t launch_tridiag_x(const GridDev& g, const double* ly, const double* lz
     hipLaunchKernelGGL((k_tridiag_x<T, M, LPW>), grid, dim3(64 * kTriWaves), 0, st, rd, rdd, dx, n, ny, lines, ly, lz, zj, \
                        zk, in, out);                                                                                 \
   }
-  if (n <= 32) TRI(2, 16)
+  const bool few = lines <= (n > 256 ? 20000 : 1600);
+  if (few && n > 64 && n <= 128) TRI(2, 64)
+  else if (few && n > 128 && n <= 256) TRI(4, 64)
+  else if (few && n > 256 && n <= 512) TRI(8, 64)
+  else if (n <= 32) TRI(2, 16)
   else if (n <= 64) TRI(4, 16)
   else if (n <= 80) TRI(5, 16)
   else if (n <= 96) TRI(6, 16)
