@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "lk_device.h"
 
@@ -22,9 +23,10 @@ __device__ __forceinline__ int xcd_tile(int bid, int nb) {
 }
 
 // ------------------------------------------------------------------ momentum
-// A row of 32 lanes owns 60 faces along x, two neighbouring ones per lane (its lanes hold
+// A row of L = 32 lanes owns 60 faces along x, two neighbouring ones per lane (its lanes hold
 // i0 - 2 .. i0 + 61; the first and the last lane are halo); a wave is two rows, a block four waves
-// on eight consecutive rows, marching along z over a chunk of planes.  Every lane loads its pair of
+// on eight consecutive rows, marching along z over a chunk of planes.  (Grids whose faces fill 60 badly have rows of
+// 16 or 8 lanes, 28 or 12 faces, and blocks of 16 or 32 rows: momentum_lanes.)  Every lane loads its pair of
 // each of the six fields (a = U and b, components u, v, w) one plane ahead; the pairs reach the
 // neighbouring rows through LDS, and the rows around the block are loaded by its waves in turn.
 // Neighbours along x come from the neighbouring lane, and what two planes share is carried in
@@ -87,19 +89,19 @@ __device__ __forceinline__ double lane_value(double x, int l) {
 __device__ __forceinline__ D2 fma2(D2 a, D2 b, D2 c) { return D2{fma(a.x, b.x, c.x), fma(a.y, b.y, c.y)}; }
 __device__ __forceinline__ D2 fma2(double a, D2 b, D2 c) { return D2{fma(a, b.x, c.x), fma(a, b.y, c.y)}; }
 
-constexpr int kMomWY = 4;                                 // waves per block
-constexpr int kMomMaxChunk = 13;                          // planes per chunk (at most 62: a lane each for its z metrics)
-constexpr int kMomL = 32;                                 // lanes per row
-constexpr int kMomTX = 2 * kMomL - 4;                     // faces along x per row
-constexpr int kMomTY = kMomWY * 64 / kMomL;               // rows per block
+constexpr int kMomWY = 4;         // waves per block
+constexpr int kMomMaxChunk = 13;  // planes per chunk (at most 62: a lane each for its z metrics)
+// of L lanes per row: faces along x per row, and rows per block
+constexpr int mom_tx(int L) { return 2 * L - 4; }
+constexpr int mom_ty(int L) { return kMomWY * 64 / L; }
 
-template <bool LID, bool ODD>
+template <bool LID, bool ODD, int L>
 __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const double* __restrict__ a,
                                                            const double* __restrict__ b, double* __restrict__ out,
                                                            double rre, double lid_u, double lid_v, int kchunk, int nbx,
                                                            int nby) {
-  constexpr int L = kMomL, TX = kMomTX, TY = kMomTY, NR = TY + 2;  // rows in LDS per field
-  static_assert(L == 32, "a load of the rows around the block holds one below and one above it");
+  constexpr int TX = mom_tx(L), TY = mom_ty(L), NR = TY + 2;  // rows in LDS per field
+  static_assert(L <= 32, "a load of the rows around the block holds one below and one above it");
   constexpr int NH = (6 + kMomWY - 1) / kMomWY;  // of those a wave's share of the six fields
   // plane in work: rows j0 - 1 .. j0 + TY of a (u, v, w) and b (u, v, w); one row nobody reads
   __shared__ D2 sm[(6 * NR + 1) * L];
@@ -152,7 +154,7 @@ __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const do
 #pragma unroll
   for (int t = 0; t < NH; ++t) {
     const int e = wave * NH + t, f = min(e, 5), c = f % 3;
-    const bool use = e < 6;
+    const bool use = e < 6 && sub < 2;
     Halo& h = halo[t];
     h.p = (f < 3 ? a : b) + (c == 0 ? 0 : c == 1 ? nu : nu + nv);
     h.bytes = c == 0 ? nbytes[0] : c == 1 ? nbytes[1] : nbytes[2];
@@ -454,13 +456,14 @@ __global__ void __launch_bounds__(kCorTX* kCorTY) k_correct(GridDev g, const dou
 // HBM bound: 2 F_u + 2 F_p, 514 MB at 200^3, where a separate certificate read v again (193 MB).
 // 200^3: 130 us (4.0 TB/s; the misses of the L2 are 604 MB) against 109 + 55 for the two kernels;
 // 100^3 17 / 14 + 9; 256^3 250 / 226 + 111; 97 x 121 x 65 15 / 13 + 8.
+constexpr int kCdL = 32;  // lanes per row
 template <bool ODD>
 __global__ void __launch_bounds__(64 * kMomWY, 4) k_correct_div(GridDev g, const double* __restrict__ w,
                                                                 const double* __restrict__ phi,
                                                                 double* __restrict__ v, double* __restrict__ p,
                                                                 double* __restrict__ r, double* __restrict__ partials,
                                                                 int kchunk, int nbx, int nby) {
-  constexpr int L = kMomL, TX = kMomTX, TY = kMomTY;
+  constexpr int L = kCdL, TX = mom_tx(L), TY = mom_ty(L);
   constexpr unsigned kGhost = 1u << 31;
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -573,8 +576,8 @@ __global__ void __launch_bounds__(64 * kMomWY, 4) k_correct_div(GridDev g, const
 // Small grids take chunks down to one plane (16^3 6.8 us, three planes 10.6; 64^3 14.1 / 15.9).
 constexpr int kMomSlots = 512;
 
-int momentum_chunk(int nx, int ny, int nz) {
-  const long tiles = (long)blocks_for(nx + 1, kMomTX) * blocks_for(ny + 1, kMomTY);
+int momentum_chunk(int nx, int ny, int nz, int L) {
+  const long tiles = (long)blocks_for(nx + 1, mom_tx(L)) * blocks_for(ny + 1, mom_ty(L));
   int best = 0;
   double least = 0.0;
   for (int most = kMomMaxChunk; most >= 1; --most) {
@@ -586,25 +589,40 @@ int momentum_chunk(int nx, int ny, int nz) {
   return best;
 }
 
+// Lanes per row of the stencil: those whose rows have the fewest lanes over nx + 1 faces, if that is 10 % (16 lanes)
+// or 20 % (8) fewer than with the longer rows, whose halo is less: 32 / 16 / 8 lanes with (y, z) = 256^2: nx = 11 49 / 29 / 21
+// us, 15 49 / 29 / 31, 27 51 / 32 / 45, 31 51 / 51 / 46, 36 52 / 53 / 57; 64^3 15.6 / 14.1 / 16.0, 70 x 200^2 61 / 51 / 55,
+// 128^3 38.9 / 37.6; with as many lanes, 200^3 157 / 165.
+static int momentum_lanes(int nx) {
+  auto lanes = [&](int L) { return (int)blocks_for(nx + 1, mom_tx(L)) * L; };
+  int best = 32;
+  if (lanes(16) * 11 < lanes(32) * 10) best = 16;
+  if (lanes(8) * 12 < lanes(best) * 10) best = 8;
+  return best;
+}
+
 hipError_t launch_momentum(const GridDev& g, const double* a, const double* b, double* out, double rre, bool lid,
                            double lid_u, double lid_v, hipStream_t st) {
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
-  const VelLayout L = vel_layout(nx, ny, nz);
-  if (8 * std::max(L.nu, std::max(L.nv, L.nw)) >= (size_t(1) << 31)) return hipErrorInvalidValue;
-  const int nbx = (int)blocks_for(nx + 1, kMomTX), nby = (int)blocks_for(ny + 1, kMomTY);
-  const int kchunk = momentum_chunk(nx, ny, nz);
+  const VelLayout V = vel_layout(nx, ny, nz);
+  if (8 * std::max(V.nu, std::max(V.nv, V.nw)) >= (size_t(1) << 31)) return hipErrorInvalidValue;
+  const int L = momentum_lanes(nx);
+  const int nbx = (int)blocks_for(nx + 1, mom_tx(L)), nby = (int)blocks_for(ny + 1, mom_ty(L));
+  const int kchunk = momentum_chunk(nx, ny, nz, L);
   const dim3 grid(nbx * nby * blocks_for(nz + 1, kchunk)), block(64 * kMomWY);
-#define LK_MOM(LID, ODD) \
-  hipLaunchKernelGGL((k_momentum<LID, ODD>), grid, block, 0, st, g, a, b, out, rre, lid_u, lid_v, kchunk, nbx, nby)
-  if (lid) {
-    if (nx & 1) LK_MOM(true, true);
-    else LK_MOM(true, false);
-  } else {
-    if (nx & 1) LK_MOM(false, true);
-    else LK_MOM(false, false);
-  }
-#undef LK_MOM
-  return hipGetLastError();
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, g, a, b, out, rre, lid_u, lid_v, kchunk, nbx, nby);
+    return hipGetLastError();
+  };
+  auto rows = [&](auto LID, auto ODD) {
+    if (L == 8) return run(k_momentum<LID.value, ODD.value, 8>);
+    if (L == 16) return run(k_momentum<LID.value, ODD.value, 16>);
+    return run(k_momentum<LID.value, ODD.value, 32>);
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  if (lid) return nx & 1 ? rows(yes, yes) : rows(yes, no);
+  return nx & 1 ? rows(no, yes) : rows(no, no);
 }
 
 int divergence_parts(int nx, int ny, int nz) {
@@ -636,19 +654,19 @@ hipError_t launch_correct(const GridDev& g, const double* w, const double* phi, 
 // 131 us, 8 130 us, 16 and 25 142 us; 256^3 253 / 251 / 259 / 285).  Grids that would not fill the chip
 // with chunks of eight (four blocks per CU, 2 kMomSlots) take shorter ones.
 static int correct_chunk(int nx, int ny, int nz) {
-  const long tiles = (long)blocks_for(nx + 1, kMomTX) * blocks_for(ny + 1, kMomTY);
+  const long tiles = (long)blocks_for(nx + 1, mom_tx(kCdL)) * blocks_for(ny + 1, mom_ty(kCdL));
   const long most = std::max<long>(1, 2 * kMomSlots / tiles);
   return (int)std::min<long>(kCdMaxChunk, std::max<long>(1, blocks_for(nz, (unsigned)most)));
 }
 
 int correct_div_parts(int nx, int ny, int nz) {
-  return (int)(blocks_for(nx + 1, kMomTX) * blocks_for(ny + 1, kMomTY) * blocks_for(nz, correct_chunk(nx, ny, nz)));
+  return (int)(blocks_for(nx + 1, mom_tx(kCdL)) * blocks_for(ny + 1, mom_ty(kCdL)) * blocks_for(nz, correct_chunk(nx, ny, nz)));
 }
 
 hipError_t launch_correct_div(const GridDev& g, const double* w, const double* phi, double* v, double* p, double* r,
                               double* partials, hipStream_t st) {
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
-  const int nbx = (int)blocks_for(nx + 1, kMomTX), nby = (int)blocks_for(ny + 1, kMomTY);
+  const int nbx = (int)blocks_for(nx + 1, mom_tx(kCdL)), nby = (int)blocks_for(ny + 1, mom_ty(kCdL));
   const dim3 grid((unsigned)correct_div_parts(nx, ny, nz)), block(64 * kMomWY);
   const int kchunk = correct_chunk(nx, ny, nz);
   if (nx & 1)
