@@ -192,10 +192,9 @@ int upload_grid(lc_ctx* c) {
   }
   HIPCHK(c, hipMemcpyAsync(c->metric, host.data(), total * sizeof(double), hipMemcpyHostToDevice, c->stream));
 
-  // tensor-product factorization of each axis (full matrices, plus the parity-sorted
-  // half matrices of mirror-symmetric axes, in both precisions)
+  // tensor-product factorization of each axis, in both precisions
   size_t mbytes = 0;
-  for (int a = 0; a < 3; ++a) mbytes += mode_bytes(n[a]);
+  for (int a = 0; a < 3; ++a) mbytes += mode_bytes(n[a], true);
   if (!c->modes_mem) HIPCHK(c, ctx_alloc(c, &c->modes_mem, mbytes));
   Stager st(mbytes, c->modes_mem);
   for (int a = 0; a < 3; ++a) {
@@ -213,7 +212,7 @@ int upload_grid(lc_ctx* c) {
     ModeHost H;
     if (!compute_modes(m, kd, ko, AH.d, sym, H))
       return fail(c, LC_EINVAL, "tridiagonal eigen-solver did not converge on axis %d", a);
-    place_modes(H, c->modes[a], st);
+    place_modes(H, c->modes[a], st, true);
     // ascending; the Neumann null mode is the largest (~0), last of the even modes when folded
     c->zero_mode[a] = sym ? (m + 1) / 2 - 1 : m - 1;
   }
@@ -324,7 +323,7 @@ size_t metric_doubles(int nx, int ny, int nz) { return 4 * ((size_t)nx + ny + nz
 
 size_t viscous_bytes(int nx, int ny, int nz) {
   size_t b = 0;
-  for (int n : {nx, ny, nz}) b += mode_bytes(n) + mode_bytes(n + 1);
+  for (int n : {nx, ny, nz}) b += mode_bytes(n, false) + mode_bytes(n + 1, false);
   return b;
 }
 
@@ -362,7 +361,7 @@ bool carve_all(lc_ctx* c) {
   if (!ok || !(c->arena || c->dry)) return ok;
   const int nx = c->nx, ny = c->ny, nz = c->nz;
   size_t mbytes = 0;
-  for (int n : {nx, ny, nz}) mbytes += mode_bytes(n);
+  for (int n : {nx, ny, nz}) mbytes += mode_bytes(n, true);
   return dalloc(c, &c->metric, metric_doubles(nx, ny, nz)) == hipSuccess &&
          ctx_alloc(c, &c->modes_mem, mbytes) == hipSuccess &&
          ctx_alloc(c, &c->stokes_mem, viscous_bytes(nx, ny, nz)) == hipSuccess &&

@@ -1,6 +1,7 @@
 // Tensor-product factors of 1D operators: host eigen-decomposition and device placement.
 #include "lk_modes.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -21,14 +22,19 @@ bool compute_modes(int n, const std::vector<double>& kd, const std::vector<doubl
   return true;
 }
 
-size_t mode_bytes(int n) {
-  const size_t nn = (size_t)n * n;
-  const int he = (n + 1) / 2;
-  return 2 * n * sizeof(double) + 4 * nn * sizeof(double) + 4 * nn * sizeof(float) +
-         3 * nn * (sizeof(double) + sizeof(float)) +
-         4 * (mf_pack_size(he, 2) * sizeof(double) + mf_pack_size(he, 4) * sizeof(float)) +
-         (he <= kMfMaxHalf ? 2 * (mx_full_size(n) * sizeof(double) + m4_pack_size(he) * sizeof(float)) : 0) +
-         64 * 16;  // alignment padding (at most 15 bytes for each of an operator's <= 36 arrays)
+size_t mode_bytes(int n, bool f32) {
+  const size_t nn = (size_t)n * n, he = (n + 1) / 2, ho = n / 2;
+  const size_t each = sizeof(double) + (f32 ? sizeof(float) : 0);
+  size_t sym, full;  // the arrays of a mirror-symmetric operator and of any other
+  if (he <= (size_t)kMfMaxHalf) {
+    sym = 2 * mx_pack_size(he) * sizeof(double) + (mx_along_x(n) ? 0 : 4 * mf_pack_size(he, 2) * sizeof(double));
+    if (f32) sym += (2 * m4_pack_size(he) + 4 * mf_pack_size(he, 4)) * sizeof(float);
+    full = 2 * mx_full_size(n) * sizeof(double) + (f32 ? 4 * nn * sizeof(float) : 0);
+  } else {
+    sym = (4 * he * he + 2 * ho * ho + 2 * he * ho) * each;
+    full = 4 * nn * each;
+  }
+  return n * sizeof(double) + std::max(sym, full) + 17 * 16;  // the eigenvalues; padding of at most 17 arrays
 }
 
 void* Stager::put(const void* src, size_t bytes) {
@@ -51,39 +57,47 @@ float* Stager::put_f(const std::vector<double>& v) {
   return (float*)put(f.data(), f.size() * sizeof(float));
 }
 
-void place_modes(const ModeHost& H, AxisModes& M, Stager& st) {
-  const int n = H.n;
-  const size_t nn = (size_t)n * n;
-  std::vector<double> FT(nn), BkT(nn);
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j) {
-      FT[(size_t)j * n + i] = H.Wf[(size_t)i * n + j];
-      BkT[(size_t)j * n + i] = H.S[(size_t)i * n + j];
-    }
-  M.lam = st.put_d(H.lam);
-  M.F = st.put_d(H.Wf);
-  M.Bk = st.put_d(H.S);
-  M.FT = st.put_d(FT);
-  M.BkT = st.put_d(BkT);
-  M.F32 = st.put_f(H.Wf);
-  M.Bk32 = st.put_f(H.S);
-  M.FT32 = st.put_f(FT);
-  M.BkT32 = st.put_f(BkT);
-  const int he = (n + 1) / 2, ho = n / 2;
+void place_modes(const ModeHost& H, AxisModes& M, Stager& st, bool f32) {
+  const int n = H.n, he = (n + 1) / 2, ho = n / 2;
+  const bool cores = he <= kMfMaxHalf;
+  M = AxisModes{};
   M.sym = H.sym;
-  M.mf = false;
-  M.full64 = !H.sym && he <= kMfMaxHalf;
+  M.mf = H.sym && cores;
+  M.full64 = !H.sym && cores;
   M.he = he;
   M.ho = ho;
-  if (M.full64)
-    for (int b = 0; b < 2; ++b) {
-      std::vector<double> X(mx_full_size(n), 0.0);
-      const std::vector<double>& A = b ? H.S : H.Wf;
-      for (int o = 0; o < n; ++o)
-        for (int k = 0; k < n; ++k) X[mx_pack_index(o < he ? o : o - he, k, he, o >= he)] = A[(size_t)o * n + k];
-      M.x64[b] = st.put_d(X);
+  if (!H.sym) {
+    M.lam = st.put_d(H.lam);
+    if (M.full64)
+      for (int b = 0; b < 2; ++b) {
+        std::vector<double> X(mx_full_size(n), 0.0);
+        const std::vector<double>& A = b ? H.S : H.Wf;
+        for (int o = 0; o < n; ++o)
+          for (int k = 0; k < n; ++k) X[mx_pack_index(o < he ? o : o - he, k, he, o >= he)] = A[(size_t)o * n + k];
+        M.x64[b] = st.put_d(X);
+      }
+    if (M.full64 && !f32) return;
+    const size_t nn = (size_t)n * n;
+    std::vector<double> FT(nn), BkT(nn);
+    for (int i = 0; i < n; ++i)
+      for (int j = 0; j < n; ++j) {
+        FT[(size_t)j * n + i] = H.Wf[(size_t)i * n + j];
+        BkT[(size_t)j * n + i] = H.S[(size_t)i * n + j];
+      }
+    if (!M.full64) {
+      M.F = st.put_d(H.Wf);
+      M.Bk = st.put_d(H.S);
+      M.FT = st.put_d(FT);
+      M.BkT = st.put_d(BkT);
     }
-  if (!H.sym) return;
+    if (f32) {
+      M.F32 = st.put_f(H.Wf);
+      M.Bk32 = st.put_f(H.S);
+      M.FT32 = st.put_f(FT);
+      M.BkT32 = st.put_f(BkT);
+    }
+    return;
+  }
   // parity-sorted modes: the he even ones (ascending), then the odd ones
   const double r2 = std::sqrt(0.5);
   const bool mid = (n % 2) == 1;
@@ -106,54 +120,56 @@ void place_modes(const ModeHost& H, AxisModes& M, Stager& st) {
       h[1][(size_t)k * ho + p] = Sh_o[(size_t)p * ho + k] * m[p] * r2;
       h[3][(size_t)p * ho + k] = Sh_o[(size_t)p * ho + k] * r2;  // rows p < ho; the middle row stays 0
     }
-  h[4].resize((size_t)he * he);
-  h[5].resize((size_t)ho * ho);
-  h[6].resize((size_t)he * he);
-  h[7].resize((size_t)ho * he);
-  for (int r = 0; r < he; ++r)
-    for (int i = 0; i < he; ++i) {
-      h[4][(size_t)i * he + r] = h[0][(size_t)r * he + i];
-      h[6][(size_t)r * he + i] = h[2][(size_t)i * he + r];
-    }
-  for (int r = 0; r < ho; ++r)
-    for (int i = 0; i < ho; ++i) h[5][(size_t)i * ho + r] = h[1][(size_t)r * ho + i];
-  for (int i = 0; i < he; ++i)
-    for (int r = 0; r < ho; ++r) h[7][(size_t)r * he + i] = h[3][(size_t)i * ho + r];
   M.lam_s = st.put_d(lam_s);
-  for (int q = 0; q < 8; ++q) M.h64[q] = st.put_d(h[q]);
-  for (int q = 0; q < 8; ++q) M.h32[q] = st.put_f(h[q]);
+  if (!M.mf) {
+    h[4].resize((size_t)he * he);
+    h[5].resize((size_t)ho * ho);
+    h[6].resize((size_t)he * he);
+    h[7].resize((size_t)ho * he);
+    for (int r = 0; r < he; ++r)
+      for (int i = 0; i < he; ++i) {
+        h[4][(size_t)i * he + r] = h[0][(size_t)r * he + i];
+        h[6][(size_t)r * he + i] = h[2][(size_t)i * he + r];
+      }
+    for (int r = 0; r < ho; ++r)
+      for (int i = 0; i < ho; ++i) h[5][(size_t)i * ho + r] = h[1][(size_t)r * ho + i];
+    for (int i = 0; i < he; ++i)
+      for (int r = 0; r < ho; ++r) h[7][(size_t)r * he + i] = h[3][(size_t)i * ho + r];
+    for (int q = 0; q < 8; ++q) M.h64[q] = st.put_d(h[q]);
+    for (int q = 0; q < 8 && f32; ++q) M.h32[q] = st.put_f(h[q]);
+    return;
+  }
   // fragment packs for the matrix-core transforms: fragment (kq, t, l) =
   // Mat[o = 16 t + l % 16][k = 4 kq + l / 16], zero outside the matrix, laid out by
   // mf_pack_index (two FP64 / four FP32 fragments per 16-byte lane load)
-  M.mf = he <= kMfMaxHalf;
-  if (!M.mf) return;
   const int RT = (he + 15) / 16, KQ = mf_steps(he);
   const int rows[4] = {he, ho, he, he}, cols[4] = {he, ho, he, ho};
-  for (int q = 0; q < 4; ++q) {
-    std::vector<double> P2(mf_pack_size(he, 2), 0.0), P4(mf_pack_size(he, 4), 0.0);
+  const bool p64 = !mx_along_x(n);
+  for (int q = 0; q < 4 && (p64 || f32); ++q) {
+    std::vector<double> P2(p64 ? mf_pack_size(he, 2) : 0, 0.0), P4(f32 ? mf_pack_size(he, 4) : 0, 0.0);
     for (int kq = 0; kq < KQ; ++kq)
       for (int t = 0; t < RT; ++t)
         for (int l = 0; l < 64; ++l) {
           const int o = 16 * t + l % 16, k = 4 * kq + l / 16;
           if (o < rows[q] && k < cols[q]) {
             const double v = h[q][(size_t)o * cols[q] + k];
-            P2[mf_pack_index(kq, t, l, RT, 2)] = v;
-            P4[mf_pack_index(kq, t, l, RT, 4)] = v;
+            if (p64) P2[mf_pack_index(kq, t, l, RT, 2)] = v;
+            if (f32) P4[mf_pack_index(kq, t, l, RT, 4)] = v;
           }
         }
-    if (!mx_along_x(n)) M.p64[q] = st.put_d(P2);
-    M.p32[q] = st.put_f(P4);
+    if (p64) M.p64[q] = st.put_d(P2);
+    if (f32) M.p32[q] = st.put_f(P4);
   }
   for (int b = 0; b < 2; ++b) {
-    std::vector<double> X(mx_pack_size(he), 0.0), X4(m4_pack_size(he), 0.0);
+    std::vector<double> X(mx_pack_size(he), 0.0), X4(f32 ? m4_pack_size(he) : 0, 0.0);
     for (int q = 2 * b; q < 2 * b + 2; ++q)
       for (int o = 0; o < rows[q]; ++o)
         for (int k = 0; k < cols[q]; ++k) {
           X[mx_pack_index(o, k, he, q % 2)] = h[q][(size_t)o * cols[q] + k];
-          X4[m4_pack_index(o, k, he, q % 2)] = h[q][(size_t)o * cols[q] + k];
+          if (f32) X4[m4_pack_index(o, k, he, q % 2)] = h[q][(size_t)o * cols[q] + k];
         }
     M.x64[b] = st.put_d(X);
-    M.x32[b] = st.put_f(X4);
+    if (f32) M.x32[b] = st.put_f(X4);
   }
 }
 

@@ -22,8 +22,8 @@ struct ModeHost {
 bool compute_modes(int n, const std::vector<double>& kd, const std::vector<double>& ko, const std::vector<double>& m,
                    bool sym, ModeHost& H);
 
-// Device bytes that place_modes needs for one operator of n points (alignment included).
-size_t mode_bytes(int n);
+// Device bytes that place_modes needs for any operator of n points (alignment included).
+size_t mode_bytes(int n, bool f32);
 
 // Writes arrays into a host staging buffer whose image is later copied to the device
 // allocation `dev` in one transfer; device pointers are handed out as the arrays are
@@ -39,10 +39,10 @@ struct Stager {
   float* put_f(const std::vector<double>& v);  // rounded to float32
 };
 
-// Places the factors of one operator: the full matrices F = S^T M, Bk = S and their
-// transposes (float64 and float32), and for a mirror-symmetric operator the
-// parity-sorted eigenvalues, the half-size matrices and (half length <= kMfMaxHalf) the
-// matrix-core fragment packs.
-void place_modes(const ModeHost& H, AxisModes& M, Stager& st);
+// Places the factors of one operator that its transforms (lk_lines.h) use, in float64 and with f32 in float32 too.
+// Half length up to kMfMaxHalf: the matrix-core packs, of the parity-sorted half-size matrices of a
+// mirror-symmetric operator, else (float64) of the full ones F = S^T M and Bk = S.  Longer ones, and the float32
+// factors of an operator without the symmetry: the matrices themselves and their transposes.
+void place_modes(const ModeHost& H, AxisModes& M, Stager& st, bool f32);
 
 }  // namespace lk

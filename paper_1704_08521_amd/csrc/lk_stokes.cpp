@@ -43,8 +43,8 @@ int build_viscous_factors(lc_ctx* c) {
     dirichlet_face_operator(n[a], AH.d.data(), AH.dd.data(), kd, ko, m);
     if (!compute_modes(n[a] + 1, kd, ko, m, sym, Hf))
       return fail(c, LC_EINVAL, "viscous factors: eigen-solver did not converge on axis %d (faces)", a);
-    place_modes(Hc, c->vcell[a], st);
-    place_modes(Hf, c->vface[a], st);
+    place_modes(Hc, c->vcell[a], st, false);
+    place_modes(Hf, c->vface[a], st, false);
     auto order = [](const ModeHost& H) {
       if (!H.sym) return H.lam;
       std::vector<double> l(H.lam_e);
