@@ -61,7 +61,7 @@ struct AxisModes {
 }  // namespace lk
 
 namespace lk {
-constexpr int kSumSlots = 3;
+constexpr int kSumSlots = 2;
 }  // namespace lk
 
 struct lc_ctx {
