@@ -245,6 +245,9 @@ hipError_t launch_gs_update(const double* V, long ld, int nv, const double* h, d
                             hipStream_t st);
 // The same update for 1 to kGsFused vectors with h2[i] = V_i . w of the new w; gs_update_dot_parts() partial sums of
 // the norm; dots holds kGsBlocks * kGsVectors doubles.
+// (Up to 48: the vector kernels of a run of 48 vectors with 0, 32, 40 and 48 of them fused take 7.4, 7.2, 6.9 and 6.8 ms at
+// 48^3, 12.6, 11.8, 11.1 and 10.6 at 64^3, 43.5, 40.0, 37.6 and 35.0 at 100^3; at 32^3 4.6, 4.6, 4.5 and 4.4, at 16^3 no
+// gain.  More vectors than 48 would not stay in registers: their scalar addresses spill from 40 on already.)
 constexpr int kGsFused = 48;
 int gs_update_dot_parts(size_t n, int nv);  // at most kHostParts
 hipError_t launch_gs_update_dot(const double* V, long ld, int nv, const double* h, double* w, size_t n,
