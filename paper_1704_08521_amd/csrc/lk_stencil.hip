@@ -589,15 +589,15 @@ int momentum_chunk(int nx, int ny, int nz, int L) {
   return best;
 }
 
-// Lanes per row of the stencil: those whose rows have the fewest lanes over nx + 1 faces, if that is 10 % (16 lanes)
+// Lanes per row of the stencil: those whose rows have the fewest lanes over nx + 1 faces, if that is 15 % (16 lanes)
 // or 20 % (8) fewer than with the longer rows, whose halo is less: 32 / 16 / 8 lanes with (y, z) = 256^2: nx = 11 49 / 29 / 21
 // us, 15 49 / 29 / 31, 27 51 / 32 / 45, 31 51 / 51 / 46, 36 52 / 53 / 57; 64^3 15.6 / 14.1 / 16.0, 70 x 200^2 61 / 51 / 55,
-// 128^3 38.9 / 37.6; with as many lanes, 200^3 157 / 165.
+// 128^3 38.9 / 37.6; with nearly as many lanes, 240 x 200^2 184 / 187, and as many, 200^3 157 / 165.
 static int momentum_lanes(int nx) {
   auto lanes = [&](int L) { return (int)blocks_for(nx + 1, mom_tx(L)) * L; };
   int best = 32;
-  if (lanes(16) * 11 < lanes(32) * 10) best = 16;
-  if (lanes(8) * 12 < lanes(best) * 10) best = 8;
+  if (lanes(16) * 115 < lanes(32) * 100) best = 16;
+  if (lanes(8) * 120 < lanes(best) * 100) best = 8;
   return best;
 }
 
