@@ -95,7 +95,7 @@ constexpr int kMomMaxChunk = 13;  // planes per chunk (at most 62: a lane each f
 constexpr int mom_tx(int L) { return 2 * L - 4; }
 constexpr int mom_ty(int L) { return kMomWY * 64 / L; }
 
-template <bool LID, bool ODD, int L>
+template <bool LID, bool ODD, int L, bool WIDE = false>
 __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const double* __restrict__ a,
                                                            const double* __restrict__ b, double* __restrict__ out,
                                                            double rre, double lid_u, double lid_v, int kchunk, int nbx,
@@ -211,8 +211,13 @@ __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const do
   D2 ou[2], ov[2], ot[2], ow[2];
   D2 tuz = 0.0, tvz = 0.0, twz = 0.0, su = 0.0, sv = 0.0, sw = 0.0;
   // (the advecting field is scaled by Re, and by 1/2 for the residual, as it is read: the fluxes are
-  // then Re times the momentum's and the sums are divided by Re as they are stored)
-  const double sa = LID ? 0.5 / rre : 1.0 / rre;
+  // then Re times the momentum's and the sums are divided by Re as they are stored.  WIDE scales the viscous parts
+  // instead, for Reynolds numbers whose products would leave the range of the type.)
+  const double sa = (LID ? 0.5 : 1.0) / (WIDE ? 1.0 : rre), so = WIDE ? 1.0 : rre;
+  auto flux = [&](auto m, D2 db, D2 e) {  // viscous part m db less the convective part e
+    if constexpr (WIDE) m *= rre;
+    return fma2(m, db, -e);
+  };
   const unsigned ofst = offset(1, j + 1);
 #pragma unroll
   for (int f = 0; f < 2; ++f) {
@@ -282,10 +287,10 @@ __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const do
       const D2 aw = fma2(thx, O[2] - aw0, aw0), bw = fma2(thx, dbw, bw0);
       const D2 au = fma2(thz, O[0] - ou[0], ou[0]), bu = fma2(thz, dbu, ou[1]);
       const D2 e = fma2(aw, bu, bw * au);
-      const D2 tz = fma2(rddz, dbu, -e), tx = fma2(rddx, dbw, -e);
+      const D2 tz = flux(rddz, dbu, e), tx = flux(rddx, dbw, e);
       nsw = (above(tx) - tx) * rdx;
       const D2 val = fma2(rdzm, tz - tuz, su);
-      res[0] = D2{u0 ? rre * val.x : 0.0, u1 ? rre * val.y : 0.0};
+      res[0] = D2{u0 ? so * val.x : 0.0, u1 ? so * val.y : 0.0};
       tuz = tz;
     }
     {  // edges (y_j, z_k) and (y_{j+1}, z_k): z flux of v, y flux of w
@@ -294,10 +299,10 @@ __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const do
       const D2 aw = fma2(thy0, O[2] - aw0, aw0), bw = fma2(thy0, dbw, bw0);
       const D2 av = fma2(thz, O[1] - ov[0], ov[0]), bv = fma2(thz, dbv, ov[1]);
       const D2 e = fma2(aw, bv, bw * av);
-      const D2 tz = fma2(rddz, dbv, -e);
-      nsw = fma2(-rdy1, fma2(rddy0, dbw, -e), nsw);
+      const D2 tz = flux(rddz, dbv, e);
+      nsw = fma2(-rdy1, flux(rddy0, dbw, e), nsw);
       const D2 val = fma2(rdzm, tz - tvz, sv);
-      res[1] = j > 0 && j < ny ? rre * val : D2{0.0, 0.0};
+      res[1] = j > 0 && j < ny ? so * val : D2{0.0, 0.0};
       tvz = tz;
     }
     {
@@ -307,21 +312,21 @@ __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const do
       const D2 aw = fma2(thy1, aw1 - O[2], O[2]), bw = fma2(thy1, dbw, O[5]);
       const D2 av = fma2(thz, av1 - ot[0], ot[0]), bv = fma2(thz, bv1 - ot[1], ot[1]);
       const D2 e = fma2(aw, bv, bw * av);
-      nsw = fma2(rdy1, fma2(rddy1, dbw, -e), nsw);
+      nsw = fma2(rdy1, flux(rddy1, dbw, e), nsw);
       ot[0] = av1;
       ot[1] = bv1;
     }
     {  // centre of cell k - 1: z flux of w
       const D2 aw = ow[0] + O[2], bw = ow[1] + O[5];
-      const D2 tz = fma2(rdzm, O[5] - ow[1], -((0.5 * aw) * bw));
-      res[2] = k > 1 && k <= nz ? rre * fma2(rddzm, tz - twz, sw) : D2{0.0, 0.0};
+      const D2 tz = flux(rdzm, O[5] - ow[1], (0.5 * aw) * bw);
+      res[2] = k > 1 && k <= nz ? so * fma2(rddzm, tz - twz, sw) : D2{0.0, 0.0};
       twz = tz;
       sw = nsw;
     }
     {  // centres along x
       const D2 au1 = above(O[0]), bu1 = above(O[3]);
       const D2 au = O[0] + au1, bu = O[3] + bu1;
-      const D2 t = fma2(rdx, bu1 - O[3], -((0.5 * au) * bu));
+      const D2 t = flux(rdx, bu1 - O[3], (0.5 * au) * bu);
       su = (t - below(t)) * rddx;
     }
     {  // edges (x_i, y_j) and (x_i, y_{j+1}): y flux of u, x flux of v
@@ -331,8 +336,8 @@ __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const do
       const D2 av = fma2(thx, O[1] - av0, av0), bv = fma2(thx, dbv, bv0);
       const D2 au = fma2(thy0, O[0] - au0, au0), bu = fma2(thy0, dbu, bu0);
       const D2 e = fma2(av, bu, bv * au);
-      const D2 tx = fma2(rddx, dbv, -e);
-      su = fma2(-rdy1, fma2(rddy0, dbu, -e), su);
+      const D2 tx = flux(rddx, dbv, e);
+      su = fma2(-rdy1, flux(rddy0, dbu, e), su);
       sv = (above(tx) - tx) * rdx;
     }
     {
@@ -342,12 +347,12 @@ __global__ void __launch_bounds__(64 * kMomWY, 2) k_momentum(GridDev g, const do
       const D2 av = fma2(thx, ot[0] - av0, av0), bv = fma2(thx, ot[1] - bv0, bv0);
       const D2 au = fma2(thy1, au1 - O[0], O[0]), bu = fma2(thy1, dbu, O[3]);
       const D2 e = fma2(av, bu, bv * au);
-      su = fma2(rdy1, fma2(rddy1, dbu, -e), su);
+      su = fma2(rdy1, flux(rddy1, dbu, e), su);
     }
     {  // centres along y
       const D2 avm = row_at(1, 0), bvm = row_at(4, 0);
-      const D2 tm = fma2(rdy0, O[4] - bvm, -((0.5 * (avm + O[1])) * (bvm + O[4])));
-      const D2 tp = fma2(rdy1, ot[1] - O[4], -((0.5 * (O[1] + ot[0])) * (O[4] + ot[1])));
+      const D2 tm = flux(rdy0, O[4] - bvm, (0.5 * (avm + O[1])) * (bvm + O[4]));
+      const D2 tp = flux(rdy1, ot[1] - O[4], (0.5 * (O[1] + ot[0])) * (O[4] + ot[1]));
       sv = fma2(rddy0, tp - tm, sv);
     }
 #pragma unroll
@@ -606,7 +611,9 @@ hipError_t launch_momentum(const GridDev& g, const double* a, const double* b, d
   const int nx = g.x.n, ny = g.y.n, nz = g.z.n;
   const VelLayout V = vel_layout(nx, ny, nz);
   if (8 * std::max(V.nu, std::max(V.nv, V.nw)) >= (size_t(1) << 31)) return hipErrorInvalidValue;
-  const int L = momentum_lanes(nx);
+  // far from any flow, but accepted: nothing may overflow that the formula itself does not let overflow
+  const bool wide = !(rre > 0x1p-256 && rre < 0x1p256);
+  const int L = wide ? 32 : momentum_lanes(nx);
   const int nbx = (int)blocks_for(nx + 1, mom_tx(L)), nby = (int)blocks_for(ny + 1, mom_ty(L));
   const int kchunk = momentum_chunk(nx, ny, nz, L);
   const dim3 grid(nbx * nby * blocks_for(nz + 1, kchunk)), block(64 * kMomWY);
@@ -615,6 +622,7 @@ hipError_t launch_momentum(const GridDev& g, const double* a, const double* b, d
     return hipGetLastError();
   };
   auto rows = [&](auto LID, auto ODD) {
+    if (wide) return run(k_momentum<LID.value, ODD.value, 32, true>);
     if (L == 8) return run(k_momentum<LID.value, ODD.value, 8>);
     if (L == 16) return run(k_momentum<LID.value, ODD.value, 16>);
     return run(k_momentum<LID.value, ODD.value, 32>);
