@@ -687,13 +687,15 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   };
   // |D w| decides whether there is a pass at all, and v and p stay as they are if it is not finite.  Without a
   // guess it is read while the pass's first transform runs, which needs D w but not its norm and writes
-  // nothing of the caller's, so that the GPU does not wait for the host here.
+  // nothing of the caller's, so that the GPU does not wait for the host here.  (Axes without the matrix cores have long
+  // transforms: 300 points, 256 columns 57 us, which an input without divergence would pay for nothing.)
   double n0 = 0.0;
   auto read_norm = [&]() -> int {
     n0 = std::sqrt(sum_of(c, 0));
     return std::isfinite(n0) ? LC_OK : fail(c, LC_EINVAL, "non-finite input");
   };
-  const bool ahead = precision != LC_LEARNED;
+  const AxisModes& first = c->modes[uses_tridiag(c) ? 1 : 0];
+  const bool ahead = precision != LC_LEARNED && (first.mf || (first.full64 && precision == LC_FP64));
   if ((rc = div_queue(c, w, c->r, 0, ahead))) return rc;
   if (ahead) {
     constexpr int kNoPass = 2;
