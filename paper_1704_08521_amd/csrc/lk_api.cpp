@@ -231,7 +231,7 @@ static bool uses_tridiag(const lc_ctx* c) { return c->poisson_method == LC_POISS
 // solve per x-line, transforms back with S.  TPF: transforms along x, y and z and a division by
 // the sums of the axis eigenvalues (constant mode set to zero).
 template <typename T, typename F>
-int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2, const std::function<int()>& after_first) {
+int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2, const SolveHook& hook) {
   const int nx = c->nx, ny = c->ny, nz = c->nz;
   const AxisModes &X = c->modes[0], &Y = c->modes[1], &Z = c->modes[2];
   auto lams = [](const AxisModes& M) { return M.sym ? M.lam_s : M.lam; };
@@ -241,9 +241,9 @@ int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2, const std::function<in
   const LineScale none;
   if (uses_tridiag(c)) {
     KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, r, t1, none, s));
-    if (after_first)
-      if (const int rc = after_first()) return rc;
+    if (const int rc = hook(1)) return rc;
     KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t1, t2, none, s));
+    if (const int rc = hook(2)) return rc;
     KLAUNCH(c, LC_K_TRIDIAG,
             launch_tridiag_x<T>(c->g, lams(Y), lams(Z), c->zero_mode[1], c->zero_mode[2], t2, t1, s));
     KLAUNCH(c, LC_K_TP_Z, left_backward<T>(Z, nz, cz, t1, t2, none, s));
@@ -253,9 +253,9 @@ int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2, const std::function<in
   if constexpr (sizeof(F) == sizeof(T)) {
     const LineScale sc{lams(Z), lams(Y), lams(X), nx, c->zero_mode[2], c->zero_mode[1], c->zero_mode[0]};
     KLAUNCH(c, LC_K_TP_X, right_forward<T>(X, nx, ny * nz, r, t1, s));
-    if (after_first)
-      if (const int rc = after_first()) return rc;
+    if (const int rc = hook(1)) return rc;
     KLAUNCH(c, LC_K_TP_Y, left_forward<T>(Y, ny, cy, t1, t2, none, s));
+    if (const int rc = hook(2)) return rc;
     KLAUNCH(c, LC_K_TP_Z, left_forward<T>(Z, nz, cz, t2, t1, sc, s));
     KLAUNCH(c, LC_K_TP_Z, left_backward<T>(Z, nz, cz, t1, t2, sc, s));
     KLAUNCH(c, LC_K_TP_Y, left_backward<T>(Y, ny, cy, t2, t1, none, s));
@@ -265,12 +265,12 @@ int tp_solve(lc_ctx* c, const F* r, F* phi, T* t1, T* t2, const std::function<in
   return fail(c, LC_ESTATE, "FP64 field in an FP32 solve along x (internal)");
 }
 
-int poisson(lc_ctx* c, const double* r, double* phi, int precision, const std::function<int()>& after_first) {
-  if (precision == LC_FP64) return tp_solve<double>(c, r, phi, c->t1, c->t2, after_first);
+int poisson(lc_ctx* c, const double* r, double* phi, int precision, const SolveHook& hook) {
+  if (precision == LC_FP64) return tp_solve<double>(c, r, phi, c->t1, c->t2, hook);
   // FP32: where the first and the last transform read and write FP64 fields there are no casts
-  if (uses_tridiag(c) && c->modes[1].mf) return tp_solve<float>(c, r, phi, c->t1_32, c->t2_32, after_first);
+  if (uses_tridiag(c) && c->modes[1].mf) return tp_solve<float>(c, r, phi, c->t1_32, c->t2_32, hook);
   KLAUNCH(c, LC_K_CAST, launch_d2f(c->ncell, r, c->r32, c->stream));
-  int rc = tp_solve<float>(c, c->r32, c->r32, c->t1_32, c->t2_32, after_first);
+  int rc = tp_solve<float>(c, c->r32, c->r32, c->t1_32, c->t2_32, hook);
   if (rc) return rc;
   KLAUNCH(c, LC_K_CAST, launch_f2d(c->ncell, c->r32, phi, false, c->stream));
   return LC_OK;
@@ -673,9 +673,9 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   // keep D v from the certificate.
   const int pass_precision = precision == LC_LEARNED ? LC_MIXED : precision;
   const bool keep_r = pass_precision != LC_FP64;
-  auto pass = [&](bool accumulate, const std::function<int()>& after_first = {}) -> int {
-    int e = poisson(c, c->r, c->phi, pass_precision, after_first);
-    if (e) return e;
+  auto pass = [&](bool accumulate, const SolveHook& hook = {}) -> int {
+    int e = poisson(c, c->r, c->phi, pass_precision, hook);
+    if (e || (e = hook(3))) return e;
     if (!accumulate) {
       const int np = correct_div_parts(c->nx, c->ny, c->nz);
       KLAUNCH(c, LC_K_CORRECT,
@@ -686,9 +686,11 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
     return div_queue(c, v, keep_r ? c->r : nullptr, 1);
   };
   // |D w| decides whether there is a pass at all, and v and p stay as they are if it is not finite.  Without a
-  // guess it is read while the pass's first transform runs, which needs D w but not its norm and writes
-  // nothing of the caller's, so that the GPU does not wait for the host here.  (Axes without the matrix cores have long
-  // transforms: 300 points, 256 columns 57 us, which an input without divergence would pay for nothing.)
+  // guess it is read while the pass's solve is under way, which needs D w but not its norm and writes nothing of the
+  // caller's; the GPU must not run dry before the host has queued more, and an input without divergence
+  // pays for what is queued: the whole solve up to 64^3 (read after the first transform, 16^3 to 64^3 lose
+  // 5 to 8 us of 58 to 70), two transforms up to 150^3, one beyond.  (Axes without the matrix cores have long
+  // transforms, 300 points, 256 columns 57 us: none.)
   double n0 = 0.0;
   auto read_norm = [&]() -> int {
     n0 = std::sqrt(sum_of(c, 0));
@@ -699,14 +701,14 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   if ((rc = div_queue(c, w, c->r, 0, ahead))) return rc;
   if (ahead) {
     constexpr int kNoPass = 2;
-    rc = pass(false, [&]() -> int {
+    rc = pass(false, {c->ncell <= 300000 ? 3 : c->ncell <= 3500000 ? 2 : 1, [&]() -> int {
       if (const int e = watched_wait(c, 0)) return e;
       if (const int e = read_norm()) {
         HIPCHK(c, hipStreamSynchronize(c->stream));
         return e;
       }
       return n0 == 0.0 ? kNoPass : LC_OK;
-    });
+    }});
     if (rc == LC_OK) rc = sums_wait(c);
     if (rc && rc != kNoPass) return rc;
   } else if ((rc = sums_wait(c)) || (rc = read_norm())) {

@@ -181,9 +181,15 @@ int finish_queue(lc_ctx* c, int slot, int nparts);
 double sum_of(const lc_ctx* c, int slot);
 // |D v|_V (r receives D v when not null)
 int vnorm_div(lc_ctx* c, const double* v, double* r, double* out);
-// pressure-correction solve in the given precision; after_first (may be empty) is called when its first transform
-// is queued, and ends it by returning nonzero
-int poisson(lc_ctx* c, const double* r, double* phi, int precision, const std::function<int()>& after_first = {});
+// Called once a solve has queued `at` of its kernels (1 or 2: its forward transforms; 3: all, by the caller); ends it by
+// returning nonzero.
+struct SolveHook {
+  int at = 0;
+  std::function<int()> f;
+  int operator()(int step) const { return step == at ? f() : LC_OK; }
+};
+// pressure-correction solve in the given precision
+int poisson(lc_ctx* c, const double* r, double* phi, int precision, const SolveHook& hook = {});
 // Euclidean dot product / max |x| of velocity vectors, host results
 int vdot(lc_ctx* c, const double* a, const double* b, double* out);
 int vmaxabs(lc_ctx* c, const double* a, double* out);
