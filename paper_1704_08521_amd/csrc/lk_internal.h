@@ -130,7 +130,7 @@ hipError_t launch_tpu_right(int n, int Mlines, const T* A, const T* SeT, const T
 constexpr int kMfMaxHalf = 128;
 // FP64 transforms along x of a mirror-symmetric axis of n points go by the left kernels (a line being a column whose
 // rows are neighbours), else by the kernels for lines.  The left kernels' matrix instructions are twice as
-// fast, but their reads and writes are 32-byte pieces: us a transform of a cube, left / lines, 64^3 7.6 / 9.0, 80^3
+// fast, but their reads and writes are 32-byte pieces: us a transform of a cube by events, left / lines, 64^3 7.6 / 9.0, 80^3
 // 10.1 / 11.5, 100^3 12.2 / 15.6, 120^3 16.7 / 18.1, 136^3 22 / 28, 150^3 25 / 31, 200^3 58 / 62, 201^3 61 / 67.
 // Lines that start on 128-byte boundaries all meet the same few places of the caches: 96^3 16 / 14, 112^3 20 / 16,
 // 128^3 21 / 17, 176^3 41 / 36, 208^3 70 / 68 (32^3 to 80^3 as the others).  From 161 to 192 points the

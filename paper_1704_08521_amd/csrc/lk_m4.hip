@@ -34,7 +34,7 @@ typedef float F4 __attribute__((ext_vector_type(4)));
 typedef float F2 __attribute__((ext_vector_type(2)));
 typedef unsigned U2 __attribute__((ext_vector_type(2)));
 
-// v / a for the eigenvalue scaling, a > 0: hardware reciprocal and one Newton step
+// v / a for the eigenvalue scaling, a not zero: hardware reciprocal and one Newton step
 __device__ __forceinline__ float m4_div(float v, double a) {
   const float af = (float)a;
   float y = __builtin_amdgcn_rcpf(af);

@@ -31,7 +31,7 @@ namespace {
 typedef unsigned U2 __attribute__((ext_vector_type(2)));
 typedef double D2 __attribute__((ext_vector_type(2)));
 
-// v / a, a > 0: hardware reciprocal refined by two Newton steps and one residual correction of
+// v / a, a not zero (the eigenvalue sums of the pressure are negative): hardware reciprocal refined by two Newton steps and one residual correction of
 // the quotient (within an ulp of v / a, a third of the instructions of the IEEE sequence).
 __device__ __forceinline__ double mx_div(double v, double a) {
   double y = __builtin_amdgcn_rcp(a);
@@ -243,15 +243,16 @@ hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, si
   // Groups per class, column tiles and ring by the number of row groups G (of n = 8 G points) and the columns.  Up
   // to n = 120 the columns of a cube are few: narrow waves and more classes fill the chip (100^3: 7.3 us a
   // transform; 13 groups in one class of 2 tiles 12), and so they do for any length with up to about 10000 columns
-  // (64, 2500 and 10000 columns of 200: 12, 11 and 22 us; the wide variant 26, 28 and 26; of 256: 13, 18 and 32
-  // against 37, 42 and 35; 16384 columns of 200 and 256: 26 and 43 against 27 and 36).  At n = 128 two
+  // (these and the cubes with two figures by events on the stream, 2 to 3 us above the kernel's own time:
+  // 64, 3000 and 10000 columns of 200: 11, 11 and 21 us; the wide variant 26, 28 and 25; of 256: 13, 16 and 31
+  // against 37, 41 and 34; 16384 columns of 200 and 256: 26 and 43 against 26 and 35).  At n = 128 two
   // classes of 8 groups (128^3 14.4 and 18.2 us along y and z, 10 groups 15.7 and 19.6).  From there the data is read
   // once or twice and wider waves save reads of the pieces (150^3: 16 us; 3 classes 18); blocks of up to 16
   // waves, four per SIMD, hold all of 160^3 at once (27 and 30 us; blocks of 12, whose last few
   // made a second round, 36 and 41).  The last three need their registers for the accumulators: W = 2 halves the
-  // LDS reads, which else bound them (200^3 42 against 45 us), at three waves per SIMD (n <= 208; classes of 11 groups up to 176, where
-  // two of 13 have more rows to spare: 176^3 29 and 34 us against 33 and 37) or two (256^3: 92 us; narrower
-  // classes 97-125).  With 13 groups one to three vector registers are spilled; smaller chunks of pieces change neither
+  // LDS reads, which else bound them (200^3 42 against 45 us side by side; other runs 44-46), at three waves per SIMD
+  // (n <= 208; classes of 11 groups up to 176, where two of 13 have more rows to spare: 176^3 29 and 34 us
+  // against 33 and 37) or two (256^3: 92 us; narrower classes 97-125).  With 13 groups one to three vector registers are spilled; smaller chunks of pieces change neither
   // that nor the time.
 #define MX(GT, W, PD, CH, MAXW, OCC) \
   return mx_launch<GT, W, PD, CH, MAXW, OCC, FORM>(n, N, P, B, C, elems, nseg, seg_stride, kstride, sc, st)

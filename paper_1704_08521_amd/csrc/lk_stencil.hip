@@ -38,15 +38,15 @@ __device__ __forceinline__ int xcd_tile(int bid, int nb) {
 // residual, the lid velocity at z = 1 (eq. 4).  With these ghosts the wall fluxes of the
 // Laplacian ((first - wall)/half width) and the vanishing edge fluxes on walls follow from the
 // interior formulas, so the compute has no wall branches.
-// What bounds it: at 200^3 it moves 657 MB (111 us at the 5.9 TB/s that a kernel reading two
-// fields and writing one reaches), issues about 60 us of vector instructions at two waves per
-// SIMD, and its loads and stores take the address unit about 35 us (16 cycles per load
-// instruction of a CU whether a lane asks for 8 or 16 bytes, hence the pairs).  Measured, against
-// 16 x 8 tiles whose threads each took one face and all neighbours from LDS: 16^3 11 against 32 us,
-// 64^3 17 / 28, 100^3 24 / 35, 150^3 69 / 88, 200^3 153 / 181 (3.8 TB/s of 3 fields), 256^3 283 / 354;
-// 97 x 121 x 65 22 / 32.  Rows of 64 lanes leave more of them idle (150^3 85 us), rows of 16 do
-// more halo work (200^3 163 us); everything in registers with no LDS (8-byte loads of every
-// neighbouring row) is bound by the address unit: 189 us with two rows per wave, 218 us with one.
+// What bounds it: at 200^3 it moves 701 MB (502 read, where its two input fields are 386, and 200
+// written; 119 us at the 5.9 TB/s that a kernel reading two fields and writing one reaches), issues about 60 us
+// of vector instructions at two waves per SIMD, and its loads and stores take the address unit about 35
+// us (16 cycles per load instruction of a CU whether a lane asks for 8 or 16 bytes, hence the pairs): 161 us
+// by kernel trace.  Within a Krylov vector, by events on the stream (which add 2 to 3 us), against 16 x 8 tiles
+// whose threads each took one face and all neighbours from LDS: 16^3 9-12 / 31 us, 64^3 15-17 / 29, 100^3 24-26 /
+// 35, 150^3 70-73 / 85, 200^3 171-177 / 182, 256^3 315 / 360; 97 x 121 x 65 21-24 / 30.  Rows of 64 lanes leave
+// more of them idle (150^3 85 us alone, 69 with 32); everything in registers with no LDS (8-byte loads of every
+// neighbouring row) is bound by the address unit: 189 us at 200^3 with two rows per wave, 218 us with one, 153 here.
 
 typedef double D2 __attribute__((ext_vector_type(2)));
 typedef unsigned U2 __attribute__((ext_vector_type(2)));
@@ -459,8 +459,8 @@ __global__ void __launch_bounds__(kCorTX* kCorTY) k_correct(GridDev g, const dou
 // output), so D v is that of the stored field to the bit and no value passes between waves.  A
 // block marches over a chunk of planes with the next plane's loads in flight.
 // HBM bound: 2 F_u + 2 F_p, 514 MB at 200^3, where a separate certificate read v again (193 MB).
-// 200^3: 130 us (4.0 TB/s; the misses of the L2 are 604 MB) against 109 + 55 for the two kernels;
-// 100^3 17 / 14 + 9; 256^3 250 / 226 + 111; 97 x 121 x 65 15 / 13 + 8.
+// 200^3: 116 us by kernel trace (518 MB, 4.5 TB/s); by events on the stream 124 against 109 + 56 for the two
+// kernels; 100^3 17 / 14 + 9; 256^3 248 / 226 + 103; 97 x 121 x 65 15 / 12 + 9.
 constexpr int kCdL = 32;  // lanes per row
 template <bool ODD>
 __global__ void __launch_bounds__(64 * kMomWY, 4) k_correct_div(GridDev g, const double* __restrict__ w,
@@ -577,7 +577,8 @@ __global__ void __launch_bounds__(64 * kMomWY, 4) k_correct_div(GridDev g, const
 // (registers), so up to kMomSlots run at once; the number of chunks is the one whose rounds of
 // blocks, each as long as a chunk's planes and its start-up, end soonest.  Chunks stay short
 // because neighbouring blocks then read their common rows and planes at about the same time, from
-// the L2: at 256^3 13 planes 283 us, 16 to 20 292-304 us, 34 323 us; at 200^3 12 to 20 150-155 us, 34 177 us.
+// the L2 (the stencil alone): at 256^3 13 planes 283 us, 16 to 20 292-304 us, 34 323 us; at 200^3 12 to 20 150-155 us,
+// 34 177 us.
 // Small grids take chunks down to one plane (16^3 6.8 us, three planes 10.6; 64^3 14.1 / 15.9).
 constexpr int kMomSlots = 512;
 
@@ -658,7 +659,7 @@ hipError_t launch_correct(const GridDev& g, const double* w, const double* phi, 
 }
 
 // Planes per chunk of k_correct_div: a chunk reads one level of phi and w more than its planes, and
-// longer chunks read what neighbouring blocks share at more different times (200^3: 5 planes
+// longer chunks read what neighbouring blocks share at more different times (by events, 200^3: 5 planes
 // 131 us, 8 130 us, 16 and 25 142 us; 256^3 253 / 251 / 259 / 285).  Grids that would not fill the chip
 // with chunks of eight (four blocks per CU, 2 kMomSlots) take shorter ones.
 static int correct_chunk(int nx, int ny, int nz) {

@@ -23,8 +23,9 @@
 // sg = -shift >= 0, every pivot is a sum of positive terms, in the segments and across the lanes.  In FP32 the
 // error of the pressure solve falls from 5e-6 .. 6e-4 (16 to 400 cells) to 2e-7 .. 6e-7, so the FP32 form
 // often needs a pass less; in FP64 it is as before.
-// HBM bound: one read and one write of the field (128 MB, 22 us at 200^3).  Against one wave per line: 64^3 5.2 us / 7.7,
-// 100^3 10.7 / 15.6, 200^3 30 / 53, 256^3 63 / 88; FP32 100^3 8 / 12, 150^3 15 / 21.
+// HBM bound: one read and one write of the field (128 MB, 22 us at 200^3; 29.4 us by kernel trace).  By events on the
+// stream, against one wave per line with subtractions: 64^3 7 us / 9, 100^3 12 / 17, 150^3 18 / 28, 200^3 31 / 47, 256^3 61 / 76;
+// FP32 100^3 10 / 12, 150^3 16 / 22, 200^3 23 / 33.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -259,7 +260,7 @@ hipError_t launch_tridiag_x(const GridDev& g, const double* ly, const double* lz
   // Rows per lane: the smallest instance that covers the line with 16 lanes; from 208 cells on the 16 rows that this
   // would take leave no registers for the next group's loads in FP64 (256^3 69 us, 8 rows on 32 lanes 63).  Where
   // there are few lines, a wave's own chain of rows and steps is all that counts, and that is shortest with all 64 lanes
-  // on a line: 200 cells, 1024 lines 7.0 us against 10.4 (2500 lines 10.7 / 10.9, 4096 13.2 / 11.9), 128 cells 6.3
+  // on a line (by events): 200 cells, 1024 lines 7.0 us against 10.4 (2500 lines 10.7 / 10.9, 4096 13.2 / 11.9), 128 cells 6.3
   // / 8.3 (2000 lines 8.8 / 8.4); up to 64 cells no difference.  Past 256 cells 16 rows are a long chain for longer: 512
   // cells, 1024 lines 9.2 / 16, 10000 25.8 / 31.8, 20480 43 / 47, but 300 cells, 40000 lines 67 / 59.
 #define TRI(M, LPW)                                                                                                  \
