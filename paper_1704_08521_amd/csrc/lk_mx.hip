@@ -52,7 +52,7 @@ struct MxScale {
 
 enum MxForm { kFold, kUnfold, kFull };
 
-template <int GT, int W, int PD, int CHP, MxForm FORM, bool SCALE, int MAXW, int OCC>
+template <int GT, int W, int PD, int CHP, MxForm FORM, bool SCALE, int MAXW, int OCC, bool SHORT>
 __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int ho, int N, const double* __restrict__ P,
                                                             int G, int classes,
                                                             const double* __restrict__ B, double* __restrict__ C,
@@ -69,8 +69,8 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
   constexpr int NX = 8;
   const int bid = blockIdx.x, nb = gridDim.x, xcd = bid % NX, per = nb / NX, more = nb % NX;
   const int tile = (xcd < more ? xcd * (per + 1) : more * (per + 1) + (xcd - more) * per) + bid / NX;
-  const int cls = tile % classes, g0 = cls * GT;
-  const int col0 = ((tile / classes) * nw + wave) * 16 * W;
+  const int cls = SHORT ? 0 : tile % classes, g0 = cls * GT;
+  const int col0 = ((SHORT ? tile : tile / classes) * nw + wave) * 16 * W;
   const int g = lane >> 4;
   const __amdgpu_buffer_rsrc_t rin =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(B), (short)0, (int)bytes, 0x00020000);
@@ -105,8 +105,25 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
   };
 #pragma unroll
   for (int u = 0; u < PD; ++u) load(u, u);
-  // the class's pieces; groups past the matrix are zero
-  {
+  // SHORT: the ring holds every step and the class every group, so the pieces (and eigenvalues) are loaded with
+  // the data, straight into registers
+  D2 fr[SHORT ? PD : 1][GT];
+  double lr[2][SHORT ? PD : 1];
+  if constexpr (SHORT) {
+    const D2* src = (const D2*)P + (lane >> 4) * 4 + (lane & 3);
+#pragma unroll
+    for (int u = 0; u < PD; ++u) {
+#pragma unroll
+      for (int t = 0; t < GT; ++t) {
+        fr[u][t] = src[(min(u, KQ - 1) * G + min(t, G - 1)) * 16];
+        if (t >= G) fr[u][t] = D2{0.0, 0.0};
+      }
+      if (SCALE) {
+        lr[0][u] = sc.lm[min(4 * u + g, K - 1)];
+        lr[1][u] = sc.lm[min(he + 4 * u + g, n - 1)];
+      }
+    }
+  } else {  // the class's pieces; groups past the matrix are zero
     const D2* src = (const D2*)P;
     const int total = KQ * GT * 16, step = blockDim.x;
     constexpr int NB = 8;
@@ -124,12 +141,12 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
     }
   }
   double* lam = (double*)(lds + (KQ + 1) * GT * 16);
-  if (SCALE)
+  if (SCALE && !SHORT)
     for (int k = tid; k < 4 * KQ; k += blockDim.x) {
       lam[k] = k < K ? sc.lm[k] : 1.0;
       if (!FULL) lam[4 * KQ + k] = k < ho ? sc.lm[he + k] : 1.0;
     }
-  __syncthreads();
+  if (!SHORT) __syncthreads();
   if (col0 >= N) return;
 
   double ae[GT][W], ao[GT][W];
@@ -146,7 +163,7 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
   auto pieces = [&](int q, int kq, int ch) {
 #pragma unroll
     for (int t = 0; t < CH; ++t)
-      if (ch * CH + t < GT) f[q][t] = pl[(kq * GT + ch * CH + t) * 16];
+      if (ch * CH + t < GT) f[q][t] = SHORT ? fr[min(kq, PD - 1)][ch * CH + t] : pl[(kq * GT + ch * CH + t) * 16];
   };
   auto step = [&](int u, int kq) {
     double s[W], d[W];
@@ -157,8 +174,8 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
         s[c] = x1[u][c] + x2[u][c];
         d[c] = x1[u][c] - x2[u][c];
       } else if (SCALE) {  // padding and the constant mode stay exactly zero (no 0 / 0)
-        s[c] = (k >= K || (zc[c] && k == sc.zm)) ? 0.0 : mx_div(x1[u][c], lam[k] + sxy[c]);
-        d[c] = FULL ? s[c] : (k >= ho || (zc[c] && he + k == sc.zm)) ? 0.0 : mx_div(x2[u][c], lam[4 * KQ + k] + sxy[c]);
+        s[c] = (k >= K || (zc[c] && k == sc.zm)) ? 0.0 : mx_div(x1[u][c], (SHORT ? lr[0][u] : lam[k]) + sxy[c]);
+        d[c] = FULL ? s[c] : (k >= ho || (zc[c] && he + k == sc.zm)) ? 0.0 : mx_div(x2[u][c], (SHORT ? lr[1][u] : lam[4 * KQ + k]) + sxy[c]);
       } else {
         s[c] = x1[u][c];
         d[c] = FULL ? s[c] : x2[u][c];
@@ -184,16 +201,17 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
   static_assert(PD * NCH % 2 == 0, "the two piece buffers alternate across the ring");
   pieces(0, 0, 0);
   int kq = 0;
-  for (; kq + PD <= KQ; kq += PD) {
+  if (!SHORT)
+    for (; kq + PD <= KQ; kq += PD) {
 #pragma unroll
-    for (int u = 0; u < PD; ++u) {
-      step(u, kq + u);
-      load(u, kq + u + PD);
+      for (int u = 0; u < PD; ++u) {
+        step(u, kq + u);
+        load(u, kq + u + PD);
+      }
     }
-  }
 #pragma unroll
-  for (int u = 0; u < PD - 1; ++u)
-    if (kq + u < KQ) step(u, kq + u);
+  for (int u = 0; u < (SHORT ? PD : PD - 1); ++u)
+    if (kq + u < KQ) step(u, SHORT ? u : kq + u);
 
   auto put = [&](double x, unsigned ofs) {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, x), rout, (int)ofs, 0, 0);
@@ -212,12 +230,13 @@ __global__ void __launch_bounds__(64 * MAXW, OCC) k_mx_left(int n, int he, int h
   }
 }
 
-template <int GT, int W, int PD, int CH, int MAXW, int OCC, MxForm FORM>
+template <int GT, int W, int PD, int CH, int MAXW, int OCC, MxForm FORM, bool SHORT>
 hipError_t mx_launch(int n, int N, const double* P, const double* B, double* C, size_t elems, int nseg,
                      long seg_stride, long kstride, const MxScale* sc, hipStream_t st) {
   const int he = (n + 1) / 2, ho = n / 2, G = (he + 3) / 4, classes = (G + GT - 1) / GT;
   const int KQ = FORM == kFull ? (n + 3) / 4 : G;
-  const size_t lds = (size_t)(2 * (KQ + 1) * GT * 16 + (sc ? 8 * KQ : 0)) * sizeof(double);
+  if (SHORT && (KQ > PD || G > GT)) return hipErrorInvalidValue;
+  const size_t lds = SHORT ? 0 : (size_t)(2 * (KQ + 1) * GT * 16 + (sc ? 8 * KQ : 0)) * sizeof(double);
   const long tiles = (N + 16 * W - 1) / (16 * W);
   // one block per CU where the waves of all classes fit the chip, else blocks of the full size
   const int nw = (int)std::min<long>(MAXW, std::max<long>(1, (tiles * classes + 255) / 256));
@@ -232,8 +251,8 @@ hipError_t mx_launch(int n, int N, const double* P, const double* B, double* C, 
     return hipGetLastError();
   };
   if constexpr (FORM != kFold)
-    if (sc) return run(k_mx_left<GT, W, PD, CH, FORM, true, MAXW, OCC>);
-  return run(k_mx_left<GT, W, PD, CH, FORM, false, MAXW, OCC>);
+    if (sc) return run(k_mx_left<GT, W, PD, CH, FORM, true, MAXW, OCC, SHORT>);
+  return run(k_mx_left<GT, W, PD, CH, FORM, false, MAXW, OCC, SHORT>);
 }
 
 template <MxForm FORM>
@@ -254,18 +273,25 @@ hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, si
   // (n <= 208; classes of 11 groups up to 176, where two of 13 have more rows to spare: 176^3 29 and 34 us
   // against 33 and 37) or two (256^3: 92 us; narrower classes 97-125).  With 13 groups one to three vector registers are spilled; smaller chunks of pieces change neither
   // that nor the time.
-#define MX(GT, W, PD, CH, MAXW, OCC) \
-  return mx_launch<GT, W, PD, CH, MAXW, OCC, FORM>(n, N, P, B, C, elems, nseg, seg_stride, kstride, sc, st)
+  // Lines of up to 32 points (16 with the full matrix) have so few pieces that the way through LDS costs more than it
+  // saves: a launch at 8^3 and 16^3 takes 2.2 and 2.8 us by kernel trace, through LDS 2.8 and 3.6.
+#define MX(...) MX_LAUNCH(false, __VA_ARGS__)
+#define MX_SHORT(...) MX_LAUNCH(true, __VA_ARGS__)
+#define MX_LAUNCH(SHORT, GT, W, PD, CH, MAXW, OCC) \
+  return mx_launch<GT, W, PD, CH, MAXW, OCC, FORM, SHORT>(n, N, P, B, C, elems, nseg, seg_stride, kstride, sc, st)
   if constexpr (FORM == kFull) {
     // Twice the products of the folded form, so the matrix cores bound it (97 x 121 x 65: 10.6 us a
     // transform against 23 and 15 us on the vector units).  The same reasons choose the variant: few
     // columns up to n = 136 (cubes of 100 and 130: 12 and 25 us; 5 groups of 2 tiles 11 and 29), then two
     // tiles a wave (160^3 36 us, 200^3 87; one tile 43 and 112), and at the end half as many classes
     // (256^3 197 us; 5 groups 225).
+    if (G <= 2) MX_SHORT(2, 1, 4, 2, 4, 4);
     if (G <= 17) MX(4, 1, 4, 4, 4, 4);
     if (G <= 26) MX(5, 2, 4, 5, 8, 3);
     MX(8, 2, 4, 4, 8, 2);
   } else {
+    if (G <= 2) MX_SHORT(2, 1, 2, 2, 4, 4);
+    if (G <= 4) MX_SHORT(4, 1, 4, 4, 4, 4);
     if (G <= 8) MX(4, 1, 4, 4, 4, 4);
     if (G <= 15 || N <= 10000) MX(5, 1, 4, 5, 4, 4);
     if (G <= 16) MX(8, 1, 4, 4, 4, 4);
@@ -275,6 +301,8 @@ hipError_t mx_pick(int n, int N, const double* P, const double* B, double* C, si
     MX(16, 2, 2, 4, 8, 2);
   }
 #undef MX
+#undef MX_SHORT
+#undef MX_LAUNCH
 }
 
 }  // namespace
