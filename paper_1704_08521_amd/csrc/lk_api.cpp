@@ -689,8 +689,9 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   // guess it is read while the pass's solve is under way, which needs D w but not its norm and writes nothing of the
   // caller's; the GPU must not run dry before the host has queued more, and an input without divergence
   // pays for what is queued: the whole solve up to 64^3 (read after the first transform, 16^3 to 64^3 lose
-  // 5 to 8 us of 58 to 70), two transforms up to 150^3, one beyond.  (Axes without the matrix cores have long
-  // transforms, 300 points, 256 columns 57 us: none.)
+  // 5 to 8 us of 58 to 70), two transforms up to 150^3, one beyond.  Long axes take long enough by themselves (16 x 16
+  // x 300 one-sided, input without divergence: 65 us if read after the first transform, 235 after the solve), and
+  // those without the matrix cores even in the first one (300 points, 256 columns 57 us): it waits before them.
   double n0 = 0.0;
   auto read_norm = [&]() -> int {
     n0 = std::sqrt(sum_of(c, 0));
@@ -698,10 +699,12 @@ int project_impl(lc_ctx* c, const double* w, double* v, double* p, int precision
   };
   const AxisModes& first = c->modes[uses_tridiag(c) ? 1 : 0];
   const bool ahead = precision != LC_LEARNED && (first.mf || (first.full64 && precision == LC_FP64));
+  const int longest = std::max(uses_tridiag(c) ? 0 : c->nx, std::max(c->ny, c->nz));
+  const int queued = c->ncell <= 300000 && longest <= 100 ? 3 : c->ncell <= 3500000 && longest <= 160 ? 2 : 1;
   if ((rc = div_queue(c, w, c->r, 0, ahead))) return rc;
   if (ahead) {
     constexpr int kNoPass = 2;
-    rc = pass(false, {c->ncell <= 300000 ? 3 : c->ncell <= 3500000 ? 2 : 1, [&]() -> int {
+    rc = pass(false, {queued, [&]() -> int {
       if (const int e = watched_wait(c, 0)) return e;
       if (const int e = read_norm()) {
         HIPCHK(c, hipStreamSynchronize(c->stream));
