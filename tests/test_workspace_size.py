@@ -1,5 +1,5 @@
 """A caller's block keeps its use: the workspace of a context (lc_workspace_query) does not outgrow the sizes that
-earlier builds of the library asked for, which a program may have fixed.  Host only."""
+earlier versions of the library asked for, which a program may have fixed.  Host only."""
 import ctypes as C
 
 import pytest
